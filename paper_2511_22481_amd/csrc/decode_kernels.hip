@@ -101,25 +101,36 @@ __device__ __forceinline__ void settle_o(f32x16 (&acc)[kV / 32]) {
 // with r = that exact maximum, which cannot overflow.
 constexpr float kRefSlack = 64.f;
 
-// One head row of one (sequence, head block) that was cut into nslots partial results:
-// out = sum_s w_s O_s with w_s = exp(lse_s - lse), lse = log sum_s exp(lse_s).  One wave per
-// row, 64 lanes x 8 columns.  Partials are taken four at a time, all their loads in flight
-// together, and folded into a running (maximum, sum, row) triple, so any number of partials
-// takes one pass.  hl: the row inside the head block; orow: the row of out / lse.
+// A running merge of partial results of one head row: out = sum_s w_s O_s with
+// w_s = exp(lse_s - lse), lse = log sum_s exp(lse_s), kept as (maximum, sum, row), the lane
+// holding 8 of the row's 512 columns.
+struct MergeState {
+  float m, z, o[8];
+  __device__ __forceinline__ void rescale(float mb) {  // mb >= m, finite
+    const float keep = __expf(m - mb);  // 0 as long as nothing was folded in (m = -inf)
+    z *= keep;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) o[c] *= keep;
+    m = mb;
+  }
+};
+
+// Slots slot0 + first, + first + stride, ... of a row's nslots partials, four at a time with all
+// their loads in flight, so any number of partials takes one pass.  hl: the row inside the head block.
 template <bool OUT_FP32>
-__device__ __forceinline__ void merge_row(const void* part_o, const float* part_lse, int slot0, int nslots,
-                                          int head_block, int hl, int lane, void* out, float* lse_out, size_t orow) {
+__device__ __forceinline__ MergeState merge_slots(const void* part_o, const float* part_lse, int slot0, int nslots,
+                                                  int first, int stride, int head_block, int hl, int lane) {
   constexpr int kBatch = 4;
-  float m = -INFINITY, z = 0.f;
-  float o[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int s0 = 0; s0 < nslots; s0 += kBatch) {
+  MergeState r = {-INFINITY, 0.f, {0, 0, 0, 0, 0, 0, 0, 0}};
+  for (int s0 = first; s0 < nslots; s0 += kBatch * stride) {
     float l[kBatch];
     f32x4 ra[kBatch], rb[kBatch];
     bf16x8 rh[kBatch];
 #pragma unroll
     for (int k = 0; k < kBatch; ++k) {
-      const bool ok = s0 + k < nslots;
-      const size_t row = (size_t)(slot0 + (ok ? s0 + k : 0)) * head_block + hl;
+      const int s = s0 + k * stride;
+      const bool ok = s < nslots;
+      const size_t row = (size_t)(slot0 + (ok ? s : s0)) * head_block + hl;
       l[k] = ok ? part_lse[row] : -INFINITY;
       if constexpr (OUT_FP32) {
         const f32x4* src = (const f32x4*)((const float*)part_o + row * kV + lane * 8);
@@ -129,41 +140,42 @@ __device__ __forceinline__ void merge_row(const void* part_o, const float* part_
         rh[k] = *(const bf16x8*)((const uint16_t*)part_o + row * kV + lane * 8);
       }
     }
-    float mb = m;
+    float mb = r.m;
 #pragma unroll
     for (int k = 0; k < kBatch; ++k) mb = fmaxf(mb, l[k]);
     if (mb == -INFINITY) continue;  // nothing but empty partials so far
-    const float keep = __expf(m - mb);  // 0 on the first batch (m = -inf)
-    z *= keep;
-#pragma unroll
-    for (int c = 0; c < 8; ++c) o[c] *= keep;
+    r.rescale(mb);
 #pragma unroll
     for (int k = 0; k < kBatch; ++k) {
       const float w = __expf(l[k] - mb);  // 0 for a slot past the end
-      z += w;
+      r.z += w;
       if constexpr (OUT_FP32) {
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-          o[c] = fmaf(w, ra[k][c], o[c]);
-          o[4 + c] = fmaf(w, rb[k][c], o[4 + c]);
+          r.o[c] = fmaf(w, ra[k][c], r.o[c]);
+          r.o[4 + c] = fmaf(w, rb[k][c], r.o[4 + c]);
         }
       } else {
 #pragma unroll
-        for (int c = 0; c < 8; ++c) o[c] = fmaf(w, (float)rh[k][c], o[c]);
+        for (int c = 0; c < 8; ++c) r.o[c] = fmaf(w, (float)rh[k][c], r.o[c]);
       }
     }
-    m = mb;
   }
-  const float inv = z > 0.f ? 1.0f / z : 0.f;
-  if (lane == 0) lse_out[orow] = z > 0.f ? m + __logf(z) : -INFINITY;
+  return r;
+}
+
+template <bool OUT_FP32>
+__device__ __forceinline__ void write_merged(const MergeState& r, int lane, void* out, float* lse_out, size_t orow) {
+  const float inv = r.z > 0.f ? 1.0f / r.z : 0.f;
+  if (lane == 0) lse_out[orow] = r.z > 0.f ? r.m + __logf(r.z) : -INFINITY;
   if constexpr (OUT_FP32) {
     float* dst = (float*)out + orow * kV + lane * 8;
-    *(f32x4*)dst = f32x4{o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv};
-    *(f32x4*)(dst + 4) = f32x4{o[4] * inv, o[5] * inv, o[6] * inv, o[7] * inv};
+    *(f32x4*)dst = f32x4{r.o[0] * inv, r.o[1] * inv, r.o[2] * inv, r.o[3] * inv};
+    *(f32x4*)(dst + 4) = f32x4{r.o[4] * inv, r.o[5] * inv, r.o[6] * inv, r.o[7] * inv};
   } else {
     bf16x8 v;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = (__bf16)(o[k] * inv);
+    for (int k = 0; k < 8; ++k) v[k] = (__bf16)(r.o[k] * inv);
     *(bf16x8*)((uint16_t*)out + orow * kV + lane * 8) = v;
   }
 }
@@ -750,18 +762,51 @@ __global__ __launch_bounds__(WAVES * 64, 1) void decode_kernel(DecodeParams p) {
   }
 }
 
-// Merge the partial results of one (sequence, head block): one work group per
-// (combine item, group of 4 heads), one wave per head row (see merge_row).
+// Merge the partial results of one (sequence, head block): one work group per (combine item,
+// group of 4 / WPR heads), WPR waves per head row.  With few partials a wave takes a whole
+// row: one or two round trips to memory, and the kernel is bound by the bytes it moves.  More partials of
+// few sequences (a single sequence of 2176 kept tokens is cut into 69) are bound by the chain of
+// such round trips, so four waves share a row, each every fourth slot, and their sums meet in LDS.
 // One instance per output type: with both in one kernel the registers of the fp32 path
 // cost the bf16 path a third of its waves in flight, and this kernel lives on those.
-template <bool OUT_FP32>
+template <bool OUT_FP32, int WPR>
 __global__ __launch_bounds__(256) void combine_kernel(CombineParams p) {
+  constexpr int kRows = 4 / WPR;
   const CombineItem it = p.items[blockIdx.x];
-  const int hl = blockIdx.y * 4 + (threadIdx.x >> 6);
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int hl = blockIdx.y * kRows + wave / WPR, part = wave % WPR;
   const int head = it.hb * p.head_block + hl;
-  if (hl >= p.head_block || head >= p.H) return;
-  merge_row<OUT_FP32>(p.part_o, p.part_lse, it.slot0, it.nslots, p.head_block, hl, threadIdx.x & 63, p.out, p.lse,
-                      (size_t)it.b * p.H + head);
+  if (hl >= p.head_block || head >= p.H) return;  // (WPR > 1: for all waves of a row, and kRows is 1)
+  MergeState r = merge_slots<OUT_FP32>(p.part_o, p.part_lse, it.slot0, it.nslots, part, WPR, p.head_block, hl, lane);
+  if constexpr (WPR > 1) {
+    static_assert(kRows == 1);
+    __shared__ float sh_mz[WPR][2];
+    __shared__ f32x4 sh_o[WPR][2][64];
+    if (part > 0) {
+      if (lane == 0) {
+        sh_mz[part][0] = r.m;
+        sh_mz[part][1] = r.z;
+      }
+      sh_o[part][0][lane] = f32x4{r.o[0], r.o[1], r.o[2], r.o[3]};
+      sh_o[part][1][lane] = f32x4{r.o[4], r.o[5], r.o[6], r.o[7]};
+    }
+    __syncthreads();
+    if (part > 0) return;
+    float mb = r.m;
+#pragma unroll
+    for (int k = 1; k < WPR; ++k) mb = fmaxf(mb, sh_mz[k][0]);
+    if (mb != -INFINITY) {
+      r.rescale(mb);
+#pragma unroll
+      for (int k = 1; k < WPR; ++k) {
+        const float w = __expf(sh_mz[k][0] - mb);
+        r.z = fmaf(w, sh_mz[k][1], r.z);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) r.o[c] = fmaf(w, sh_o[k][c >> 2][lane][c & 3], r.o[c]);
+      }
+    }
+  }
+  write_merged<OUT_FP32>(r, lane, p.out, p.lse, (size_t)it.b * p.H + head);
 }
 
 // Plan metadata from the plan's pinned host buffer (mapped into the device's address space)
@@ -799,11 +844,24 @@ hipError_t launch_decode(const DecodeParams& p, int waves, int n_units, hipStrea
   return hipGetLastError();
 }
 
+// Four waves to a row from nine partials on: 69 partials of one sequence 32.8 -> 23.9 us per decode, 9
+// partials of four sequences 15.6 -> 14.4; with 8 or 6 partials of 32 to 40 sequences of 128 heads the
+// rows alone fill the chip and the exchange costs 1 us.
+constexpr int kWideSlots = 8;
+
 hipError_t launch_combine(const CombineParams& p, int n_items, hipStream_t stream) {
   if (n_items <= 0) return hipSuccess;
-  dim3 grid(n_items, (p.head_block + 3) / 4), block(256);
-  if (p.out_fp32) hipLaunchKernelGGL(combine_kernel<true>, grid, block, 0, stream, p);
-  else hipLaunchKernelGGL(combine_kernel<false>, grid, block, 0, stream, p);
+  const int rows = p.head_block < p.H ? p.head_block : p.H;
+  const dim3 block(256);
+  if (p.max_slots > kWideSlots) {
+    const dim3 grid(n_items, rows);
+    if (p.out_fp32) hipLaunchKernelGGL((combine_kernel<true, 4>), grid, block, 0, stream, p);
+    else hipLaunchKernelGGL((combine_kernel<false, 4>), grid, block, 0, stream, p);
+  } else {
+    const dim3 grid(n_items, (rows + 3) / 4);
+    if (p.out_fp32) hipLaunchKernelGGL((combine_kernel<true, 1>), grid, block, 0, stream, p);
+    else hipLaunchKernelGGL((combine_kernel<false, 1>), grid, block, 0, stream, p);
+  }
   return hipGetLastError();
 }
 

@@ -48,6 +48,7 @@ struct CombineParams {
   void* out;
   float* lse;
   int H, head_block, out_fp32, n_items;
+  int max_slots;  // most partials any item has
 };
 
 struct AppendParams {

@@ -3,7 +3,10 @@
 
 #include <algorithm>
 #include <climits>
+#include <cmath>
 #include <cstring>
+#include <functional>
+#include <utility>
 
 namespace omniattn {
 
@@ -13,37 +16,48 @@ struct Item {
   int b, hb, ntiles;
 };
 
-// A segment carries a fixed cost (loading the query block, writing a result)
-// worth about this many KV tiles.
-constexpr int kSegFixedCost = 1;
+// What a partition costs, in units of one KV tile's time in the long loop (measured on MI355X
+// with time stamps in the kernels at 128 heads; a tile takes 1.8 us in the bf16 kernel and 3.4 us
+// in the fp8 one when all compute units work):
+//   seg      a segment behind another one in the same unit: page-table entries, query block,
+//            first tile, last PV, result rows (9 us / 13 us);
+//   combine  the second launch that merges partial rows, with the gap in front of it (6 us), and
+//   slots_per_tile  partial rows of how many slots are written and read back in a tile's time by
+//            the whole chip (262 KB each at 5 TB/s).
+struct PartitionCost {
+  int seg;
+  double combine;
+  double slots_per_tile;
+};
+constexpr PartitionCost kCostBf16 = {5, 3.3, 36.0};
+constexpr PartitionCost kCostFp8 = {4, 1.8, 65.0};
 // Do not leave slivers shorter than this many tiles unless the item itself is shorter.
 constexpr int kMinSegTiles = 2;
 
-// Greedy fill of units of capacity `cap`; returns the number of units used.
-int fill_units(const std::vector<Item>& items, int cap, std::vector<Segment>* segs_out,
-               std::vector<int32_t>* unit_seg_out) {
-  std::vector<Segment> segs;
-  std::vector<int32_t> unit_seg;
-  unit_seg.push_back(0);
-  int load = 0;
+// Deals the items in order to units of capacity `cap` (tiles plus `seg` per segment), cutting an
+// item where a unit is full.  emit(item, tile_lo, tile_hi, unit) for every segment; returns the
+// number of units used.
+template <typename Emit>
+int fill_units(const std::vector<Item>& items, int cap, int seg, Emit emit) {
+  int load = 0, unit = 0;
   auto close_unit = [&]() {
-    if ((int)segs.size() > unit_seg.back()) {
-      unit_seg.push_back((int32_t)segs.size());
+    if (load > 0) {
+      ++unit;
       load = 0;
     }
   };
   for (const Item& it : items) {
-    int done = 0;
     if (it.ntiles == 0) {  // empty retained set: one segment that only writes zeros / -inf
-      if (load + kSegFixedCost > cap) close_unit();
-      segs.push_back({it.b, it.hb, 0, 0, -1, (int32_t)unit_seg.size() - 1, 0, 0});
-      load += kSegFixedCost;
+      if (load + seg > cap) close_unit();
+      emit(it, 0, 0, unit);
+      load += seg;
       continue;
     }
+    int done = 0;
     while (done < it.ntiles) {
-      int rem = it.ntiles - done;
-      int room = cap - load - kSegFixedCost;
-      int need = std::min(rem, kMinSegTiles);
+      const int rem = it.ntiles - done;
+      int room = cap - load - seg;
+      const int need = std::min(rem, kMinSegTiles);
       if (room < need) {
         if (load == 0) room = need;  // capacity smaller than one minimal segment
         else { close_unit(); continue; }
@@ -51,20 +65,156 @@ int fill_units(const std::vector<Item>& items, int cap, std::vector<Segment>* se
       int take = std::min(std::min(rem, room), kMaxSegTiles);
       // avoid leaving a sliver behind
       if (rem - take > 0 && rem - take < kMinSegTiles) take = std::max(1, rem - kMinSegTiles);
-      segs.push_back({it.b, it.hb, done, done + take, -1, (int32_t)unit_seg.size() - 1, 0,
-                      it.ntiles});
+      emit(it, done, done + take, unit);
       done += take;
-      load += take + kSegFixedCost;
+      load += take + seg;
       if (load >= cap) close_unit();
     }
   }
   close_unit();
-  int n_units = (int)unit_seg.size() - 1;
-  if (segs_out) {
-    *segs_out = std::move(segs);
-    *unit_seg_out = std::move(unit_seg);
+  return unit;
+}
+
+// Work partition over `num_cus` compute units that all start together: the launch lasts as long
+// as its longest unit, and one more launch follows if any item was cut.  Three shapes are
+// estimated with the costs above and the cheapest is taken:
+//   whole  items dealt whole, largest first, to the unit with the least work: nothing to merge.
+//          Wins when items of one size come close to a multiple of the unit count (256 sequences
+//          of 133 tiles on 256 units: 137 against 143 + merge);
+//   even   every item cut into equal pieces, one piece per unit: wins for a few equal items (32
+//          sequences of 130 tiles: eight pieces of 16 or 17, where filling units to the brim
+//          leaves some with the ends of two sequences, which cost them a second start);
+//   fill   units filled one after the other to the same load, items cut wherever that falls: wins
+//          when the item count is not near a multiple or divisor of the unit count.
+//
+// `most_slots`: partial slots that fit the built-in scratch buffer.  Even pieces are not cut so
+// short that omniattn_decode_static would refuse the plan.
+void partition(const std::vector<Item>& items, int num_cus, const PartitionCost& cost, int most_slots,
+               std::vector<Segment>& segs, std::vector<int32_t>& unit_seg) {
+  const int n = (int)items.size();
+  int64_t total = 0;
+  int n_max = 0;
+  for (const Item& it : items) {
+    total += it.ntiles + cost.seg;
+    n_max = std::max(n_max, it.ntiles);
   }
-  return n_units;
+  auto merge_cost = [&](int slots) { return slots ? cost.combine + slots / cost.slots_per_tile : 0.0; };
+
+  // fill: the smallest capacity that needs no more units than there are
+  int lo = std::max((int)std::min<int64_t>((total + num_cus - 1) / num_cus, INT32_MAX / 2), cost.seg + 1), fill_cap = lo;
+  auto units_at = [&](int cap) { return fill_units(items, cap, cost.seg, [](const Item&, int, int, int) {}); };
+  if (units_at(lo) > num_cus) {
+    int step = 1;
+    while (units_at(lo + step) > num_cus && step < (1 << 28)) step *= 2;
+    int bad = lo + step / 2, good = lo + step;
+    while (good - bad > 1) {
+      const int mid = bad + (good - bad) / 2;
+      (units_at(mid) > num_cus ? bad : good) = mid;
+    }
+    fill_cap = good;
+  }
+  double best;
+  {
+    int slots = 0, longest = 0, load = 0, last_unit = -1;
+    fill_units(items, fill_cap, cost.seg, [&](const Item& it, int a, int b, int unit) {
+      if (b - a < it.ntiles) ++slots;
+      load = (unit == last_unit ? load : 0) + b - a + cost.seg;
+      last_unit = unit;
+      longest = std::max(longest, load);
+    });
+    best = longest + merge_cost(slots);
+  }
+  enum { kFill, kWhole, kEven } shape = kFill;
+
+  // whole (a segment's tile table holds kMaxSegTiles)
+  std::vector<int32_t> unit_of;
+  if (n_max <= kMaxSegTiles && n_max + cost.seg < best) {
+    std::vector<int32_t> order(n);
+    for (int i = 0; i < n; ++i) order[i] = i;
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return items[a].ntiles > items[b].ntiles; });
+    unit_of.resize(n);
+    std::vector<std::pair<int32_t, int32_t>> heap;  // (load, unit), least loaded on top
+    const auto later = std::greater<std::pair<int32_t, int32_t>>();
+    int longest = 0;
+    for (int i = 0; i < n && longest < best; ++i) {
+      const int cost_i = items[order[i]].ntiles + cost.seg;
+      int unit = i, load = cost_i;
+      if (i < num_cus) {
+        heap.emplace_back(load, unit);
+        if (i == num_cus - 1 || i == n - 1) std::make_heap(heap.begin(), heap.end(), later);
+      } else {
+        std::pop_heap(heap.begin(), heap.end(), later);
+        unit = heap.back().second;
+        load = heap.back().first += cost_i;
+        std::push_heap(heap.begin(), heap.end(), later);
+      }
+      unit_of[order[i]] = unit;
+      longest = std::max(longest, load);
+    }
+    if (longest < best) {
+      best = longest;
+      shape = kWhole;
+    }
+  }
+  // even: the smallest piece that needs no more pieces than there are units
+  int piece = 0;
+  if (n <= num_cus && n_max > 1) {
+    auto pieces_at = [&](int p) {
+      int64_t k = 0;
+      for (const Item& it : items) k += std::max(1, (it.ntiles + p - 1) / p);
+      return k;
+    };
+    int bad = 0, good = n_max;  // (one piece per item fits)
+    while (good - bad > 1) {
+      const int mid = bad + (good - bad) / 2;
+      (pieces_at(mid) > num_cus ? bad : good) = mid;
+    }
+    // (with few items the shortest pieces give more partial rows than they save tiles: sum / p
+    // slots cost sum / p / slots_per_tile, which balances p at the square root below)
+    const int balanced = (int)std::sqrt((double)(total - (int64_t)n * cost.seg) / cost.slots_per_tile);
+    for (int p : {good, std::max(good, balanced), 2 * good}) {
+      p = std::min({p, n_max, kMaxSegTiles});
+      if (pieces_at(p) > num_cus) continue;
+      int slots = 0;
+      for (const Item& it : items)
+        if (it.ntiles > p) slots += (it.ntiles + p - 1) / p;
+      if (slots > most_slots) continue;
+      const double t = p + cost.seg + merge_cost(slots);
+      if (t < best) {
+        best = t;
+        shape = kEven;
+        piece = p;
+      }
+    }
+  }
+
+  segs.clear();
+  unit_seg.assign(1, 0);
+  auto add = [&](const Item& it, int a, int b, int unit) {
+    while ((int)unit_seg.size() <= unit) unit_seg.push_back((int32_t)segs.size());
+    segs.push_back({it.b, it.hb, a, b, -1, unit, 0, it.ntiles});
+  };
+  if (shape == kFill) {
+    fill_units(items, fill_cap, cost.seg, add);
+  } else if (shape == kEven) {
+    int unit = 0;
+    for (const Item& it : items) {
+      const int k = std::max(1, (it.ntiles + piece - 1) / piece);
+      for (int s = 0; s < k; ++s)
+        add(it, (int)((int64_t)it.ntiles * s / k), (int)((int64_t)it.ntiles * (s + 1) / k), unit++);
+    }
+  } else {
+    // units in order, each with its items
+    const int n_units = std::min(n, num_cus);
+    std::vector<int32_t> first(n_units + 1, 0), at(n);
+    for (int i = 0; i < n; ++i) ++first[unit_of[i] + 1];
+    for (int u = 0; u < n_units; ++u) first[u + 1] += first[u];
+    std::vector<int32_t> next(first.begin(), first.end() - 1);
+    for (int i = 0; i < n; ++i) at[next[unit_of[i]]++] = i;
+    for (int u = 0; u < n_units; ++u)
+      for (int k = first[u]; k < first[u + 1]; ++k) add(items[at[k]], 0, items[at[k]].ntiles, u);
+  }
+  unit_seg.push_back((int32_t)segs.size());
 }
 
 }  // namespace
@@ -104,10 +254,11 @@ int build_host_plan(HostPlan& hp, const omniattn_problem_t& prob, const int32_t*
   hp.window_union = prob.window > 0 ? (int)std::min<int64_t>((int64_t)prob.window + q_len - 1, INT32_MAX) : 0;
   hp.n_hb = (hp.heads_total + hp.head_block - 1) / hp.head_block;
 
+  const size_t elt = prob.out_dtype == OMNIATTN_FP32 ? 4 : 2;
+  const size_t slot_bytes = (size_t)hp.head_block * (sizeof(float) + kV * elt) + 1;  // (+ 1: room for alignment)
   std::vector<Item> items;
   items.reserve((size_t)prob.batch * hp.n_hb);
   hp.retained_tokens = 0;
-  int64_t total_cost = 0;
   for (int b = 0; b < prob.batch; ++b) {
     int L = seq_lens[b];
     int64_t sink_end = std::min<int64_t>(prob.sink, L);
@@ -120,7 +271,6 @@ int build_host_plan(HostPlan& hp, const omniattn_problem_t& prob, const int32_t*
     for (int hb = 0; hb < hp.n_hb; ++hb) {
       int n = tile_layout(seq_lens[b], prob.sink, hp.window_union, hp.tile).count();
       items.push_back({b, hb, n});
-      total_cost += n + kSegFixedCost;
     }
 
   if (prob.num_splits_hint > 0) {
@@ -137,14 +287,8 @@ int build_host_plan(HostPlan& hp, const omniattn_problem_t& prob, const int32_t*
       }
     }
   } else {
-    int cap = (int)((total_cost + num_cus - 1) / num_cus);
-    cap = std::max(cap, kSegFixedCost + 1);
-    // splitting adds fixed costs, so the first capacity may need a few more units than CUs
-    for (int iter = 0; iter < 64; ++iter) {
-      if (fill_units(items, cap, nullptr, nullptr) <= num_cus) break;
-      ++cap;
-    }
-    fill_units(items, cap, &hp.segs, &hp.unit_seg);
+    partition(items, num_cus, prob.kv_dtype == OMNIATTN_FP8_E4M3 ? kCostFp8 : kCostBf16,
+              (int)(OMNIATTN_STATIC_SCRATCH_BYTES / slot_bytes), hp.segs, hp.unit_seg);
   }
 
   // partial slots for every (sequence, head block) cut into more than one segment
@@ -167,7 +311,6 @@ int build_host_plan(HostPlan& hp, const omniattn_problem_t& prob, const int32_t*
   for (Segment& s : hp.segs) s.L = seq_lens[s.b];
   // workspace: lse of every partial row (fp32), then the partial rows in the output type
   const size_t rows = (size_t)hp.n_slots * hp.head_block;
-  const size_t elt = prob.out_dtype == OMNIATTN_FP32 ? 4 : 2;
   hp.part_rows_offset = (rows * sizeof(float) + 255) & ~(size_t)255;
   hp.workspace_bytes = rows ? ((hp.part_rows_offset + rows * kV * elt + 255) & ~(size_t)255) : 0;
   return OMNIATTN_OK;
