@@ -16,6 +16,7 @@ import sys
 VALU_STATES = 12  # vector-ALU read of an 8-pass MFMA result
 MEM_STATES = 19   # memory / LDS / export instruction reading it
 MIN_STATES = VALU_STATES
+SGPR_STATES = 5   # vector instruction writes a scalar register -> vector-memory instruction reads it
 EXTRA_16_PASS = 8  # a 16-pass MFMA (the 32x32x64 8-bit one) needs this many more of each
 _MEM_PREFIXES = ("scratch_", "global_", "buffer_", "flat_", "ds_")
 
@@ -29,6 +30,18 @@ def _regs(text):
         out.update((k, i) for i in range(int(lo), int(hi) + 1))
     for k, i in _REG_ONE.findall(_REG_RANGE.sub(" ", text)):
         out.add((k, int(i)))
+    return out
+
+
+_SREG_RANGE = re.compile(r"\bs\[(\d+):(\d+)\]")
+_SREG_ONE = re.compile(r"\bs(\d+)\b")
+
+
+def _sregs(text):
+    out = set()
+    for lo, hi in _SREG_RANGE.findall(text):
+        out.update(range(int(lo), int(hi) + 1))
+    out.update(int(i) for i in _SREG_ONE.findall(_SREG_RANGE.sub(" ", text)))
     return out
 
 
@@ -50,7 +63,29 @@ def check(asm_text, kernel_filter="decode_kernel"):
             block, name = [], line
         elif line:
             block.append(line)
-    # 2. MFMA results read too early
+    # 2. scalar address of a direct global->LDS load written by a vector instruction too shortly before
+    #    (the load is inside inline assembly, so the compiler does not place the wait states)
+    in_k, age = False, {}
+    for lineno, raw in enumerate(asm_text.splitlines(), 1):
+        line = raw.split(";")[0].strip()
+        if not line:
+            continue
+        if line.endswith(":"):
+            if not line.startswith("."):
+                in_k, age = kernel_filter in line, {}
+            continue
+        if not in_k or line.startswith("."):
+            continue
+        op, _, rest = line.partition(" ")
+        if op.startswith("global_load_lds"):
+            for r in sorted(_sregs(rest)):
+                if age.get(r, SGPR_STATES) < SGPR_STATES:
+                    problems.append(f"line {lineno}: direct load reads s{r} {age[r]} states after a vector instruction wrote it: {line}")
+        for r in age:
+            age[r] += int(rest.strip()) + 1 if op == "s_nop" else 1
+        if op.startswith("v_readfirstlane") or op.startswith("v_readlane"):
+            age.update((r, 0) for r in _sregs(rest.split(",")[0]))
+    # 3. MFMA results read too early
     in_kernel = False
     pending = {}  # register -> wait states elapsed since the MFMA that writes it
     extra = {}    # register -> additional wait states its MFMA needs (16-pass)

@@ -70,6 +70,7 @@ int init_device(int dev) {
   if (g_init_done[dev]) return OMNIATTN_OK;
   hipError_t e = init_kernels();
   if (e == hipSuccess) e = init_fp8_kernel();
+  if (e == hipSuccess) e = init_narrow_kernels();
   if (e != hipSuccess) return hip_fail(e, "kernel attribute setup");
   // (the caller made `dev` current: the address is that of this device's copy)
   void* sp = nullptr;
@@ -344,7 +345,8 @@ int omniattn_decode_timed(const omniattn_plan_t* plan, const void* q, const void
   dp.scale_log2 = hp.prob.softmax_scale * 1.4426950408889634f;
   if (dp.scale_log2 == 0.f) dp.scale_log2 = 1e-30f;
   if (ev_begin) OA_HIP(hipEventRecord((hipEvent_t)ev_begin, stream));
-  if (fp8) OA_HIP(launch_decode_fp8(dp, (int)hp.unit_seg.size() - 1, stream));
+  if (hp.head_block == kHeadsPerWave) OA_HIP(launch_decode_narrow(dp, fp8, (int)hp.unit_seg.size() - 1, stream));
+  else if (fp8) OA_HIP(launch_decode_fp8(dp, (int)hp.unit_seg.size() - 1, stream));
   else OA_HIP(launch_decode(dp, hp.waves, (int)hp.unit_seg.size() - 1, stream));
   if (ev_main_end) OA_HIP(hipEventRecord((hipEvent_t)ev_main_end, stream));
 

@@ -32,9 +32,6 @@ namespace omniattn {
 
 namespace {
 
-typedef __attribute__((ext_vector_type(8))) int i32x8;
-typedef __attribute__((ext_vector_type(4))) int i32x4;
-typedef __attribute__((ext_vector_type(2))) int i32x2;
 typedef __attribute__((ext_vector_type(2))) unsigned short u16x2;
 
 constexpr int kT8 = kTileFp8;                   // tokens per tile

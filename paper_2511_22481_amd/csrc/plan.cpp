@@ -16,21 +16,27 @@ struct Item {
   int b, hb, ntiles;
 };
 
-// What a partition costs, in units of one KV tile's time in the long loop (measured on MI355X
-// with time stamps in the kernels at 128 heads; a tile takes 1.8 us in the bf16 kernel and 3.4 us
-// in the fp8 one when all compute units work):
-//   seg      a segment behind another one in the same unit: page-table entries, query block,
-//            first tile, last PV, result rows (9 us / 13 us);
-//   combine  the second launch that merges partial rows, with the gap in front of it (6 us), and
+// What a partition costs with one of the kernels (measured on MI355X):
+//   head_block  head rows per work unit;
+//   tile_us  a KV tile in the long loop when all compute units work;
+//   seg      a segment (page-table entries, query block, first tile, last PV, result rows), in tiles;
+//   combine  the second launch that merges partial rows, with the gap in front of it (6 us), in tiles;
 //   slots_per_tile  partial rows of how many slots are written and read back in a tile's time by
-//            the whole chip (262 KB each at 5 TB/s).
-struct PartitionCost {
+//            the whole chip (131 KB each per 128 rows, both ways, at 5 TB/s).
+struct KernelCost {
+  int head_block;
+  double tile_us;
   int seg;
   double combine;
   double slots_per_tile;
 };
-constexpr PartitionCost kCostBf16 = {5, 3.3, 36.0};
-constexpr PartitionCost kCostFp8 = {4, 1.8, 65.0};
+// The kernels for full head blocks: 9 us and 13 us a segment.
+constexpr KernelCost kWideBf16 = {4 * kHeadsPerWave, 1.8, 5, 3.3, 36.0};
+constexpr KernelCost kWideFp8 = {4 * kHeadsPerWave, 3.4, 4, 1.8, 65.0};
+// The kernel for blocks of 32 rows: every tile passes through once per block, but its tile and its start
+// cost less.
+constexpr KernelCost kNarrowBf16 = {kHeadsPerWave, 1.4, 4, 4.3, 112.0};
+constexpr KernelCost kNarrowFp8 = {kHeadsPerWave, 1.5, 4, 4.0, 120.0};
 // Do not leave slivers shorter than this many tiles unless the item itself is shorter.
 constexpr int kMinSegTiles = 2;
 
@@ -88,9 +94,9 @@ int fill_units(const std::vector<Item>& items, int cap, int seg, Emit emit) {
 //          when the item count is not near a multiple or divisor of the unit count.
 //
 // `most_slots`: partial slots that fit the built-in scratch buffer.  Even pieces are not cut so
-// short that omniattn_decode_static would refuse the plan.
-void partition(const std::vector<Item>& items, int num_cus, const PartitionCost& cost, int most_slots,
-               std::vector<Segment>& segs, std::vector<int32_t>& unit_seg) {
+// short that omniattn_decode_static would refuse the plan.  Returns the estimate in us.
+double partition(const std::vector<Item>& items, int num_cus, const KernelCost& cost, int most_slots,
+                 std::vector<Segment>& segs, std::vector<int32_t>& unit_seg) {
   const int n = (int)items.size();
   int64_t total = 0;
   int n_max = 0;
@@ -215,6 +221,7 @@ void partition(const std::vector<Item>& items, int num_cus, const PartitionCost&
       for (int k = first[u]; k < first[u + 1]; ++k) add(items[at[k]], 0, items[at[k]].ntiles, u);
   }
   unit_seg.push_back((int32_t)segs.size());
+  return best * cost.tile_us;
 }
 
 }  // namespace
@@ -242,9 +249,6 @@ int build_host_plan(HostPlan& hp, const omniattn_problem_t& prob, const int32_t*
   hp.prob = prob;
   hp.num_cus = num_cus;
   hp.seq_lens.assign(seq_lens, seq_lens + prob.batch);
-  // Always four waves (one per SIMD), 32 heads each; waves past the last head idle along.
-  hp.waves = 4;
-  hp.head_block = hp.waves * kHeadsPerWave;
   hp.q_len = q_len;
   hp.tile = prob.kv_dtype == OMNIATTN_FP8_E4M3 ? kTileFp8 : kTile;
   hp.heads_total = prob.num_heads * q_len;
@@ -252,28 +256,39 @@ int build_host_plan(HostPlan& hp, const omniattn_problem_t& prob, const int32_t*
   // Over all queries that is [0, S) and (for W > 0) the W + q_len - 1 positions ending at L:
   // tiles are laid out for that union, the kernel masks per query.
   hp.window_union = prob.window > 0 ? (int)std::min<int64_t>((int64_t)prob.window + q_len - 1, INT32_MAX) : 0;
-  hp.n_hb = (hp.heads_total + hp.head_block - 1) / hp.head_block;
-
   const size_t elt = prob.out_dtype == OMNIATTN_FP32 ? 4 : 2;
-  const size_t slot_bytes = (size_t)hp.head_block * (sizeof(float) + kV * elt) + 1;  // (+ 1: room for alignment)
-  std::vector<Item> items;
-  items.reserve((size_t)prob.batch * hp.n_hb);
+  std::vector<int32_t> tiles(prob.batch);
+  int64_t sum_tiles = 0;
   hp.retained_tokens = 0;
   for (int b = 0; b < prob.batch; ++b) {
     int L = seq_lens[b];
     int64_t sink_end = std::min<int64_t>(prob.sink, L);
     int64_t win_lo = std::max<int64_t>((int64_t)L - hp.window_union, 0);
     hp.retained_tokens += (win_lo <= sink_end) ? L : sink_end + (L - win_lo);
+    tiles[b] = tile_layout(L, prob.sink, hp.window_union, hp.tile).count();
+    sum_tiles += tiles[b];
   }
   // sequence-major: the head blocks of one sequence read the same tiles; as neighbours they
   // land on one XCD (see the unit mapping in the kernel) and share its L2
-  for (int b = 0; b < prob.batch; ++b)
-    for (int hb = 0; hb < hp.n_hb; ++hb) {
-      int n = tile_layout(seq_lens[b], prob.sink, hp.window_union, hp.tile).count();
-      items.push_back({b, hb, n});
-    }
+  std::vector<Item> items;
+  auto deal_heads = [&](int head_block) {
+    const int n_hb = (hp.heads_total + head_block - 1) / head_block;
+    items.clear();
+    items.reserve((size_t)prob.batch * n_hb);
+    for (int b = 0; b < prob.batch; ++b)
+      for (int hb = 0; hb < n_hb; ++hb) items.push_back({b, hb, tiles[b]});
+    hp.head_block = head_block;
+    hp.n_hb = n_hb;
+  };
 
+  const bool fp8 = prob.kv_dtype == OMNIATTN_FP8_E4M3;
+  const KernelCost& wide = fp8 ? kWideFp8 : kWideBf16;
+  const KernelCost& narrow = fp8 ? kNarrowFp8 : kNarrowBf16;
+  // One block of 32 rows: the narrow kernel does the same work in fewer instructions, whatever the
+  // lengths (128 sequences of 2176 kept tokens, 16 heads: 88 -> 63 us, fp8 94 -> 43 us).
+  const bool one_block = hp.heads_total <= kHeadsPerWave;
   if (prob.num_splits_hint > 0) {
+    deal_heads(one_block ? narrow.head_block : wide.head_block);
     hp.segs.clear();
     hp.unit_seg.assign(1, 0);
     for (const Item& it : items) {
@@ -287,8 +302,28 @@ int build_host_plan(HostPlan& hp, const omniattn_problem_t& prob, const int32_t*
       }
     }
   } else {
-    partition(items, num_cus, prob.kv_dtype == OMNIATTN_FP8_E4M3 ? kCostFp8 : kCostBf16,
-              (int)(OMNIATTN_STATIC_SCRATCH_BYTES / slot_bytes), hp.segs, hp.unit_seg);
+    auto try_kernel = [&](const KernelCost& k, std::vector<Segment>& segs, std::vector<int32_t>& unit_seg) {
+      deal_heads(k.head_block);
+      const size_t slot_bytes = (size_t)k.head_block * (sizeof(float) + kV * elt) + 1;  // (+ 1: room for alignment)
+      return partition(items, num_cus, k, (int)(OMNIATTN_STATIC_SCRATCH_BYTES / slot_bytes), segs, unit_seg);
+    };
+    // With more rows the kernel with the smaller estimate is taken: the narrow one where the sequences
+    // are too few to fill the chip with long pieces (one sequence of 2176 kept tokens, 128 heads: 69
+    // pieces of one tile and 69 partial rows to merge, or 4 x 17 of four tiles: 24.1 -> 15.6 us), the
+    // other where tiles are many.
+    double best = one_block ? INFINITY : try_kernel(wide, hp.segs, hp.unit_seg);
+    const int n_narrow = (hp.heads_total + kHeadsPerWave - 1) / kHeadsPerWave;
+    if ((double)(sum_tiles * n_narrow) / num_cus * narrow.tile_us < best) {
+      std::vector<Segment> segs;
+      std::vector<int32_t> unit_seg;
+      const int blocks = hp.head_block;
+      if (try_kernel(narrow, segs, unit_seg) < best) {
+        hp.segs.swap(segs);
+        hp.unit_seg.swap(unit_seg);
+      } else {
+        deal_heads(blocks);
+      }
+    }
   }
 
   // partial slots for every (sequence, head block) cut into more than one segment

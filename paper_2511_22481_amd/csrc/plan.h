@@ -79,8 +79,8 @@ struct CombineItem {
 struct HostPlan {
   omniattn_problem_t prob;
   int num_cus = 0;
-  int waves = 0;        // waves per work group; each owns 32 heads
-  int head_block = 0;   // heads per work unit = 32 * waves
+  int waves = 4;        // waves per work group (one per SIMD)
+  int head_block = 0;   // heads per work unit: 128 (each wave owns 32), or 32 (decode_narrow_kernel)
   int n_hb = 0;         // head blocks per sequence
   int tile = kTile;       // KV tokens per tile (kTile, or kTileFp8 for an fp8 cache)
   int q_len = 1;          // queries per sequence

@@ -55,3 +55,11 @@ def test_spill_in_front_of_mfmas_is_reported():
 def test_other_kernels_are_not_checked():
     asm = "_ZN8omniattn14combine_kernelILb0EEEvNS_13CombineParamsE:\n" + MFMA + "\tv_mov_b32_e32 v5, 0\n" + TAIL
     assert check(asm) == []
+
+
+def test_scalar_address_of_a_direct_load_written_too_late_is_reported():
+    base = "\tv_readfirstlane_b32 s4, v74\n\tv_readfirstlane_b32 s5, v75\n\ts_and_b32 s4, s4, -2\n"
+    load = "\tglobal_load_lds_dwordx4 v142, s[4:5] offset:0 nt\n"
+    probs = check(HEAD + base + load + TAIL)
+    assert any("direct load reads s5" in p for p in probs)
+    assert check(HEAD + base + "\ts_nop 4\n" + load + TAIL) == []

@@ -46,3 +46,11 @@ def test_merge_of_many_partials(hint, out_dtype):
     out, lse, plan = parity.run_gpu(inp, out_dtype=out_dtype, num_splits_hint=hint)
     assert plan.max_splits == min(hint, (64 + 1024) // plan.tile_tokens + 1)
     parity.assert_parity(inp, out, lse, row_rel_l2=1e-2, what=f"{plan.max_splits} partials")
+
+
+def test_kernel_for_few_rows_or_few_sequences():
+    # 32 rows or fewer: always blocks of 32; more rows: where the sequences are too few for long pieces
+    assert check_plan([32768] * 64, 128, 2048, H=16).head_block == 32
+    assert check_plan([32768] * 2, 128, 2048, H=33).head_block == 32
+    assert check_plan([20011], 128, 2048).head_block == 32
+    assert check_plan([20011] * 64, 128, 2048).head_block == 128
