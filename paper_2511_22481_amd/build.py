@@ -6,7 +6,7 @@ import subprocess
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libomniattn.so")
-SOURCES = ["decode_kernels.hip", "decode_fp8_kernel.hip", "decode_narrow_kernel.hip", "append_kernels.hip", "api.cpp", "plan.cpp"]
+SOURCES = ["decode_kernels.hip", "decode_fp8_kernel.hip", "decode_fp8_64_kernel.hip", "decode_narrow_kernel.hip", "append_kernels.hip", "api.cpp", "plan.cpp"]
 HEADERS = ["kernels.h", "plan.h", "decode_common.h", os.path.join("..", "..", "include", "omniattn.h")]
 
 
@@ -72,6 +72,7 @@ def check_generated_code(verbose=False):
     problems = []
     with tempfile.TemporaryDirectory() as tmp:
         for src, kernel in (("decode_kernels.hip", "decode_kernel"), ("decode_fp8_kernel.hip", "decode_fp8_kernel"),
+                            ("decode_fp8_64_kernel.hip", "decode_fp8_64_kernel"),
                             ("decode_narrow_kernel.hip", "decode_narrow_kernel")):
             out = os.path.join(tmp, src + ".s")
             cmd = [hipcc(), "--offload-arch=gfx950", "-O3", "-std=c++20",

@@ -70,6 +70,7 @@ int init_device(int dev) {
   if (g_init_done[dev]) return OMNIATTN_OK;
   hipError_t e = init_kernels();
   if (e == hipSuccess) e = init_fp8_kernel();
+  if (e == hipSuccess) e = init_fp8_64_kernel();
   if (e == hipSuccess) e = init_narrow_kernels();
   if (e != hipSuccess) return hip_fail(e, "kernel attribute setup");
   // (the caller made `dev` current: the address is that of this device's copy)
@@ -346,6 +347,7 @@ int omniattn_decode_timed(const omniattn_plan_t* plan, const void* q, const void
   if (dp.scale_log2 == 0.f) dp.scale_log2 = 1e-30f;
   if (ev_begin) OA_HIP(hipEventRecord((hipEvent_t)ev_begin, stream));
   if (hp.head_block == kHeadsPerWave) OA_HIP(launch_decode_narrow(dp, fp8, (int)hp.unit_seg.size() - 1, stream));
+  else if (fp8 && hp.head_block == kHeadBlockFp8) OA_HIP(launch_decode_fp8_64(dp, (int)hp.unit_seg.size() - 1, stream));
   else if (fp8) OA_HIP(launch_decode_fp8(dp, (int)hp.unit_seg.size() - 1, stream));
   else OA_HIP(launch_decode(dp, hp.waves, (int)hp.unit_seg.size() - 1, stream));
   if (ev_main_end) OA_HIP(hipEventRecord((hipEvent_t)ev_main_end, stream));

@@ -67,6 +67,61 @@ __device__ __forceinline__ void wait_vm() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
+// Direct global->LDS loads (see dma16 for what they do), each with its LDS base.  Base and LDS address
+// come fresh from vector registers (v_readfirstlane), and the compiler does not see the memory
+// instruction inside the assembly: the five wait states that a vector-memory instruction needs behind
+// such a write of its scalar address stand in the same block.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+__device__ __forceinline__ uint64_t uniform64(uint64_t b) {
+  return ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(b >> 32)) << 32) |
+         (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)b);
+}
+template <bool NT>  // nt: rows read once (see dma16)
+__device__ __forceinline__ void load_lds16(uint32_t lds, const uint8_t* base, uint32_t off) {
+  const uint64_t b = uniform64((uint64_t)(uintptr_t)base);
+  const uint32_t m = __builtin_amdgcn_readfirstlane(lds);
+  if constexpr (NT)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2 nt" : : "s"(m), "v"(off), "s"(b) : "m0", "memory");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(m), "v"(off), "s"(b) : "m0", "memory");
+}
+__device__ __forceinline__ void load_lds4(uint32_t lds, const uint8_t* base, uint32_t off) {
+  const uint64_t b = uniform64((uint64_t)(uintptr_t)base);
+  const uint32_t m = __builtin_amdgcn_readfirstlane(lds);
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dword %1, %2" : : "s"(m), "v"(off), "s"(b) : "m0", "memory");
+}
+// The same at the LDS base set before, from scalar addresses that went through settle_address.
+// load_lds4_at: for the lanes of a mask (all lanes of the wave must be active).
+__device__ __forceinline__ void set_lds_base(uint32_t lds) {
+  const uint32_t m = __builtin_amdgcn_readfirstlane(lds);
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0" : : "s"(m) : "m0");
+}
+__device__ __forceinline__ void settle_address(uint64_t& a, uint64_t& b) {
+  a = uniform64(a);
+  b = uniform64(b);
+  asm volatile("s_nop 4" : "+s"(a), "+s"(b));
+}
+template <int IMM>
+__device__ __forceinline__ void load_lds16_at(uint64_t base, uint32_t off) {
+  asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2 nt" : : "v"(off), "s"(base), "n"(IMM) : "m0", "memory");
+}
+__device__ __forceinline__ void load_lds4_at(uint64_t lanes, uint64_t base, uint32_t off) {
+  asm volatile("s_mov_b64 exec, %0\n\tglobal_load_lds_dword %1, %2\n\ts_mov_b64 exec, -1" : : "s"(lanes), "v"(off), "s"(base) : "m0", "memory");
+}
+#pragma clang diagnostic pop
+
+// Exchange of rows of 16 lanes (halves of 32) between two registers: with a = b = x before, a and b hold the
+// lane's own value and that of lane ^ 16 (lane ^ 32) behind it, in an order that depends on the lane.
+// (Assembly: with the builtin the compiler drops one of two results that are combined at once.  The wait
+// states are the ones it places for the builtin.)
+__device__ __forceinline__ void swap16(float& a, float& b) {
+  asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
+}
+__device__ __forceinline__ void swap32(float& a, float& b) {
+  asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
+}
+
 // The XCD (accelerator complex die) this wave runs on: compute units of one XCD share an L2.
 __device__ __forceinline__ uint32_t xcc_id() {
   uint32_t id;

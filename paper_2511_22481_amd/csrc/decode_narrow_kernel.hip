@@ -69,41 +69,8 @@ struct Lay<true> {
   __host__ __device__ static constexpr int sw_tail(int r) { return (r >> 2) & 3; }
 };
 
-// Direct global->LDS loads (see dma16 for what they do), each with its LDS base.  Base and LDS address
-// come fresh from vector registers (v_readfirstlane), and the compiler does not see the memory
-// instruction inside the assembly: the five wait states that a vector-memory instruction needs behind
-// such a write of its scalar address stand in the same block.
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ uint64_t uniform_address(const uint8_t* base) {
-  const uint64_t b = (uint64_t)(uintptr_t)base;
-  return ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(b >> 32)) << 32) |
-         (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)b);
-}
-template <bool NT>  // nt: rows read once (see dma16)
-__device__ __forceinline__ void load_lds16(uint32_t lds, const uint8_t* base, uint32_t off) {
-  const uint64_t b = uniform_address(base);
-  const uint32_t m = __builtin_amdgcn_readfirstlane(lds);
-  if constexpr (NT)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2 nt" : : "s"(m), "v"(off), "s"(b) : "m0", "memory");
-  else
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(m), "v"(off), "s"(b) : "m0", "memory");
-}
-__device__ __forceinline__ void load_lds4(uint32_t lds, const uint8_t* base, uint32_t off) {
-  const uint64_t b = uniform_address(base);
-  const uint32_t m = __builtin_amdgcn_readfirstlane(lds);
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dword %1, %2" : : "s"(m), "v"(off), "s"(b) : "m0", "memory");
-}
-#pragma clang diagnostic pop
-
 // A lane's value combined with those of lanes l ^ 16, l ^ 32 and l ^ 48 (the four lanes of a head in
-// the 16x16 result layout).  The swaps exchange rows of 16 (halves of 32) lanes between two registers.
-__device__ __forceinline__ void swap16(float& a, float& b) {
-  asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
-}
-__device__ __forceinline__ void swap32(float& a, float& b) {
-  asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
-}
+// the 16x16 result layout).
 __device__ __forceinline__ float quad_max(float x) {
   float a = x, b = x;
   swap16(a, b);

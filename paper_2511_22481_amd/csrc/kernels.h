@@ -70,6 +70,9 @@ hipError_t launch_decode(const DecodeParams& p, int waves, int n_units, hipStrea
 // fp8 cache: its own kernel (decode_fp8_kernel.hip), tiles of kTileFp8 tokens.
 hipError_t init_fp8_kernel();
 hipError_t launch_decode_fp8(const DecodeParams& p, int n_units, hipStream_t stream);
+// Blocks of 64 head rows, fp8 cache (decode_fp8_64_kernel.hip).
+hipError_t init_fp8_64_kernel();
+hipError_t launch_decode_fp8_64(const DecodeParams& p, int n_units, hipStream_t stream);
 // Blocks of 32 head rows, bf16 or fp8 cache (decode_narrow_kernel.hip).
 hipError_t init_narrow_kernels();
 hipError_t launch_decode_narrow(const DecodeParams& p, bool fp8, int n_units, hipStream_t stream);

@@ -12,10 +12,6 @@ namespace omniattn {
 
 namespace {
 
-struct Item {
-  int b, hb, ntiles;
-};
-
 // What a partition costs with one of the kernels (measured on MI355X):
 //   head_block  head rows per work unit;
 //   tile_us  a KV tile in the long loop when all compute units work;
@@ -30,21 +26,22 @@ struct KernelCost {
   double combine;
   double slots_per_tile;
 };
-// The kernels for full head blocks: 9 us and 13 us a segment.
+// The kernels for blocks of 128 rows: 9 us and 13 us a segment.
 constexpr KernelCost kWideBf16 = {4 * kHeadsPerWave, 1.8, 5, 3.3, 36.0};
-constexpr KernelCost kWideFp8 = {4 * kHeadsPerWave, 3.4, 4, 1.8, 65.0};
-// The kernel for blocks of 32 rows: every tile passes through once per block, but its tile and its start
-// cost less.
+constexpr KernelCost kWideFp8 = {4 * kHeadsPerWave, 3.5, 4, 1.8, 65.0};
+// Blocks of 64 (fp8 cache) and 32 rows: every tile passes through once per block.  Fitted to nine shapes
+// from 4 to 256 sequences, each timed with each kernel forced; the estimates are within 12 % of those times.
+constexpr KernelCost kMidFp8 = {kHeadBlockFp8, 1.7, 8, 2.4, 65.0};
 constexpr KernelCost kNarrowBf16 = {kHeadsPerWave, 1.4, 4, 4.3, 112.0};
-constexpr KernelCost kNarrowFp8 = {kHeadsPerWave, 1.5, 4, 4.0, 120.0};
+constexpr KernelCost kNarrowFp8 = {kHeadsPerWave, 1.5, 7, 2.7, 114.0};
 // Do not leave slivers shorter than this many tiles unless the item itself is shorter.
 constexpr int kMinSegTiles = 2;
 
-// Deals the items in order to units of capacity `cap` (tiles plus `seg` per segment), cutting an
-// item where a unit is full.  emit(item, tile_lo, tile_hi, unit) for every segment; returns the
-// number of units used.
+// Deals the items (sequence b, head block hb) in order to units of capacity `cap` (tiles plus `seg` per
+// segment), cutting an item where a unit is full.  emit(b, hb, tile_lo, tile_hi, unit) for every segment;
+// returns the number of units used.
 template <typename Emit>
-int fill_units(const std::vector<Item>& items, int cap, int seg, Emit emit) {
+int fill_units(const std::vector<int32_t>& tiles, int n_hb, int cap, int seg, Emit emit) {
   int load = 0, unit = 0;
   auto close_unit = [&]() {
     if (load > 0) {
@@ -52,31 +49,33 @@ int fill_units(const std::vector<Item>& items, int cap, int seg, Emit emit) {
       load = 0;
     }
   };
-  for (const Item& it : items) {
-    if (it.ntiles == 0) {  // empty retained set: one segment that only writes zeros / -inf
-      if (load + seg > cap) close_unit();
-      emit(it, 0, 0, unit);
-      load += seg;
-      continue;
-    }
-    int done = 0;
-    while (done < it.ntiles) {
-      const int rem = it.ntiles - done;
-      int room = cap - load - seg;
-      const int need = std::min(rem, kMinSegTiles);
-      if (room < need) {
-        if (load == 0) room = need;  // capacity smaller than one minimal segment
-        else { close_unit(); continue; }
+  for (int b = 0; b < (int)tiles.size(); ++b)
+    for (int hb = 0; hb < n_hb; ++hb) {
+      const int ntiles = tiles[b];
+      if (ntiles == 0) {  // empty retained set: one segment that only writes zeros / -inf
+        if (load + seg > cap) close_unit();
+        emit(b, hb, 0, 0, unit);
+        load += seg;
+        continue;
       }
-      int take = std::min(std::min(rem, room), kMaxSegTiles);
-      // avoid leaving a sliver behind
-      if (rem - take > 0 && rem - take < kMinSegTiles) take = std::max(1, rem - kMinSegTiles);
-      emit(it, done, done + take, unit);
-      done += take;
-      load += take + seg;
-      if (load >= cap) close_unit();
+      int done = 0;
+      while (done < ntiles) {
+        const int rem = ntiles - done;
+        int room = cap - load - seg;
+        const int need = std::min(rem, kMinSegTiles);
+        if (room < need) {
+          if (load == 0) room = need;  // capacity smaller than one minimal segment
+          else { close_unit(); continue; }
+        }
+        int take = std::min(std::min(rem, room), kMaxSegTiles);
+        // avoid leaving a sliver behind
+        if (rem - take > 0 && rem - take < kMinSegTiles) take = std::max(1, rem - kMinSegTiles);
+        emit(b, hb, done, done + take, unit);
+        done += take;
+        load += take + seg;
+        if (load >= cap) close_unit();
+      }
     }
-  }
   close_unit();
   return unit;
 }
@@ -93,135 +92,198 @@ int fill_units(const std::vector<Item>& items, int cap, int seg, Emit emit) {
 //   fill   units filled one after the other to the same load, items cut wherever that falls: wins
 //          when the item count is not near a multiple or divisor of the unit count.
 //
-// `most_slots`: partial slots that fit the built-in scratch buffer.  Even pieces are not cut so
-// short that omniattn_decode_static would refuse the plan.  Returns the estimate in us.
-double partition(const std::vector<Item>& items, int num_cus, const KernelCost& cost, int most_slots,
-                 std::vector<Segment>& segs, std::vector<int32_t>& unit_seg) {
-  const int n = (int)items.size();
-  int64_t total = 0;
-  int n_max = 0;
-  for (const Item& it : items) {
-    total += it.ntiles + cost.seg;
-    n_max = std::max(n_max, it.ntiles);
-  }
-  auto merge_cost = [&](int slots) { return slots ? cost.combine + slots / cost.slots_per_tile : 0.0; };
+// The estimates come first and only the partition that is taken is laid out: a serving loop plans again
+// for every decode step, and searching the fill of three kernels to the end took 30 us of host time
+// (40 sequences) where this takes 5.
+struct Shape {
+  enum { kFill, kWhole, kEven } kind = kFill;
+  int size = 0;                  // kFill: capacity of a unit; kEven: tiles of a piece
+  double us = INFINITY;
+  std::vector<int32_t> unit_of;  // kWhole: unit of every item (empty: one item to a unit)
+};
 
-  // fill: the smallest capacity that needs no more units than there are
-  int lo = std::max((int)std::min<int64_t>((total + num_cus - 1) / num_cus, INT32_MAX / 2), cost.seg + 1), fill_cap = lo;
-  auto units_at = [&](int cap) { return fill_units(items, cap, cost.seg, [](const Item&, int, int, int) {}); };
-  if (units_at(lo) > num_cus) {
-    int step = 1;
-    while (units_at(lo + step) > num_cus && step < (1 << 28)) step *= 2;
-    int bad = lo + step / 2, good = lo + step;
-    while (good - bad > 1) {
-      const int mid = bad + (good - bad) / 2;
-      (units_at(mid) > num_cus ? bad : good) = mid;
-    }
-    fill_cap = good;
+// `tiles`: per sequence; every sequence is n_hb items of that many.  `most_slots`: partial slots that fit
+// the built-in scratch buffer; even pieces are not cut so short that omniattn_decode_static would refuse
+// the plan.  Returns an estimate of `limit_us` or more when nothing below it exists.
+Shape choose_shape(const std::vector<int32_t>& tiles, int n_hb, int num_cus, const KernelCost& cost, int most_slots,
+                   double limit_us) {
+  Shape r;
+  const int n = (int)tiles.size() * n_hb;
+  int64_t sum = 0;
+  int n_max = 0;
+  for (int t : tiles) {
+    sum += t;
+    n_max = std::max(n_max, t);
   }
-  double best;
-  {
-    int slots = 0, longest = 0, load = 0, last_unit = -1;
-    fill_units(items, fill_cap, cost.seg, [&](const Item& it, int a, int b, int unit) {
-      if (b - a < it.ntiles) ++slots;
-      load = (unit == last_unit ? load : 0) + b - a + cost.seg;
-      last_unit = unit;
-      longest = std::max(longest, load);
-    });
-    best = longest + merge_cost(slots);
+  sum *= n_hb;
+  auto merge_cost = [&](int64_t slots) { return slots ? cost.combine + slots / cost.slots_per_tile : 0.0; };
+  // Tile counts with how often they occur: windows make most sequences alike, and the sums over all items
+  // below are then sums over a few entries.
+  std::vector<std::pair<int32_t, int32_t>> counts;
+  counts.reserve(tiles.size());
+  for (int t : tiles) {
+    const size_t known = std::min<size_t>(counts.size(), 16);
+    size_t k = 0;
+    while (k < known && counts[k].first != t) ++k;
+    if (k < known) ++counts[k].second;
+    else counts.emplace_back(t, 1);
   }
-  enum { kFill, kWhole, kEven } shape = kFill;
+  auto pieces_at = [&](int p) {  // pieces of at most p tiles
+    int64_t k = 0;
+    for (const auto& c : counts) k += (int64_t)(c.first > p ? (c.first + p - 1) / p : 1) * c.second;
+    return k * n_hb;
+  };
+  auto cut_pieces_at = [&](int p) {  // those of items that are cut
+    int64_t k = 0;
+    for (const auto& c : counts)
+      if (c.first > p) k += (int64_t)((c.first + p - 1) / p) * c.second;
+    return k * n_hb;
+  };
+  double best = limit_us / cost.tile_us;  // in tiles, as all below
+  bool found = false;
+  auto take = [&](double t) {
+    if (t >= best) return false;
+    best = t;
+    return found = true;
+  };
+  // (some unit has at least the average tiles, and a segment)
+  if ((double)sum / num_cus + cost.seg >= best) return r;
 
   // whole (a segment's tile table holds kMaxSegTiles)
-  std::vector<int32_t> unit_of;
-  if (n_max <= kMaxSegTiles && n_max + cost.seg < best) {
-    std::vector<int32_t> order(n);
-    for (int i = 0; i < n; ++i) order[i] = i;
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return items[a].ntiles > items[b].ntiles; });
-    unit_of.resize(n);
-    std::vector<std::pair<int32_t, int32_t>> heap;  // (load, unit), least loaded on top
-    const auto later = std::greater<std::pair<int32_t, int32_t>>();
-    int longest = 0;
-    for (int i = 0; i < n && longest < best; ++i) {
-      const int cost_i = items[order[i]].ntiles + cost.seg;
-      int unit = i, load = cost_i;
-      if (i < num_cus) {
-        heap.emplace_back(load, unit);
-        if (i == num_cus - 1 || i == n - 1) std::make_heap(heap.begin(), heap.end(), later);
-      } else {
-        std::pop_heap(heap.begin(), heap.end(), later);
-        unit = heap.back().second;
-        load = heap.back().first += cost_i;
-        std::push_heap(heap.begin(), heap.end(), later);
+  if (n_max <= kMaxSegTiles) {
+    if (n <= num_cus) {
+      if (take(n_max + cost.seg)) r.kind = Shape::kWhole;
+    } else if ((double)(sum + (int64_t)n * cost.seg) / num_cus < best && n_max + cost.seg < best) {
+      std::vector<int32_t> order(n), unit_of(n);
+      for (int i = 0; i < n; ++i) order[i] = i;
+      std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return tiles[a / n_hb] > tiles[b / n_hb]; });
+      std::vector<std::pair<int32_t, int32_t>> heap;  // (load, unit), least loaded on top
+      heap.reserve(num_cus);
+      const auto later = std::greater<std::pair<int32_t, int32_t>>();
+      int longest = 0;
+      for (int i = 0; i < n && longest < best; ++i) {
+        const int cost_i = tiles[order[i] / n_hb] + cost.seg;
+        int unit = i, load = cost_i;
+        if (i < num_cus) {
+          heap.emplace_back(load, unit);
+          if (i == num_cus - 1) std::make_heap(heap.begin(), heap.end(), later);
+        } else {
+          std::pop_heap(heap.begin(), heap.end(), later);
+          unit = heap.back().second;
+          load = heap.back().first += cost_i;
+          std::push_heap(heap.begin(), heap.end(), later);
+        }
+        unit_of[order[i]] = unit;
+        longest = std::max(longest, load);
       }
-      unit_of[order[i]] = unit;
-      longest = std::max(longest, load);
-    }
-    if (longest < best) {
-      best = longest;
-      shape = kWhole;
+      if (take(longest)) {
+        r.kind = Shape::kWhole;
+        r.unit_of = std::move(unit_of);
+      }
     }
   }
   // even: the smallest piece that needs no more pieces than there are units
-  int piece = 0;
   if (n <= num_cus && n_max > 1) {
-    auto pieces_at = [&](int p) {
-      int64_t k = 0;
-      for (const Item& it : items) k += std::max(1, (it.ntiles + p - 1) / p);
-      return k;
-    };
-    int bad = 0, good = n_max;  // (one piece per item fits)
+    int bad = (int)((sum - 1) / num_cus), good = n_max;  // (shorter pieces than the average are too many; one piece per item fits)
     while (good - bad > 1) {
       const int mid = bad + (good - bad) / 2;
       (pieces_at(mid) > num_cus ? bad : good) = mid;
     }
     // (with few items the shortest pieces give more partial rows than they save tiles: sum / p
     // slots cost sum / p / slots_per_tile, which balances p at the square root below)
-    const int balanced = (int)std::sqrt((double)(total - (int64_t)n * cost.seg) / cost.slots_per_tile);
+    const int balanced = (int)std::sqrt((double)sum / cost.slots_per_tile);
     for (int p : {good, std::max(good, balanced), 2 * good}) {
       p = std::min({p, n_max, kMaxSegTiles});
-      if (pieces_at(p) > num_cus) continue;
-      int slots = 0;
-      for (const Item& it : items)
-        if (it.ntiles > p) slots += (it.ntiles + p - 1) / p;
-      if (slots > most_slots) continue;
-      const double t = p + cost.seg + merge_cost(slots);
-      if (t < best) {
-        best = t;
-        shape = kEven;
-        piece = p;
+      if (p + cost.seg >= best || pieces_at(p) > num_cus) continue;
+      const int64_t slots = cut_pieces_at(p);
+      if (slots <= most_slots && take(p + cost.seg + merge_cost(slots))) {
+        r.kind = Shape::kEven;
+        r.size = p;
       }
     }
   }
-
-  segs.clear();
-  unit_seg.assign(1, 0);
-  auto add = [&](const Item& it, int a, int b, int unit) {
-    while ((int)unit_seg.size() <= unit) unit_seg.push_back((int32_t)segs.size());
-    segs.push_back({it.b, it.hb, a, b, -1, unit, 0, it.ntiles});
-  };
-  if (shape == kFill) {
-    fill_units(items, fill_cap, cost.seg, add);
-  } else if (shape == kEven) {
-    int unit = 0;
-    for (const Item& it : items) {
-      const int k = std::max(1, (it.ntiles + piece - 1) / piece);
-      for (int s = 0; s < k; ++s)
-        add(it, (int)((int64_t)it.ntiles * s / k), (int)((int64_t)it.ntiles * (s + 1) / k), unit++);
+  // fill: the smallest capacity that needs no more units than there are, if one can win at all
+  auto units_at = [&](int cap) { return fill_units(tiles, n_hb, cap, cost.seg, [](int, int, int, int, int) {}); };
+  int lo = (int)std::min<int64_t>((sum + (int64_t)n * cost.seg + num_cus - 1) / num_cus, INT32_MAX / 2);
+  lo = std::max(lo, cost.seg + 1);
+  // (a capacity that gives no more than whole items may come without a merge; then `whole` is as good)
+  const double cap_max = found || best < INFINITY ? best - cost.combine : INFINITY;
+  // (a capacity c gives segments of at most c - seg tiles: at least that many of them, and slots)
+  bool worth_it = cap_max == INFINITY;
+  for (int c = lo; !worth_it && c < cap_max; ++c) {
+    if (sum + cost.seg * pieces_at(c - cost.seg) > (int64_t)num_cus * c) {
+      if (c == lo) ++lo;
+      continue;
     }
+    worth_it = c + merge_cost(cut_pieces_at(c - cost.seg)) < best;
+  }
+  int cap = 0;
+  if (worth_it) {  // upwards from the bound, which is close, then back to the smallest
+    int bad = lo - 1, step = 1;
+    while (lo < cap_max && step < (1 << 28) && units_at(lo) > num_cus) {
+      bad = lo;
+      lo += step;
+      step *= 2;
+    }
+    if (lo < cap_max) {
+      cap = lo;
+      while (cap - bad > 1) {
+        const int mid = bad + (cap - bad) / 2;
+        (units_at(mid) > num_cus ? bad : cap) = mid;
+      }
+    }
+  }
+  if (cap > 0) {
+    int64_t slots = 0;
+    int longest = 0, load = 0, last_unit = -1;
+    fill_units(tiles, n_hb, cap, cost.seg, [&](int b, int, int lo_t, int hi_t, int unit) {
+      if (hi_t - lo_t < tiles[b]) ++slots;
+      load = (unit == last_unit ? load : 0) + hi_t - lo_t + cost.seg;
+      last_unit = unit;
+      longest = std::max(longest, load);
+    });
+    if (take(longest + merge_cost(slots))) {
+      r.kind = Shape::kFill;
+      r.size = cap;
+    }
+  }
+  if (found) r.us = best * cost.tile_us;
+  return r;
+}
+
+void lay_out(const Shape& shape, const std::vector<int32_t>& tiles, int n_hb, int num_cus, const KernelCost& cost,
+             std::vector<Segment>& segs, std::vector<int32_t>& unit_seg) {
+  segs.clear();
+  segs.reserve(2 * (size_t)num_cus + tiles.size() * n_hb);
+  unit_seg.reserve(num_cus + 1);
+  unit_seg.assign(1, 0);
+  auto add = [&](int b, int hb, int lo, int hi, int unit) {
+    while ((int)unit_seg.size() <= unit) unit_seg.push_back((int32_t)segs.size());
+    segs.push_back({b, hb, lo, hi, -1, unit, 0, tiles[b]});
+  };
+  const int batch = (int)tiles.size(), n = batch * n_hb;
+  if (shape.kind == Shape::kFill) {
+    fill_units(tiles, n_hb, shape.size, cost.seg, add);
+  } else if (shape.kind == Shape::kEven) {
+    int unit = 0;
+    for (int b = 0; b < batch; ++b) {
+      const int t = tiles[b], k = std::max(1, (t + shape.size - 1) / shape.size);
+      for (int hb = 0; hb < n_hb; ++hb)
+        for (int s = 0; s < k; ++s) add(b, hb, (int)((int64_t)t * s / k), (int)((int64_t)t * (s + 1) / k), unit++);
+    }
+  } else if (shape.unit_of.empty()) {
+    for (int i = 0; i < n; ++i) add(i / n_hb, i % n_hb, 0, tiles[i / n_hb], i);
   } else {
     // units in order, each with its items
-    const int n_units = std::min(n, num_cus);
-    std::vector<int32_t> first(n_units + 1, 0), at(n);
-    for (int i = 0; i < n; ++i) ++first[unit_of[i] + 1];
-    for (int u = 0; u < n_units; ++u) first[u + 1] += first[u];
+    std::vector<int32_t> first(num_cus + 1, 0), at(n);
+    for (int i = 0; i < n; ++i) ++first[shape.unit_of[i] + 1];
+    for (int u = 0; u < num_cus; ++u) first[u + 1] += first[u];
     std::vector<int32_t> next(first.begin(), first.end() - 1);
-    for (int i = 0; i < n; ++i) at[next[unit_of[i]]++] = i;
-    for (int u = 0; u < n_units; ++u)
-      for (int k = first[u]; k < first[u + 1]; ++k) add(items[at[k]], 0, items[at[k]].ntiles, u);
+    for (int i = 0; i < n; ++i) at[next[shape.unit_of[i]]++] = i;
+    for (int u = 0; u < num_cus; ++u)
+      for (int k = first[u]; k < first[u + 1]; ++k) add(at[k] / n_hb, at[k] % n_hb, 0, tiles[at[k] / n_hb], u);
   }
   unit_seg.push_back((int32_t)segs.size());
-  return best * cost.tile_us;
 }
 
 }  // namespace
@@ -268,63 +330,66 @@ int build_host_plan(HostPlan& hp, const omniattn_problem_t& prob, const int32_t*
     tiles[b] = tile_layout(L, prob.sink, hp.window_union, hp.tile).count();
     sum_tiles += tiles[b];
   }
-  // sequence-major: the head blocks of one sequence read the same tiles; as neighbours they
-  // land on one XCD (see the unit mapping in the kernel) and share its L2
-  std::vector<Item> items;
-  auto deal_heads = [&](int head_block) {
-    const int n_hb = (hp.heads_total + head_block - 1) / head_block;
-    items.clear();
-    items.reserve((size_t)prob.batch * n_hb);
-    for (int b = 0; b < prob.batch; ++b)
-      for (int hb = 0; hb < n_hb; ++hb) items.push_back({b, hb, tiles[b]});
-    hp.head_block = head_block;
-    hp.n_hb = n_hb;
-  };
+  // (segments are listed sequence-major: the head blocks of one sequence read the same tiles; as
+  // neighbours they land on one XCD (see the unit mapping in the kernel) and share its L2)
+  auto blocks_of = [&](int head_block) { return (hp.heads_total + head_block - 1) / head_block; };
 
+  // The kernels that this problem can run on.  One block of 32 rows: only the narrow kernel, which does
+  // the same work in fewer instructions whatever the lengths (128 sequences of 2176 kept tokens, 16
+  // heads: 88 -> 62 us, fp8 94 -> 43 us).
   const bool fp8 = prob.kv_dtype == OMNIATTN_FP8_E4M3;
   const KernelCost& wide = fp8 ? kWideFp8 : kWideBf16;
-  const KernelCost& narrow = fp8 ? kNarrowFp8 : kNarrowBf16;
-  // One block of 32 rows: the narrow kernel does the same work in fewer instructions, whatever the
-  // lengths (128 sequences of 2176 kept tokens, 16 heads: 88 -> 63 us, fp8 94 -> 43 us).
-  const bool one_block = hp.heads_total <= kHeadsPerWave;
+  std::vector<const KernelCost*> kernels;
+  if (hp.heads_total > kHeadsPerWave) {
+    kernels.push_back(&wide);
+    if (fp8) kernels.push_back(&kMidFp8);
+  }
+  kernels.push_back(fp8 ? &kNarrowFp8 : &kNarrowBf16);
   if (prob.num_splits_hint > 0) {
-    deal_heads(one_block ? narrow.head_block : wide.head_block);
+    // forced splits: the smallest block that takes all rows, or the largest
+    int block = kernels[0]->head_block;
+    for (const KernelCost* k : kernels)
+      if (hp.heads_total <= k->head_block) block = k->head_block;
+    hp.head_block = block;
     hp.segs.clear();
     hp.unit_seg.assign(1, 0);
-    for (const Item& it : items) {
-      int pieces = std::max(1, std::min(prob.num_splits_hint, it.ntiles));
-      pieces = std::max(pieces, (it.ntiles + kMaxSegTiles - 1) / kMaxSegTiles);
-      for (int s = 0; s < pieces; ++s) {
-        int lo = (int)((int64_t)it.ntiles * s / pieces);
-        int hi = (int)((int64_t)it.ntiles * (s + 1) / pieces);
-        hp.segs.push_back({it.b, it.hb, lo, hi, -1, (int32_t)hp.unit_seg.size() - 1, 0, it.ntiles});
-        hp.unit_seg.push_back((int32_t)hp.segs.size());
+    for (int b = 0; b < prob.batch; ++b)
+      for (int hb = 0; hb < blocks_of(block); ++hb) {
+        int pieces = std::max(1, std::min(prob.num_splits_hint, tiles[b]));
+        pieces = std::max(pieces, (tiles[b] + kMaxSegTiles - 1) / kMaxSegTiles);
+        for (int s = 0; s < pieces; ++s) {
+          int lo = (int)((int64_t)tiles[b] * s / pieces);
+          int hi = (int)((int64_t)tiles[b] * (s + 1) / pieces);
+          hp.segs.push_back({b, hb, lo, hi, -1, (int32_t)hp.unit_seg.size() - 1, 0, tiles[b]});
+          hp.unit_seg.push_back((int32_t)hp.segs.size());
+        }
       }
-    }
   } else {
-    auto try_kernel = [&](const KernelCost& k, std::vector<Segment>& segs, std::vector<int32_t>& unit_seg) {
-      deal_heads(k.head_block);
-      const size_t slot_bytes = (size_t)k.head_block * (sizeof(float) + kV * elt) + 1;  // (+ 1: room for alignment)
-      return partition(items, num_cus, k, (int)(OMNIATTN_STATIC_SCRATCH_BYTES / slot_bytes), segs, unit_seg);
-    };
-    // With more rows the kernel with the smaller estimate is taken: the narrow one where the sequences
-    // are too few to fill the chip with long pieces (one sequence of 2176 kept tokens, 128 heads: 69
-    // pieces of one tile and 69 partial rows to merge, or 4 x 17 of four tiles: 24.1 -> 15.6 us), the
-    // other where tiles are many.
-    double best = one_block ? INFINITY : try_kernel(wide, hp.segs, hp.unit_seg);
-    const int n_narrow = (hp.heads_total + kHeadsPerWave - 1) / kHeadsPerWave;
-    if ((double)(sum_tiles * n_narrow) / num_cus * narrow.tile_us < best) {
-      std::vector<Segment> segs;
-      std::vector<int32_t> unit_seg;
-      const int blocks = hp.head_block;
-      if (try_kernel(narrow, segs, unit_seg) < best) {
-        hp.segs.swap(segs);
-        hp.unit_seg.swap(unit_seg);
-      } else {
-        deal_heads(blocks);
+    // The kernel with the smallest estimate is taken.  Narrow: few sequences, whose pieces would be short
+    // (one sequence of 2176 kept tokens, 128 heads: 69 pieces of one tile and 69 partial rows to merge, or
+    // 4 x 17 pieces of four tiles: 24.1 -> 15.4 us).  64 rows, fp8: most of the rest (32 sequences of 8320
+    // tokens, 128 heads: 83 -> 75 us; 128 of 2176, 64 heads: 87 -> 56).  128 rows: bf16, and fp8 with many short
+    // sequences (256 of 1024 tokens: 76 against 93 us).
+    Shape best;
+    const KernelCost* kernel = nullptr;
+    for (const KernelCost* k : kernels) {
+      const int n_hb = blocks_of(k->head_block);
+      const size_t slot_bytes = (size_t)k->head_block * (sizeof(float) + kV * elt) + 1;  // (+ 1: room for alignment)
+      const int most_slots = (int)(OMNIATTN_STATIC_SCRATCH_BYTES / slot_bytes);
+      Shape s = choose_shape(tiles, n_hb, num_cus, *k, most_slots, best.us);
+      if (s.us >= best.us) continue;
+      if (kernel && s.kind == Shape::kFill) {  // (not at the price of a plan that omniattn_decode_static would refuse)
+        int64_t slots = 0;
+        fill_units(tiles, n_hb, s.size, k->seg, [&](int b, int, int lo, int hi, int) { slots += hi - lo < tiles[b]; });
+        if (slots > most_slots) continue;
       }
+      best = std::move(s);
+      kernel = k;
     }
+    hp.head_block = kernel->head_block;
+    lay_out(best, tiles, blocks_of(hp.head_block), num_cus, *kernel, hp.segs, hp.unit_seg);
   }
+  hp.n_hb = blocks_of(hp.head_block);
 
   // partial slots for every (sequence, head block) cut into more than one segment
   hp.combine.clear();
