@@ -3,7 +3,10 @@
 Argument marshalling only: every step of the decode path runs in the HIP
 library.  PyTorch appears solely as the owner of device memory and streams.
 """
+import array
 import ctypes
+import functools
+import operator
 import os
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -159,17 +162,34 @@ def _problem(batch, num_heads, max_pages_per_seq, num_pages, sink, window, softm
 
 
 def _lens_array(seq_lens):
+    """(object to keep alive, its address) of the lengths as int32.  A list of ints, which a serving loop
+    hands over each step, goes through array.array: 1 us for 64 lengths instead of 5."""
+    if isinstance(seq_lens, list) and seq_lens:
+        try:
+            a = array.array("i", seq_lens)
+            return a, a.buffer_info()[0]
+        except (TypeError, OverflowError):
+            pass
     lens = [int(x) for x in seq_lens]
-    return (ctypes.c_int32 * max(len(lens), 1))(*lens)
+    a = (ctypes.c_int32 * max(len(lens), 1))(*lens)
+    return a, ctypes.addressof(a)
+
+
+def _current_stream():
+    """Handle of torch's current stream.  The raw query costs a tenth of torch.cuda.current_stream()."""
+    import torch
+    if not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _stream_handle(stream):
     import torch
     if stream is None:
         if not torch.cuda.is_available():
-            return ctypes.c_void_p(None)  # no GPU: the library itself reports that
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+            return None  # no GPU: the library itself reports that
+        return _current_stream()
+    return stream.cuda_stream
 
 
 def omniattn_plan(seq_lens, stream=None, **problem_fields):
@@ -177,16 +197,19 @@ def omniattn_plan(seq_lens, stream=None, **problem_fields):
     current stream).  seq_lens: host sequence of B ints."""
     prob = _problem(**problem_fields)
     h = ctypes.c_void_p()
-    _check(load_library().omniattn_plan(ctypes.byref(h), ctypes.byref(prob), _lens_array(seq_lens),
-                                        _stream_handle(stream)))
+    lens, address = _lens_array(seq_lens)
+    _check(load_library().omniattn_plan(ctypes.byref(h), ctypes.byref(prob), address, _stream_handle(stream)))
     return Plan(h, prob)
 
 
 def omniattn_plan_update(plan, seq_lens, stream=None):
     """Plan again for new lengths into the same object (no allocation, no synchronisation).
     seq_lens: host sequence of B ints, or a ctypes int32 array made once by the caller."""
-    lens = seq_lens if isinstance(seq_lens, ctypes.Array) else _lens_array(seq_lens)
-    _check(load_library().omniattn_plan_update(plan.handle, lens, _stream_handle(stream)))
+    if isinstance(seq_lens, ctypes.Array):
+        lens, address = seq_lens, ctypes.addressof(seq_lens)
+    else:
+        lens, address = _lens_array(seq_lens)
+    _check(load_library().omniattn_plan_update(plan.handle, address, _stream_handle(stream)))
     return plan
 
 
@@ -194,26 +217,23 @@ def omniattn_plan_host(seq_lens, num_cus=256, **problem_fields):
     """Host-only plan (inspection; cannot decode)."""
     prob = _problem(**problem_fields)
     h = ctypes.c_void_p()
-    _check(load_library().omniattn_plan_host(ctypes.byref(h), ctypes.byref(prob),
-                                             _lens_array(seq_lens), num_cus))
+    lens, address = _lens_array(seq_lens)
+    _check(load_library().omniattn_plan_host(ctypes.byref(h), ctypes.byref(prob), address, num_cus))
     return Plan(h, prob)
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
 
 
 def omniattn_decode(plan, q, kv_cache, kv_scales, page_table, out, lse, workspace=None,
                     stream=None):
     """Launch the decode on `stream` (a torch.cuda.Stream; default: current).
     All tensors are CUDA tensors owned by the caller; nothing is allocated."""
-    import torch
-    if stream is None:
-        stream = torch.cuda.current_stream()
     ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
     _check(load_library().omniattn_decode(
         plan.handle, _ptr(q), _ptr(kv_cache), _ptr(kv_scales), _ptr(page_table), _ptr(out),
-        _ptr(lse), _ptr(workspace), ws_bytes, ctypes.c_void_p(stream.cuda_stream)))
+        _ptr(lse), _ptr(workspace), ws_bytes, _current_stream() if stream is None else stream.cuda_stream))
 
 
 def omniattn_decode_timed(plan, q, kv_cache, kv_scales, page_table, out, lse, workspace, stream,
@@ -229,12 +249,9 @@ def omniattn_decode_timed(plan, q, kv_cache, kv_scales, page_table, out, lse, wo
 def omniattn_decode_static(plan, q, kv_cache, kv_scales, page_table, out, lse, stream=None):
     """omniattn_decode without a workspace argument: partial rows go to the library's own
     device buffer (omniattn_static_scratch_bytes() bytes); nothing is allocated."""
-    import torch
-    if stream is None:
-        stream = torch.cuda.current_stream()
     _check(load_library().omniattn_decode_static(
         plan.handle, _ptr(q), _ptr(kv_cache), _ptr(kv_scales), _ptr(page_table), _ptr(out),
-        _ptr(lse), ctypes.c_void_p(stream.cuda_stream)))
+        _ptr(lse), _current_stream() if stream is None else stream.cuda_stream))
 
 
 def omniattn_static_scratch_bytes():
@@ -255,20 +272,25 @@ def omniattn_ring_slot(sink, window, logical_page, q_len=1):
     return int(load_library().omniattn_ring_slot(sink, _window_union(window, q_len), logical_page))
 
 
+@functools.lru_cache(maxsize=64)
+def _ring_problem(batch, max_pages, num_pages, sink, window, fp8, q_len):
+    """The record that the library reads (and does not keep or change) on every append of a layer."""
+    prob = _problem(batch=batch, num_heads=1, max_pages_per_seq=max_pages, num_pages=num_pages, sink=sink, window=window,
+                    softmax_scale=1.0, kv_dtype=FP8_E4M3 if fp8 else BF16, q_len=q_len)
+    return ctypes.pointer(prob)
+
+
 def omniattn_ring_append(seq_lens, new_rows, new_scales, seq_pages, kv_cache, kv_scales, page_table,
                          *, sink, window, q_len=1, stream=None):
     """Append one token per sequence to a physically compressed cache (all CUDA tensors,
     seq_lens int32 [B] is incremented in place)."""
     import torch
-    if stream is None:
-        stream = torch.cuda.current_stream()
     fp8 = kv_cache.dtype == torch.float8_e4m3fn
-    prob = _problem(batch=int(seq_lens.shape[0]), num_heads=1, max_pages_per_seq=int(page_table.shape[1]),
-                    num_pages=int(kv_cache.shape[0]), sink=sink, window=window, softmax_scale=1.0,
-                    kv_dtype=FP8_E4M3 if fp8 else BF16, q_len=q_len)
+    prob = _ring_problem(seq_lens.shape[0], page_table.shape[1], kv_cache.shape[0], operator.index(sink),
+                         operator.index(window), fp8, operator.index(q_len))
     _check(load_library().omniattn_ring_append(
-        ctypes.byref(prob), _ptr(seq_lens), _ptr(new_rows), _ptr(new_scales), _ptr(seq_pages),
-        _ptr(kv_cache), _ptr(kv_scales), _ptr(page_table), ctypes.c_void_p(stream.cuda_stream)))
+        prob, _ptr(seq_lens), _ptr(new_rows), _ptr(new_scales), _ptr(seq_pages),
+        _ptr(kv_cache), _ptr(kv_scales), _ptr(page_table), _current_stream() if stream is None else stream.cuda_stream))
 
 
 def decode(q, kv_cache, kv_scales, page_table, seq_lens_host, sink, window, softmax_scale,

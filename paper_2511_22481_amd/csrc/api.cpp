@@ -1,6 +1,7 @@
 // C ABI of the sparse MLA decode library (see include/omniattn.h).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <climits>
 #include <cmath>
 #include <cstdlib>
@@ -14,22 +15,27 @@
 
 using namespace omniattn;
 
+namespace {
+// Device copy of a plan's metadata: one allocation holding the unit headers, the segments and the combine
+// items, filled by one asynchronous copy from one of two pinned host buffers of the same layout
+// (used in turn; an event per buffer says when its last copy has been read).
+struct MetaBuffers {
+  uint8_t* d = nullptr;
+  size_t cap = 0;
+  uint8_t* h[2] = {nullptr, nullptr};
+  hipEvent_t done[2] = {nullptr, nullptr};
+  bool busy[2] = {false, false};
+  int next = 0;
+};
+}  // namespace
+
 struct omniattn_plan_s {
   HostPlan hp;
   bool on_device = false;
   int device = -1;
   int num_cus = 0;
   int xcds = 1;        // work group i runs on XCD i % xcds (measured once per device)
-  // Device copy of the plan metadata (owned): one allocation holding the unit headers, the
-  // segments and the combine items, filled by one asynchronous copy from one of two pinned
-  // host buffers of the same layout (used in turn; an event per buffer says when its last
-  // copy has been read).  omniattn_plan_update reuses all of it when the new plan fits.
-  uint8_t* d_meta = nullptr;
-  size_t meta_cap = 0;
-  uint8_t* h_meta[2] = {nullptr, nullptr};
-  hipEvent_t h_done[2] = {nullptr, nullptr};
-  bool h_busy[2] = {false, false};
-  int h_next = 0;
+  MetaBuffers meta;    // owned; omniattn_plan_update reuses it when the new plan fits
   size_t off_segs = 0, off_combine = 0;
 };
 
@@ -86,17 +92,65 @@ int init_device(int dev) {
   return OMNIATTN_OK;
 }
 
-void free_device(omniattn_plan_s* pl) {
-  if (pl->d_meta) (void)hipFree(pl->d_meta);
+void free_meta(MetaBuffers& m) {
+  if (m.d) (void)hipFree(m.d);
   for (int i = 0; i < 2; ++i) {
-    if (pl->h_meta[i]) (void)hipHostFree(pl->h_meta[i]);
-    if (pl->h_done[i]) (void)hipEventDestroy(pl->h_done[i]);
-    pl->h_meta[i] = nullptr;
-    pl->h_done[i] = nullptr;
-    pl->h_busy[i] = false;
+    if (m.h[i]) (void)hipHostFree(m.h[i]);
+    if (m.done[i]) (void)hipEventDestroy(m.done[i]);
   }
-  pl->d_meta = nullptr;
-  pl->meta_cap = 0;
+  m = MetaBuffers{};
+}
+
+// Buffers of destroyed plans, kept for the next one: a program that plans anew for each call paid two pinned
+// and a device allocation and their release each time (plan and decode 3 sequences of 48 heads in one call:
+// 117 us, now 39).  At most kSpare per device, of at most kSpareBytes each; the rest is freed at once.
+// Kernels of any stream may still read a destroyed plan's copy, so a buffer is taken only behind a
+// device synchronisation, which the release used to imply.
+constexpr size_t kSpare = 2, kSpareBytes = 256 * 1024;
+std::mutex g_spare_mutex;
+MetaBuffers g_spare[kMaxDevices][kSpare];
+size_t g_spares[kMaxDevices] = {};
+
+bool take_spare(int dev, size_t bytes, MetaBuffers& m) {
+  MetaBuffers got;
+  {
+    std::lock_guard<std::mutex> lock(g_spare_mutex);
+    size_t& n = g_spares[dev];
+    size_t i = 0;
+    while (i < n && g_spare[dev][i].cap < bytes) ++i;
+    if (i == n) return false;
+    got = g_spare[dev][i];
+    g_spare[dev][i] = g_spare[dev][--n];
+  }
+  if (hipDeviceSynchronize() != hipSuccess) {  // (another thread captures, for instance: not now)
+    (void)hipGetLastError();
+    std::lock_guard<std::mutex> lock(g_spare_mutex);
+    if (g_spares[dev] < kSpare) {
+      g_spare[dev][g_spares[dev]++] = got;
+      return false;
+    }
+    free_meta(got);
+    return false;
+  }
+  got.busy[0] = got.busy[1] = false;
+  m = got;
+  return true;
+}
+
+void free_device(omniattn_plan_s* pl) {
+  MetaBuffers& m = pl->meta;
+  const int dev = pl->device;
+  if (m.d && m.h[0] && m.h[1] && m.done[0] && m.done[1] && m.cap <= kSpareBytes && dev >= 0 && dev < kMaxDevices) {
+    std::lock_guard<std::mutex> lock(g_spare_mutex);
+    if (g_spares[dev] < kSpare) {
+      g_spare[dev][g_spares[dev]++] = m;
+      m = MetaBuffers{};
+    } else {  // the larger ones stay: they serve more plans
+      for (MetaBuffers& kept : g_spare[dev])
+        if (kept.cap < m.cap) std::swap(kept, m);
+    }
+  }
+  free_meta(m);
 }
 
 int build_plan(HostPlan& hp, const omniattn_problem_t& prob, const int32_t* seq_lens, int num_cus) {
@@ -133,26 +187,27 @@ int upload_plan(omniattn_plan_s* pl, hipStream_t stream) {
   pl->off_segs = align16(n_units * sizeof(UnitHeader));
   pl->off_combine = pl->off_segs + align16(n_segs * sizeof(DevSegment));
   const size_t bytes = pl->off_combine + align16(n_items * sizeof(CombineItem));
-  if (bytes > pl->meta_cap) {
+  MetaBuffers& m = pl->meta;
+  if (bytes > m.cap && !(m.cap == 0 && take_spare(pl->device, bytes, m))) {
     // (rare: a plan larger than any before it; freeing waits for the device)
-    const size_t cap = bytes + bytes / 2 + 4096;
-    if (pl->d_meta) (void)hipFree(pl->d_meta);
-    pl->d_meta = nullptr;
-    pl->meta_cap = 0;
+    const size_t cap = std::max<size_t>(bytes + bytes / 2 + 4096, 64 * 1024);  // (most plans need 10 to 40 KB)
+    if (m.d) (void)hipFree(m.d);
+    m.d = nullptr;
+    m.cap = 0;
     for (int i = 0; i < 2; ++i) {
-      if (pl->h_meta[i]) (void)hipHostFree(pl->h_meta[i]);
-      pl->h_meta[i] = nullptr;
-      pl->h_busy[i] = false;
-      OA_HIP(hipHostMalloc((void**)&pl->h_meta[i], cap, hipHostMallocDefault));
-      if (!pl->h_done[i]) OA_HIP(hipEventCreateWithFlags(&pl->h_done[i], hipEventDisableTiming));
+      if (m.h[i]) (void)hipHostFree(m.h[i]);
+      m.h[i] = nullptr;
+      m.busy[i] = false;
+      OA_HIP(hipHostMalloc((void**)&m.h[i], cap, hipHostMallocDefault));
+      if (!m.done[i]) OA_HIP(hipEventCreateWithFlags(&m.done[i], hipEventDisableTiming));
     }
-    OA_HIP(hipMalloc((void**)&pl->d_meta, cap));
-    pl->meta_cap = cap;
+    OA_HIP(hipMalloc((void**)&m.d, cap));
+    m.cap = cap;
   }
-  const int hi = pl->h_next;
-  pl->h_next ^= 1;
-  if (pl->h_busy[hi]) OA_HIP(hipEventSynchronize(pl->h_done[hi]));  // its previous copy has been read
-  uint8_t* h = pl->h_meta[hi];
+  const int hi = m.next;
+  m.next ^= 1;
+  if (m.busy[hi]) OA_HIP(hipEventSynchronize(m.done[hi]));  // its previous copy has been read
+  uint8_t* h = m.h[hi];
   // The kernels read a segment's partial slots where the planner's record has the unit and tile count.
   std::vector<int32_t> item_of_slot((size_t)hp.n_slots, -1);
   for (size_t i = 0; i < n_items; ++i)
@@ -175,9 +230,9 @@ int upload_plan(omniattn_plan_s* pl, hipStream_t stream) {
     if (hu[u].seg_lo < hu[u].seg_hi) hu[u].first = hs[hu[u].seg_lo];
   }
   if (n_items) std::memcpy(h + pl->off_combine, hp.combine.data(), n_items * sizeof(CombineItem));
-  OA_HIP(launch_copy16(pl->d_meta, h, bytes, stream));
-  OA_HIP(hipEventRecord(pl->h_done[hi], stream));
-  pl->h_busy[hi] = true;
+  OA_HIP(launch_copy16(m.d, h, bytes, stream));
+  OA_HIP(hipEventRecord(m.done[hi], stream));
+  m.busy[hi] = true;
   return OMNIATTN_OK;
 }
 
@@ -328,8 +383,8 @@ int omniattn_decode_timed(const omniattn_plan_t* plan, const void* q, const void
   dp.lse = lse;
   dp.part_lse = (float*)workspace;
   dp.part_o = workspace ? (char*)workspace + hp.part_rows_offset : nullptr;
-  dp.units = (const UnitHeader*)plan->d_meta;
-  dp.segs = (const DevSegment*)(plan->d_meta + plan->off_segs);
+  dp.units = (const UnitHeader*)plan->meta.d;
+  dp.segs = (const DevSegment*)(plan->meta.d + plan->off_segs);
   dp.xcds = plan->xcds;
   dp.H = hp.heads_total;
   dp.Hq = hp.prob.num_heads;
@@ -354,7 +409,7 @@ int omniattn_decode_timed(const omniattn_plan_t* plan, const void* q, const void
 
   if (!hp.combine.empty()) {
     CombineParams cp;
-    cp.items = (const CombineItem*)(plan->d_meta + plan->off_combine);
+    cp.items = (const CombineItem*)(plan->meta.d + plan->off_combine);
     cp.part_o = dp.part_o;
     cp.part_lse = dp.part_lse;
     cp.out = out;
