@@ -14,7 +14,7 @@
 // cycles per tile and 64 heads (6.6 K per 128) against 1.66 K of matrix instructions.  What bounds it is the
 // instruction issue of a lone wave per SIMD: about 290 vector, 100 scalar and 60 LDS instructions a tile at
 // 5 to 6 cycles each; loads switched off the loop takes 3.1 K, without PV 3.3 K, without half of S^T 3.5 K.
-// us per decode, 128 rows unless stated: 32 sequences of 8320 tokens 83 -> 75; 93 mixed 126 -> 116; 64 of
+// us per decode, 128 rows unless stated: 32 sequences of 8320 tokens 83 -> 73; 93 mixed 127 -> 124; 64 of
 // 2176 59 -> 51, two queries each 91 -> 75; 128 of 2176, 64 rows 87 -> 56.
 #include <hip/hip_runtime.h>
 #include <stdint.h>

@@ -1,5 +1,6 @@
-// gfx950 kernel for sparse MLA decode over an fp8 (e4m3) latent cache with one fp32 scale
-// per token (paper section 3.2.1: softmax(q K_M^T * scale) V_M with M = sinks + recents).
+// gfx950 kernel for sparse MLA decode over an fp8 (e4m3) latent cache, blocks of 128 head rows (taken
+// for many short sequences, whose segments start cheaper here; blocks of 64 and 32 rows have their own
+// kernels, decode_fp8_64_kernel.hip and decode_narrow_kernel.hip), with one fp32 scale per token (paper section 3.2.1: softmax(q K_M^T * scale) V_M with M = sinks + recents).
 //
 // The cache bytes are never widened: both contractions run on the 8-bit matrix instruction
 // (32x32x64, twice the bf16 rate) straight out of the LDS tiles.

@@ -368,7 +368,7 @@ int build_host_plan(HostPlan& hp, const omniattn_problem_t& prob, const int32_t*
     // The kernel with the smallest estimate is taken.  Narrow: few sequences, whose pieces would be short
     // (one sequence of 2176 kept tokens, 128 heads: 69 pieces of one tile and 69 partial rows to merge, or
     // 4 x 17 pieces of four tiles: 24.1 -> 15.4 us).  64 rows, fp8: most of the rest (32 sequences of 8320
-    // tokens, 128 heads: 83 -> 75 us; 128 of 2176, 64 heads: 87 -> 56).  128 rows: bf16, and fp8 with many short
+    // tokens, 128 heads: 83 -> 73 us; 128 of 2176, 64 heads: 87 -> 56).  128 rows: bf16, and fp8 with many short
     // sequences (256 of 1024 tokens: 76 against 93 us).
     Shape best;
     const KernelCost* kernel = nullptr;
