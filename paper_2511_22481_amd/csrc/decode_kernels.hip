@@ -142,9 +142,16 @@ __device__ __forceinline__ MergeState merge_slots(const void* part_o, const floa
       }
     }
     float mb = r.m;
+    bool empty = true;
 #pragma unroll
-    for (int k = 0; k < kBatch; ++k) mb = fmaxf(mb, l[k]);
-    if (mb == -INFINITY) continue;  // nothing but empty partials so far
+    for (int k = 0; k < kBatch; ++k) {
+      mb = fmaxf(mb, l[k]);
+      empty &= l[k] == -INFINITY;
+    }
+    if (empty) continue;
+    // (fmaxf passes over NaN: nothing but NaN and empty partials so far.  The weight of NaN below is NaN,
+    // and with it z and the row, whatever is folded in before or behind.)
+    if (mb == -INFINITY) mb = 0.f;
     r.rescale(mb);
 #pragma unroll
     for (int k = 0; k < kBatch; ++k) {

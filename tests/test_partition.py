@@ -6,6 +6,7 @@ import torch
 import paper_2511_22481_amd as oa
 import parity
 from test_abi_and_plan import check_plan
+from test_multi_query import _run
 from workloads import make_custom
 
 
@@ -54,3 +55,56 @@ def test_kernel_for_few_rows_or_few_sequences():
     assert check_plan([32768] * 2, 128, 2048, H=33).head_block == 32
     assert check_plan([20011], 128, 2048).head_block == 32
     assert check_plan([20011] * 64, 128, 2048).head_block == 128
+
+
+def _nan_at(inp, b, position):
+    inp.kv_cache[int(inp.page_table[b, position // 128]), position % 128, 100] = float("nan")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("out_dtype", [None, torch.float32])
+@pytest.mark.parametrize("heads", [16, 64, 128])
+@pytest.mark.parametrize("kv", ["bf16", "fp8"])
+def test_a_nan_partial_reaches_the_merged_row(kv, heads, out_dtype):
+    """Sequences cut into 2 .. 13 partials, one of them NaN, each in turn, beside ones without: the launch
+    merges with four waves per row (13 partials), so in an item of up to 7 some wave holds the NaN partial alone."""
+    tile = 64 if kv == "fp8" else 32
+    cuts = [(k, slot) for k in (2, 3, 4, 5, 6, 7, 13) for slot in range(k)]
+    lens = [k * tile for k, _ in cuts] + [2 * tile, 6 * tile, 13 * tile]
+    inp = make_custom(len(lens), heads, lens, 0, 4096, seed=heads, kv_dtype=kv, q_std=0.7, kv_std=0.7)
+    for b, (_, slot) in enumerate(cuts):
+        _nan_at(inp, b, slot * tile + 5)
+    inp = parity.to_device(inp)
+    out, lse, plan = parity.run_gpu(inp, out_dtype=out_dtype, num_splits_hint=13)
+    assert plan.max_splits == 13 and plan.num_partials == sum(lens) // tile * -(-heads // plan.head_block)
+    nan = torch.isnan(out).flatten(1)
+    missed = [c for b, c in enumerate(cuts) if not nan[b].all()]
+    assert not missed, f"finite rows although partial `slot` of `k` is NaN: {missed}"
+    assert not nan[len(cuts):].any()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("pieces, nan_slots", [(2, (1,)), (13, (4, 8, 12))])
+@pytest.mark.parametrize("kv", ["bf16", "fp8"])
+def test_nan_beside_an_empty_partial(kv, pieces, nan_slots):
+    """Two queries whose windows end one token apart: the later one keeps nothing of the first tile, so its
+    first partial is empty (lse -inf), and the others of the wave that merges it are NaN."""
+    tile = 64 if kv == "fp8" else 32
+    inp = make_custom(2, 2 * 16, [16 * tile] * 2, 0, (pieces - 1) * tile, seed=3, kv_dtype=kv, q_std=0.7, kv_std=0.7)
+    for slot in nan_slots:
+        _nan_at(inp, 0, (16 - pieces + slot) * tile + 7)
+    inp = parity.to_device(inp)
+    out, lse, plan = _run(inp, 2, 16, num_splits_hint=1000)
+    assert plan.max_splits == pieces
+    assert torch.isnan(out[0]).all() and not torch.isnan(out[1]).any()
+
+
+@pytest.mark.gpu
+def test_a_row_of_nan_partials_only():
+    inp = make_custom(2, 16, [300, 300], 0, 4096, seed=5, q_std=0.7, kv_std=0.7)
+    inp.q[0, 3, 17] = float("nan")                        # the logits of every token
+    inp = parity.to_device(inp)
+    for hint in (2, 4, 1000):
+        out, lse, plan = parity.run_gpu(inp, num_splits_hint=hint)
+        nan = torch.isnan(out).all(dim=-1)
+        assert nan[0, 3] and int(nan.sum()) == 1 and int(torch.isnan(out).sum()) == 512
