@@ -174,8 +174,9 @@ __device__ __forceinline__ MergeState merge_slots(const void* part_o, const floa
 
 template <bool OUT_FP32>
 __device__ __forceinline__ void write_merged(const MergeState& r, int lane, void* out, float* lse_out, size_t orow) {
-  const float inv = r.z > 0.f ? 1.0f / r.z : 0.f;
-  if (lane == 0) lse_out[orow] = r.z > 0.f ? r.m + __logf(r.z) : -INFINITY;
+  // (z is 0 for a row without a kept token, NaN for one with a retained NaN, else positive)
+  const float inv = r.z != 0.f ? 1.0f / r.z : 0.f;
+  if (lane == 0) lse_out[orow] = r.z != 0.f ? r.m + __logf(r.z) : -INFINITY;
   if constexpr (OUT_FP32) {
     float* dst = (float*)out + orow * kV + lane * 8;
     *(f32x4*)dst = f32x4{r.o[0] * inv, r.o[1] * inv, r.o[2] * inv, r.o[3] * inv};

@@ -81,6 +81,7 @@ def test_a_nan_partial_reaches_the_merged_row(kv, heads, out_dtype):
     missed = [c for b, c in enumerate(cuts) if not nan[b].all()]
     assert not missed, f"finite rows although partial `slot` of `k` is NaN: {missed}"
     assert not nan[len(cuts):].any()
+    assert torch.equal(torch.isnan(lse), nan.all(dim=1, keepdim=True).expand_as(lse))
 
 
 @pytest.mark.gpu
@@ -97,6 +98,7 @@ def test_nan_beside_an_empty_partial(kv, pieces, nan_slots):
     out, lse, plan = _run(inp, 2, 16, num_splits_hint=1000)
     assert plan.max_splits == pieces
     assert torch.isnan(out[0]).all() and not torch.isnan(out[1]).any()
+    assert torch.isnan(lse[0]).all() and not torch.isnan(lse[1]).any()
 
 
 @pytest.mark.gpu
@@ -108,3 +110,4 @@ def test_a_row_of_nan_partials_only():
         out, lse, plan = parity.run_gpu(inp, num_splits_hint=hint)
         nan = torch.isnan(out).all(dim=-1)
         assert nan[0, 3] and int(nan.sum()) == 1 and int(torch.isnan(out).sum()) == 512
+        assert torch.equal(torch.isnan(lse), nan)
