@@ -93,7 +93,8 @@ typedef struct omniattn_plan_s omniattn_plan_t; /* opaque, library-owned */
  *
  * omniattn_plan      also copies the metadata to the current HIP device so that
  *                    omniattn_decode can run: device and pinned host buffers are
- *                    allocated here (hipMalloc, hipHostMalloc), the copy itself is
+ *                    allocated here (hipMalloc, hipHostMalloc; the pinned buffers of a
+ *                    few destroyed plans are used again), the copy itself is
  *                    asynchronous on `hip_stream`, and decodes of this plan must be
  *                    ordered after it (same stream, or an event).  Work is balanced
  *                    over that device's CU count.
@@ -116,7 +117,8 @@ int omniattn_plan(omniattn_plan_t** plan_out, const omniattn_problem_t* prob,
 int omniattn_plan_update(omniattn_plan_t* plan, const int32_t* seq_lens_host, void* hip_stream);
 int omniattn_plan_host(omniattn_plan_t** plan_out, const omniattn_problem_t* prob,
                        const int32_t* seq_lens_host, int32_t num_cus);
-void omniattn_plan_destroy(omniattn_plan_t* plan); /* NULL is allowed */
+/* NULL is allowed.  Frees the plan's device metadata, which waits for the work of the device. */
+void omniattn_plan_destroy(omniattn_plan_t* plan);
 
 /* Introspection (host only, cheap). */
 size_t omniattn_plan_workspace_bytes(const omniattn_plan_t* plan); /* may be 0 */

@@ -16,16 +16,22 @@
 using namespace omniattn;
 
 namespace {
-// Device copy of a plan's metadata: one allocation holding the unit headers, the segments and the combine
-// items, filled by one asynchronous copy from one of two pinned host buffers of the same layout
-// (used in turn; an event per buffer says when its last copy has been read).
-struct MetaBuffers {
-  uint8_t* d = nullptr;
-  size_t cap = 0;
+// Two pinned host buffers of one size, used in turn; an event per buffer says when its last copy to the
+// device has been read.
+struct HostBuffers {
   uint8_t* h[2] = {nullptr, nullptr};
   hipEvent_t done[2] = {nullptr, nullptr};
   bool busy[2] = {false, false};
   int next = 0;
+  size_t cap = 0;         // 0 until all of the above are made
+  bool in_graph = false;  // a captured copy reads them at every replay
+};
+// Device copy of a plan's metadata: one allocation holding the unit headers, the segments and the combine
+// items, filled by one asynchronous copy from a host buffer of the same layout.
+struct MetaBuffers {
+  uint8_t* d = nullptr;
+  size_t cap = 0;
+  HostBuffers host;
 };
 }  // namespace
 
@@ -92,65 +98,54 @@ int init_device(int dev) {
   return OMNIATTN_OK;
 }
 
-void free_meta(MetaBuffers& m) {
-  if (m.d) (void)hipFree(m.d);
+void free_host(HostBuffers& b) {
   for (int i = 0; i < 2; ++i) {
-    if (m.h[i]) (void)hipHostFree(m.h[i]);
-    if (m.done[i]) (void)hipEventDestroy(m.done[i]);
+    if (b.h[i]) (void)hipHostFree(b.h[i]);
+    if (b.done[i]) (void)hipEventDestroy(b.done[i]);
   }
-  m = MetaBuffers{};
+  b = HostBuffers{};
 }
 
-// Buffers of destroyed plans, kept for the next one: a program that plans anew for each call paid two pinned
-// and a device allocation and their release each time (plan and decode 3 sequences of 48 heads in one call:
-// 117 us, now 39).  At most kSpare per device, of at most kSpareBytes each; the rest is freed at once.
-// Kernels of any stream may still read a destroyed plan's copy, so a buffer is taken only behind a
-// device synchronisation, which the release used to imply.
+// Host buffers of destroyed plans, kept for the next one: a program that plans anew for each call paid two
+// pinned allocations, two events and their release each time (a plan made and destroyed: 70 us, now 16; with
+// the decode of 3 sequences of 48 heads: 119, now 46).  At most kSpare per device, of at most kSpareBytes
+// each; the rest is freed at once.  The device copy is not kept, though that would save 7 us more: kernels of
+// any stream, and graphs, may still read a destroyed plan's copy.  Its release waits for them; a wait of
+// our own (hipDeviceSynchronize) breaks a capture under way on any thread.
 constexpr size_t kSpare = 2, kSpareBytes = 256 * 1024;
 std::mutex g_spare_mutex;
-MetaBuffers g_spare[kMaxDevices][kSpare];
+HostBuffers g_spare[kMaxDevices][kSpare];
 size_t g_spares[kMaxDevices] = {};
 
-bool take_spare(int dev, size_t bytes, MetaBuffers& m) {
-  MetaBuffers got;
-  {
-    std::lock_guard<std::mutex> lock(g_spare_mutex);
-    size_t& n = g_spares[dev];
-    size_t i = 0;
-    while (i < n && g_spare[dev][i].cap < bytes) ++i;
-    if (i == n) return false;
-    got = g_spare[dev][i];
-    g_spare[dev][i] = g_spare[dev][--n];
-  }
-  if (hipDeviceSynchronize() != hipSuccess) {  // (another thread captures, for instance: not now)
-    (void)hipGetLastError();
-    std::lock_guard<std::mutex> lock(g_spare_mutex);
-    if (g_spares[dev] < kSpare) {
-      g_spare[dev][g_spares[dev]++] = got;
-      return false;
+bool take_spare(int dev, size_t bytes, HostBuffers& b) {
+  std::lock_guard<std::mutex> lock(g_spare_mutex);
+  size_t& n = g_spares[dev];
+  for (size_t i = 0; i < n; ++i)
+    if (g_spare[dev][i].cap >= bytes) {
+      b = g_spare[dev][i];
+      g_spare[dev][i] = g_spare[dev][--n];
+      return true;
     }
-    free_meta(got);
-    return false;
-  }
-  got.busy[0] = got.busy[1] = false;
-  m = got;
-  return true;
+  return false;
 }
 
 void free_device(omniattn_plan_s* pl) {
-  MetaBuffers& m = pl->meta;
+  const bool waited = !pl->meta.d || hipFree(pl->meta.d) == hipSuccess;
+  pl->meta.d = nullptr;
+  pl->meta.cap = 0;
+  HostBuffers& b = pl->meta.host;
   const int dev = pl->device;
-  if (m.d && m.h[0] && m.h[1] && m.done[0] && m.done[1] && m.cap <= kSpareBytes && dev >= 0 && dev < kMaxDevices) {
+  if (waited && b.cap > 0 && b.cap <= kSpareBytes && !b.in_graph && dev >= 0 && dev < kMaxDevices) {
     std::lock_guard<std::mutex> lock(g_spare_mutex);
     if (g_spares[dev] < kSpare) {
-      g_spare[dev][g_spares[dev]++] = m;
-      m = MetaBuffers{};
+      g_spare[dev][g_spares[dev]++] = b;
+      b = HostBuffers{};
     } else {  // the larger ones stay: they serve more plans
-      for (MetaBuffers& kept : g_spare[dev])
-        if (kept.cap < m.cap) std::swap(kept, m);
+      for (HostBuffers& kept : g_spare[dev])
+        if (kept.cap < b.cap) std::swap(kept, b);
     }
   }
-  free_meta(m);
+  free_host(b);
 }
 
 int build_plan(HostPlan& hp, const omniattn_problem_t& prob, const int32_t* seq_lens, int num_cus) {
@@ -188,26 +183,38 @@ int upload_plan(omniattn_plan_s* pl, hipStream_t stream) {
   pl->off_combine = pl->off_segs + align16(n_segs * sizeof(DevSegment));
   const size_t bytes = pl->off_combine + align16(n_items * sizeof(CombineItem));
   MetaBuffers& m = pl->meta;
-  if (bytes > m.cap && !(m.cap == 0 && take_spare(pl->device, bytes, m))) {
+  HostBuffers& hb = m.host;
+  if (bytes > m.cap) {
     // (rare: a plan larger than any before it; freeing waits for the device)
-    const size_t cap = std::max<size_t>(bytes + bytes / 2 + 4096, 64 * 1024);  // (most plans need 10 to 40 KB)
     if (m.d) (void)hipFree(m.d);
     m.d = nullptr;
     m.cap = 0;
-    for (int i = 0; i < 2; ++i) {
-      if (m.h[i]) (void)hipHostFree(m.h[i]);
-      m.h[i] = nullptr;
-      m.busy[i] = false;
-      OA_HIP(hipHostMalloc((void**)&m.h[i], cap, hipHostMallocDefault));
-      if (!m.done[i]) OA_HIP(hipEventCreateWithFlags(&m.done[i], hipEventDisableTiming));
+    if (hb.cap < bytes && !(!hb.h[0] && take_spare(pl->device, bytes, hb))) {
+      const size_t cap = std::max<size_t>(bytes + bytes / 2 + 4096, 64 * 1024);  // (most plans need 10 to 40 KB)
+      hb.cap = 0;
+      for (int i = 0; i < 2; ++i) {
+        if (hb.h[i]) (void)hipHostFree(hb.h[i]);
+        hb.h[i] = nullptr;
+        hb.busy[i] = false;
+        OA_HIP(hipHostMalloc((void**)&hb.h[i], cap, hipHostMallocDefault));
+        if (!hb.done[i]) OA_HIP(hipEventCreateWithFlags(&hb.done[i], hipEventDisableTiming));
+      }
+      hb.cap = cap;
     }
-    OA_HIP(hipMalloc((void**)&m.d, cap));
-    m.cap = cap;
+    OA_HIP(hipMalloc((void**)&m.d, hb.cap));
+    m.cap = hb.cap;
   }
-  const int hi = m.next;
-  m.next ^= 1;
-  if (m.busy[hi]) OA_HIP(hipEventSynchronize(m.done[hi]));  // its previous copy has been read
-  uint8_t* h = m.h[hi];
+  const int hi = hb.next;
+  hb.next ^= 1;
+  if (hb.busy[hi]) OA_HIP(hipEventSynchronize(hb.done[hi]));  // its previous copy has been read
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &capture) != hipSuccess) {
+    (void)hipGetLastError();  // (the launch below reports on itself)
+    hb.in_graph = true;
+  } else if (capture != hipStreamCaptureStatusNone) {
+    hb.in_graph = true;
+  }
+  uint8_t* h = hb.h[hi];
   // The kernels read a segment's partial slots where the planner's record has the unit and tile count.
   std::vector<int32_t> item_of_slot((size_t)hp.n_slots, -1);
   for (size_t i = 0; i < n_items; ++i)
@@ -231,8 +238,8 @@ int upload_plan(omniattn_plan_s* pl, hipStream_t stream) {
   }
   if (n_items) std::memcpy(h + pl->off_combine, hp.combine.data(), n_items * sizeof(CombineItem));
   OA_HIP(launch_copy16(m.d, h, bytes, stream));
-  OA_HIP(hipEventRecord(m.done[hi], stream));
-  m.busy[hi] = true;
+  OA_HIP(hipEventRecord(hb.done[hi], stream));
+  hb.busy[hi] = true;
   return OMNIATTN_OK;
 }
 

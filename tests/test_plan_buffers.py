@@ -1,5 +1,7 @@
 """Plans that come and go: the buffers of a destroyed plan serve the next one, also while another stream
-still decodes with the destroyed plan's copy."""
+still decodes with the destroyed plan's copy.  Making a plan waits for no stream and breaks no capture."""
+import threading
+
 import pytest
 import torch
 
@@ -35,3 +37,66 @@ def test_buffers_of_destroyed_plans_are_reused_safely(kv):
     torch.cuda.synchronize()
     for k, out, lse, _ in got:
         assert torch.equal(out, want[k][0]) and torch.equal(lse, want[k][1])
+
+
+def _spare_buffers():
+    """Leaves buffers of destroyed plans behind, for the next plan to take."""
+    plans = [_small_plan(None) for _ in range(3)]
+    for p in plans:
+        p.destroy()
+    torch.cuda.synchronize()
+
+
+def _small_plan(stream):
+    return oa.omniattn_plan([700, 900], stream=stream, batch=2, num_heads=64, max_pages_per_seq=8, num_pages=16, sink=16,
+                            window=256, softmax_scale=0.1)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("mode, thread", [("thread_local", True), ("relaxed", True), ("relaxed", False)])
+def test_a_plan_is_made_while_a_stream_captures(mode, thread):
+    """The modes in which hipMalloc is allowed: a plan can be made (on a stream that does not capture) and
+    destroyed, and the capture comes out whole."""
+    _spare_buffers()
+    side, other, x, made = torch.cuda.Stream(), torch.cuda.Stream(), torch.zeros(64, device="cuda"), []
+
+    def make():
+        for _ in range(2):
+            made.append(_small_plan(other))
+            made[-1].destroy()
+        made.append(_small_plan(other))
+
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side, capture_error_mode=mode):
+        x.add_(1)
+        if thread:
+            t = threading.Thread(target=make)
+            t.start()
+            t.join()
+        else:
+            make()
+        x.add_(1)
+    assert len(made) == 3 and made[-1].num_units > 0
+    x.zero_()
+    for rep in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert float(x[5]) == 2 * (rep + 1)
+
+
+@pytest.mark.gpu
+def test_making_a_plan_waits_for_no_stream():
+    _spare_buffers()
+    busy, done = torch.cuda.Stream(), torch.cuda.Event()
+    a = torch.randn(8192, 8192, device="cuda", dtype=torch.bfloat16)
+    with torch.cuda.stream(busy):
+        a @ a
+    torch.cuda.synchronize()
+    with torch.cuda.stream(busy):
+        for _ in range(60):                              # 1 ms each
+            a @ a
+        done.record()
+    plan = _small_plan(torch.cuda.current_stream())
+    still_running = not done.query()
+    torch.cuda.synchronize()
+    assert still_running and plan.num_units > 0
