@@ -98,6 +98,7 @@ int fill_units(const std::vector<int32_t>& tiles, int n_hb, int cap, int seg, Em
 struct Shape {
   enum { kFill, kWhole, kEven } kind = kFill;
   int size = 0;                  // kFill: capacity of a unit; kEven: tiles of a piece
+  int64_t slots = 0;             // partial rows it leaves
   double us = INFINITY;
   std::vector<int32_t> unit_of;  // kWhole: unit of every item (empty: one item to a unit)
 };
@@ -199,6 +200,7 @@ Shape choose_shape(const std::vector<int32_t>& tiles, int n_hb, int num_cus, con
       if (slots <= most_slots && take(p + cost.seg + merge_cost(slots))) {
         r.kind = Shape::kEven;
         r.size = p;
+        r.slots = slots;
       }
     }
   }
@@ -245,6 +247,7 @@ Shape choose_shape(const std::vector<int32_t>& tiles, int n_hb, int num_cus, con
     if (take(longest + merge_cost(slots))) {
       r.kind = Shape::kFill;
       r.size = cap;
+      r.slots = slots;
     }
   }
   if (found) r.us = best * cost.tile_us;
@@ -370,24 +373,37 @@ int build_host_plan(HostPlan& hp, const omniattn_problem_t& prob, const int32_t*
     // 4 x 17 pieces of four tiles: 24.1 -> 15.4 us).  64 rows, fp8: most of the rest (32 sequences of 8320
     // tokens, 128 heads: 83 -> 73 us; 128 of 2176, 64 heads: 87 -> 56).  128 rows: bf16, and fp8 with many short
     // sequences (256 of 1024 tokens: 76 against 93 us).
+    const auto most_slots = [&](int head_block) {  // (+ 1: room for alignment)
+      return (int)(OMNIATTN_STATIC_SCRATCH_BYTES / ((size_t)head_block * (sizeof(float) + kV * elt) + 1));
+    };
     Shape best;
-    const KernelCost* kernel = nullptr;
+    KernelCost kernel{};
     for (const KernelCost* k : kernels) {
       const int n_hb = blocks_of(k->head_block);
-      const size_t slot_bytes = (size_t)k->head_block * (sizeof(float) + kV * elt) + 1;  // (+ 1: room for alignment)
-      const int most_slots = (int)(OMNIATTN_STATIC_SCRATCH_BYTES / slot_bytes);
-      Shape s = choose_shape(tiles, n_hb, num_cus, *k, most_slots, best.us);
+      Shape s = choose_shape(tiles, n_hb, num_cus, *k, most_slots(k->head_block), best.us);
       if (s.us >= best.us) continue;
-      if (kernel && s.kind == Shape::kFill) {  // (not at the price of a plan that omniattn_decode_static would refuse)
-        int64_t slots = 0;
-        fill_units(tiles, n_hb, s.size, k->seg, [&](int b, int, int lo, int hi, int) { slots += hi - lo < tiles[b]; });
-        if (slots > most_slots) continue;
-      }
+      // (not at the price of a plan that omniattn_decode_static would refuse)
+      if (k != kernels[0] && s.slots > most_slots(k->head_block)) continue;
       best = std::move(s);
-      kernel = k;
+      kernel = *k;
     }
-    hp.head_block = kernel->head_block;
-    lay_out(best, tiles, blocks_of(hp.head_block), num_cus, *kernel, hp.segs, hp.unit_seg);
+    // Units filled by tiles alone: a segment that costs as much as several tiles moves the cuts, and now and then
+    // (two of 3000 random problems) that makes a few partial rows more than the built-in scratch buffer holds.
+    // Then the cuts stay where one tile a segment puts them, if those fit.
+    if (best.slots > most_slots(kernel.head_block)) {
+      const int n_hb = blocks_of(wide.head_block), n = prob.batch * n_hb;
+      int cap = std::max((int)std::min<int64_t>((sum_tiles * n_hb + n + num_cus - 1) / num_cus, INT32_MAX / 2), 2);
+      for (int i = 0; i < 64 && fill_units(tiles, n_hb, cap, 1, [](int, int, int, int, int) {}) > num_cus; ++i) ++cap;
+      int64_t slots = 0;
+      fill_units(tiles, n_hb, cap, 1, [&](int b, int, int lo, int hi, int) { slots += hi - lo < tiles[b]; });
+      if (slots <= most_slots(wide.head_block)) {
+        best.size = cap;
+        kernel = wide;
+        kernel.seg = 1;
+      }
+    }
+    hp.head_block = kernel.head_block;
+    lay_out(best, tiles, blocks_of(hp.head_block), num_cus, kernel, hp.segs, hp.unit_seg);
   }
   hp.n_hb = blocks_of(hp.head_block);
 

@@ -39,6 +39,25 @@ def test_short_pieces_stay_inside_the_static_scratch(out_dtype):
     assert 64 <= p.num_partials and p.workspace_bytes <= oa.omniattn_static_scratch_bytes()
 
 
+@pytest.mark.parametrize("batch, length, heads, q_len, sink, window",
+                         [(29, 8000, 48, 8, 64, 1212), (88, 13124, 33, 2, 0, 1369)])
+def test_filled_units_stay_inside_the_static_scratch(batch, length, heads, q_len, sink, window):
+    """With the measured cost of a segment the fill cuts these into 319 and 323 partials, 41.98 and 42.5 MB of
+    partial rows; at a cost of one tile into 313 and 317, which the buffer holds."""
+    p = oa.omniattn_plan_host([length] * batch, batch=batch, num_heads=heads, max_pages_per_seq=110, num_pages=1 << 14, sink=sink,
+                              window=window, softmax_scale=0.1, q_len=q_len)
+    assert 0 < p.workspace_bytes <= oa.omniattn_static_scratch_bytes()
+    check_segments(p, batch)
+
+
+def check_segments(p, batch):
+    segs, ends = p.segments(), {}
+    for s in segs:
+        assert s["tile_lo"] == ends.get((s["b"], s["hb"]), 0) and s["tile_hi"] > s["tile_lo"] and s["unit"] < p.num_units
+        ends[s["b"], s["hb"]] = s["tile_hi"]
+    assert {b for b, _ in ends} == set(range(batch)) and all(ends[s["b"], s["hb"]] == s["ntiles"] for s in segs)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("out_dtype", [None, torch.float32])
 @pytest.mark.parametrize("hint", [8, 9, 13, 1000])
