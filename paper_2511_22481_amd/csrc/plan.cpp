@@ -37,23 +37,88 @@ constexpr KernelCost kNarrowFp8 = {kHeadsPerWave, 1.5, 7, 2.7, 114.0};
 // Do not leave slivers shorter than this many tiles unless the item itself is shorter.
 constexpr int kMinSegTiles = 2;
 
+// The sequences' tile counts: each sequence is n_hb items of that many.
+struct Items {
+  std::vector<int32_t> tiles;                        // per sequence
+  std::vector<std::pair<int32_t, int32_t>> by_size;  // (tiles, sequences of that many), largest first
+  int64_t sum = 0;                                   // of `tiles`
+  int most = 0, least = 0;
+
+  void count() {
+    by_size.clear();
+    by_size.reserve(16);
+    // (windows make most sequences alike, and a batch of any lengths spans a few hundred counts)
+    const int64_t span = (int64_t)most - least + 1;
+    if (span <= 16 * (int64_t)tiles.size() + 256) {
+      std::vector<int32_t> times(span, 0);
+      for (int t : tiles) ++times[t - least];
+      for (int64_t k = span - 1; k >= 0; --k)
+        if (times[k]) by_size.emplace_back((int32_t)(least + k), times[k]);
+    } else {
+      std::vector<int32_t> sorted(tiles);
+      std::sort(sorted.begin(), sorted.end(), std::greater<int32_t>());
+      for (int t : sorted) {
+        if (by_size.empty() || by_size.back().first != t) by_size.emplace_back(t, 0);
+        ++by_size.back().second;
+      }
+    }
+  }
+  // Pieces of at most p tiles per head block, and those of sequences that are cut (an empty sequence is a piece too).
+  int64_t cut_pieces(int p) const {
+    int64_t k = 0;
+    for (size_t i = 0; i < by_size.size() && by_size[i].first > p; ++i)
+      k += (int64_t)((by_size[i].first + p - 1) / p) * by_size[i].second;
+    return k;
+  }
+  int64_t pieces(int p) const {
+    int64_t k = 0, whole = (int64_t)tiles.size();
+    for (size_t i = 0; i < by_size.size() && by_size[i].first > p; ++i) {
+      k += (int64_t)((by_size[i].first + p - 1) / p) * by_size[i].second;
+      whole -= by_size[i].second;
+    }
+    return k + whole;
+  }
+};
+
 // Deals the items (sequence b, head block hb) in order to units of capacity `cap` (tiles plus `seg` per
 // segment), cutting an item where a unit is full.  emit(b, hb, tile_lo, tile_hi, unit) for every segment;
-// returns the number of units used.
+// stops where more than `most_units` units are needed.
+struct Filled {
+  int units = 0;      // units used (one more than `most_units`: they do not do)
+  int longest = 0;    // tiles and segments of the longest
+  int64_t slots = 0;  // segments of items that are cut
+  double need = 0;    // the capacity that the work seen so far and the rest would fill evenly
+};
 template <typename Emit>
-int fill_units(const std::vector<int32_t>& tiles, int n_hb, int cap, int seg, Emit emit) {
+Filled fill_units(const Items& items, int n_hb, int cap, int seg, int most_units, Emit emit) {
+  Filled f;
   int load = 0, unit = 0;
   auto close_unit = [&]() {
     if (load > 0) {
+      f.longest = std::max(f.longest, load);
       ++unit;
       load = 0;
     }
   };
-  for (int b = 0; b < (int)tiles.size(); ++b)
+  const int batch = (int)items.tiles.size();
+  int64_t rest = items.sum * n_hb;
+  for (int b = 0; b < batch; ++b) {
+    const int ntiles = items.tiles[b];
     for (int hb = 0; hb < n_hb; ++hb) {
-      const int ntiles = tiles[b];
+      if (unit >= most_units) {
+        f.units = unit + 1;
+        f.need = (double)cap * unit / most_units + (double)(rest + ((int64_t)(batch - b) * n_hb - hb) * seg) / most_units;
+        return f;
+      }
+      rest -= ntiles;
+      if (ntiles <= cap - load - seg && ntiles <= kMaxSegTiles) {  // (as below, at once)
+        emit(b, hb, 0, ntiles, unit);
+        load += ntiles + seg;
+        if (load >= cap) close_unit();
+        continue;
+      }
       if (ntiles == 0) {  // empty retained set: one segment that only writes zeros / -inf
-        if (load + seg > cap) close_unit();
+        close_unit();
         emit(b, hb, 0, 0, unit);
         load += seg;
         continue;
@@ -70,14 +135,49 @@ int fill_units(const std::vector<int32_t>& tiles, int n_hb, int cap, int seg, Em
         int take = std::min(std::min(rem, room), kMaxSegTiles);
         // avoid leaving a sliver behind
         if (rem - take > 0 && rem - take < kMinSegTiles) take = std::max(1, rem - kMinSegTiles);
+        f.slots += take < ntiles;
         emit(b, hb, done, done + take, unit);
         done += take;
         load += take + seg;
         if (load >= cap) close_unit();
       }
     }
+  }
+  f.need = ((double)cap * unit + load) / most_units;
   close_unit();
-  return unit;
+  f.units = unit;
+  return f;
+}
+inline Filled measure_fill(const Items& items, int n_hb, int cap, int seg, int most_units) {
+  return fill_units(items, n_hb, cap, seg, most_units, [](int, int, int, int, int) {});
+}
+
+// Loads of units that are dealt whole items, largest first, each to the unit with the least work so far: at
+// most the average and one item.  Costs are small integers, so the units stand in lists by their load.
+inline size_t most_load(const Items& items, int n_hb, int num_cus, int seg) {
+  const int64_t n = (int64_t)items.tiles.size() * n_hb;
+  return (size_t)((items.sum * n_hb + n * seg) / num_cus + items.most + seg + 1);
+}
+constexpr size_t kMostLoad = 1 << 22;  // a bound on the lists (a million items of 1024 tiles for 256 units)
+// The longest of them (or any load of at least `limit` if it is none below).
+int deal_whole(const Items& items, int n_hb, int num_cus, int seg, double limit) {
+  std::vector<int32_t> units(most_load(items, n_hb, num_cus, seg) + 1, 0);  // how many at this load
+  units[0] = num_cus;
+  int longest = 0;
+  size_t least = 0;
+  for (const auto& s : items.by_size) {
+    const int cost = s.first + seg;
+    for (int64_t left = (int64_t)s.second * n_hb; left > 0;) {
+      while (units[least] == 0) ++least;
+      const int32_t k = (int32_t)std::min<int64_t>(left, units[least]);
+      units[least] -= k;
+      units[least + cost] += k;
+      left -= k;
+      longest = std::max(longest, (int)least + cost);
+      if (longest >= limit) return longest;
+    }
+  }
+  return longest;
 }
 
 // Work partition over `num_cus` compute units that all start together: the launch lasts as long
@@ -93,53 +193,31 @@ int fill_units(const std::vector<int32_t>& tiles, int n_hb, int cap, int seg, Em
 //          when the item count is not near a multiple or divisor of the unit count.
 //
 // The estimates come first and only the partition that is taken is laid out: a serving loop plans again
-// for every decode step, and searching the fill of three kernels to the end took 30 us of host time
-// (40 sequences) where this takes 5.
+// for every decode step.  Bounds from the tile counts rule out most of the rest before any search.  us on one
+// 2.7 GHz core, 256 units, before this choice / now: 64 sequences alike 4.4 / 2.5; fp8, three kernels: 93 of
+// 1024 to 65536 tokens, window 4096 7.6 / 6.2; 256 of 512 to 32768, all kept 12 / 14; 1000 of them 34 / 44.
 struct Shape {
   enum { kFill, kWhole, kEven } kind = kFill;
   int size = 0;                  // kFill: capacity of a unit; kEven: tiles of a piece
   int64_t slots = 0;             // partial rows it leaves
   double us = INFINITY;
-  std::vector<int32_t> unit_of;  // kWhole: unit of every item (empty: one item to a unit)
 };
 
-// `tiles`: per sequence; every sequence is n_hb items of that many.  `most_slots`: partial slots that fit
-// the built-in scratch buffer; even pieces are not cut so short that omniattn_decode_static would refuse
-// the plan.  Returns an estimate of `limit_us` or more when nothing below it exists.
-Shape choose_shape(const std::vector<int32_t>& tiles, int n_hb, int num_cus, const KernelCost& cost, int most_slots,
-                   double limit_us) {
+// No partition with this kernel takes fewer tiles' time: some unit has at least the average.
+inline double least_tiles(const Items& items, int n_hb, int num_cus, const KernelCost& cost) {
+  const double tiles = (double)items.sum * n_hb / num_cus, n = (double)items.tiles.size() * n_hb;
+  return std::max(tiles + cost.seg, tiles + n * cost.seg / num_cus);
+}
+
+// `most_slots`: partial slots that fit the built-in scratch buffer; even pieces are not cut so short that
+// omniattn_decode_static would refuse the plan.  Returns an estimate of `limit_us` or more when nothing below it
+// exists.
+Shape choose_shape(const Items& items, int n_hb, int num_cus, const KernelCost& cost, int most_slots, double limit_us) {
   Shape r;
-  const int n = (int)tiles.size() * n_hb;
-  int64_t sum = 0;
-  int n_max = 0;
-  for (int t : tiles) {
-    sum += t;
-    n_max = std::max(n_max, t);
-  }
-  sum *= n_hb;
+  const int64_t n = (int64_t)items.tiles.size() * n_hb;
+  const int64_t sum = items.sum * n_hb;
+  const int n_max = items.most, seg = cost.seg;
   auto merge_cost = [&](int64_t slots) { return slots ? cost.combine + slots / cost.slots_per_tile : 0.0; };
-  // Tile counts with how often they occur: windows make most sequences alike, and the sums over all items
-  // below are then sums over a few entries.
-  std::vector<std::pair<int32_t, int32_t>> counts;
-  counts.reserve(tiles.size());
-  for (int t : tiles) {
-    const size_t known = std::min<size_t>(counts.size(), 16);
-    size_t k = 0;
-    while (k < known && counts[k].first != t) ++k;
-    if (k < known) ++counts[k].second;
-    else counts.emplace_back(t, 1);
-  }
-  auto pieces_at = [&](int p) {  // pieces of at most p tiles
-    int64_t k = 0;
-    for (const auto& c : counts) k += (int64_t)(c.first > p ? (c.first + p - 1) / p : 1) * c.second;
-    return k * n_hb;
-  };
-  auto cut_pieces_at = [&](int p) {  // those of items that are cut
-    int64_t k = 0;
-    for (const auto& c : counts)
-      if (c.first > p) k += (int64_t)((c.first + p - 1) / p) * c.second;
-    return k * n_hb;
-  };
   double best = limit_us / cost.tile_us;  // in tiles, as all below
   bool found = false;
   auto take = [&](double t) {
@@ -147,57 +225,44 @@ Shape choose_shape(const std::vector<int32_t>& tiles, int n_hb, int num_cus, con
     best = t;
     return found = true;
   };
-  // (some unit has at least the average tiles, and a segment)
-  if ((double)sum / num_cus + cost.seg >= best) return r;
+  if (least_tiles(items, n_hb, num_cus, cost) >= best) return r;
 
   // whole (a segment's tile table holds kMaxSegTiles)
   if (n_max <= kMaxSegTiles) {
     if (n <= num_cus) {
-      if (take(n_max + cost.seg)) r.kind = Shape::kWhole;
-    } else if ((double)(sum + (int64_t)n * cost.seg) / num_cus < best && n_max + cost.seg < best) {
-      std::vector<int32_t> order(n), unit_of(n);
-      for (int i = 0; i < n; ++i) order[i] = i;
-      std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return tiles[a / n_hb] > tiles[b / n_hb]; });
-      std::vector<std::pair<int32_t, int32_t>> heap;  // (load, unit), least loaded on top
-      heap.reserve(num_cus);
-      const auto later = std::greater<std::pair<int32_t, int32_t>>();
-      int longest = 0;
-      for (int i = 0; i < n && longest < best; ++i) {
-        const int cost_i = tiles[order[i] / n_hb] + cost.seg;
-        int unit = i, load = cost_i;
-        if (i < num_cus) {
-          heap.emplace_back(load, unit);
-          if (i == num_cus - 1) std::make_heap(heap.begin(), heap.end(), later);
-        } else {
-          std::pop_heap(heap.begin(), heap.end(), later);
-          unit = heap.back().second;
-          load = heap.back().first += cost_i;
-          std::push_heap(heap.begin(), heap.end(), later);
+      if (take(n_max + seg)) r.kind = Shape::kWhole;
+    } else if (most_load(items, n_hb, num_cus, seg) < kMostLoad) {
+      // (of the j * num_cus + 1 largest items some unit has j + 1)
+      int bound = n_max + seg;
+      int64_t seen = 0, j = 1;
+      for (const auto& s : items.by_size) {
+        seen += (int64_t)s.second * n_hb;
+        if (seen > j * num_cus) {
+          j = (seen - 1) / num_cus;
+          bound = (int)std::min<int64_t>(std::max<int64_t>(bound, (j + 1) * (s.first + seg)), INT32_MAX / 2);
+          ++j;
         }
-        unit_of[order[i]] = unit;
-        longest = std::max(longest, load);
       }
-      if (take(longest)) {
-        r.kind = Shape::kWhole;
-        r.unit_of = std::move(unit_of);
-      }
+      if (bound < best && take(deal_whole(items, n_hb, num_cus, seg, best))) r.kind = Shape::kWhole;
     }
   }
   // even: the smallest piece that needs no more pieces than there are units
-  if (n <= num_cus && n_max > 1) {
-    int bad = (int)((sum - 1) / num_cus), good = n_max;  // (shorter pieces than the average are too many; one piece per item fits)
+  const int average = (int)std::min<int64_t>((sum + num_cus - 1) / num_cus, INT32_MAX / 2);
+  if (n <= num_cus && n_max > 1 && average + seg < best) {
+    int bad = average - 1, good = n_max;  // (shorter pieces than the average are too many; one piece per item fits)
+    if (n < num_cus) good = std::min<int64_t>(good, sum / (num_cus - n) + 1);  // (fewer than sum / p + n pieces)
     while (good - bad > 1) {
       const int mid = bad + (good - bad) / 2;
-      (pieces_at(mid) > num_cus ? bad : good) = mid;
+      (items.pieces(mid) * n_hb > num_cus ? bad : good) = mid;
     }
     // (with few items the shortest pieces give more partial rows than they save tiles: sum / p
     // slots cost sum / p / slots_per_tile, which balances p at the square root below)
     const int balanced = (int)std::sqrt((double)sum / cost.slots_per_tile);
     for (int p : {good, std::max(good, balanced), 2 * good}) {
       p = std::min({p, n_max, kMaxSegTiles});
-      if (p + cost.seg >= best || pieces_at(p) > num_cus) continue;
-      const int64_t slots = cut_pieces_at(p);
-      if (slots <= most_slots && take(p + cost.seg + merge_cost(slots))) {
+      if (p + seg >= best || items.pieces(p) * n_hb > num_cus) continue;
+      const int64_t slots = items.cut_pieces(p) * n_hb;
+      if (slots <= most_slots && take(p + seg + merge_cost(slots))) {
         r.kind = Shape::kEven;
         r.size = p;
         r.slots = slots;
@@ -205,68 +270,108 @@ Shape choose_shape(const std::vector<int32_t>& tiles, int n_hb, int num_cus, con
     }
   }
   // fill: the smallest capacity that needs no more units than there are, if one can win at all
-  auto units_at = [&](int cap) { return fill_units(tiles, n_hb, cap, cost.seg, [](int, int, int, int, int) {}); };
-  int lo = (int)std::min<int64_t>((sum + (int64_t)n * cost.seg + num_cus - 1) / num_cus, INT32_MAX / 2);
-  lo = std::max(lo, cost.seg + 1);
-  // (a capacity that gives no more than whole items may come without a merge; then `whole` is as good)
-  const double cap_max = found || best < INFINITY ? best - cost.combine : INFINITY;
-  // (a capacity c gives segments of at most c - seg tiles: at least that many of them, and slots)
-  bool worth_it = cap_max == INFINITY;
-  for (int c = lo; !worth_it && c < cap_max; ++c) {
-    if (sum + cost.seg * pieces_at(c - cost.seg) > (int64_t)num_cus * c) {
-      if (c == lo) ++lo;
-      continue;
-    }
-    worth_it = c + merge_cost(cut_pieces_at(c - cost.seg)) < best;
-  }
-  int cap = 0;
-  if (worth_it) {  // upwards from the bound, which is close, then back to the smallest
-    int bad = lo - 1, step = 1;
-    while (lo < cap_max && step < (1 << 28) && units_at(lo) > num_cus) {
-      bad = lo;
-      lo += step;
+  const int64_t least = std::max<int64_t>((sum + n * seg + num_cus - 1) / num_cus, seg + 1);
+  int lo = (int)std::min<int64_t>(least, INT32_MAX / 2);
+  // (a capacity c gives segments of at most c - seg tiles: at least that many of them)
+  auto too_small = [&](int c) { return sum + seg * items.pieces(c - seg) * n_hb > (int64_t)num_cus * c; };
+  if (lo < INT32_MAX / 4 && too_small(lo)) {
+    int bad = lo, step = 1;
+    while (too_small(bad + step)) {
+      bad += step;
       step *= 2;
     }
-    if (lo < cap_max) {
-      cap = lo;
-      while (cap - bad > 1) {
-        const int mid = bad + (cap - bad) / 2;
-        (units_at(mid) > num_cus ? bad : cap) = mid;
-      }
+    lo = bad + step;
+    while (lo - bad > 1) {
+      const int mid = bad + (lo - bad) / 2;
+      (too_small(mid) ? bad : lo) = mid;
     }
   }
-  if (cap > 0) {
-    int64_t slots = 0;
-    int longest = 0, load = 0, last_unit = -1;
-    fill_units(tiles, n_hb, cap, cost.seg, [&](int b, int, int lo_t, int hi_t, int unit) {
-      if (hi_t - lo_t < tiles[b]) ++slots;
-      load = (unit == last_unit ? load : 0) + hi_t - lo_t + cost.seg;
-      last_unit = unit;
-      longest = std::max(longest, load);
-    });
-    if (take(longest + merge_cost(slots))) {
+  // (a capacity that gives no more than whole items may come without a merge; then `whole` is as good)
+  const double cap_max = best < INFINITY ? best - cost.combine : INFINITY;
+  // Whether some capacity of [a, z) can win: a capacity gives at least the slots of a larger one.
+  auto at_least = [&](int a, int z) { return a + merge_cost(items.cut_pieces(z - 1 - seg) * n_hb); };
+  auto can_win = [&](auto& self, int a, int z) -> bool {
+    if (a >= z || at_least(a, z) >= best) return false;
+    if (z - a == 1 || at_least(a, a + 1) < best) return true;
+    const int mid = a + (z - a) / 2;
+    return self(self, a + 1, mid + 1) || self(self, mid + 1, z);
+  };
+  if (cap_max < INFINITY && !can_win(can_win, lo, (int)std::min(std::ceil(cap_max), INT32_MAX / 2.0))) {
+    if (found) r.us = best * cost.tile_us;
+    return r;
+  }
+  // Nearly every unit ends inside an item, which is a segment more than the items have: the smallest capacity that
+  // does lies there, and each try says how much the units would hold evenly.  One or two tries.
+  int bad = lo - 1, cap = 0, step = 1;
+  Filled f;
+  for (int c = std::max(lo, (int)std::min<int64_t>(least + seg - 1, INT32_MAX / 2)); c < cap_max && step < (1 << 28);) {
+    const Filled g = measure_fill(items, n_hb, c, seg, num_cus);
+    const int even = (int)std::min(std::ceil(g.need), INT32_MAX / 2.0);
+    if (g.units <= num_cus) {
+      cap = c;
+      f = g;
+      if (cap - bad <= 1 || even >= cap) break;
+      c = std::max(even, bad + 1);
+    } else {
+      bad = c;
+      if (cap - bad == 1) break;
+      c = std::max(even, bad + step);
+      if (cap) c = std::min(c, cap - 1);
+      step *= 2;
+    }
+  }
+  if (!cap && best == INFINITY) {  // (more units than compute units, then)
+    cap = bad;
+    f = measure_fill(items, n_hb, cap, seg, INT_MAX);
+  }
+  if (cap) {
+    if (take(f.longest + merge_cost(f.slots))) {
       r.kind = Shape::kFill;
       r.size = cap;
-      r.slots = slots;
+      r.slots = f.slots;
     }
   }
   if (found) r.us = best * cost.tile_us;
   return r;
 }
 
-void lay_out(const Shape& shape, const std::vector<int32_t>& tiles, int n_hb, int num_cus, const KernelCost& cost,
-             std::vector<Segment>& segs, std::vector<int32_t>& unit_seg) {
-  segs.clear();
-  segs.reserve(2 * (size_t)num_cus + tiles.size() * n_hb);
-  unit_seg.reserve(num_cus + 1);
-  unit_seg.assign(1, 0);
-  auto add = [&](int b, int hb, int lo, int hi, int unit) {
-    while ((int)unit_seg.size() <= unit) unit_seg.push_back((int32_t)segs.size());
-    segs.push_back({b, hb, lo, hi, -1, unit, 0, tiles[b]});
-  };
+// Appends segments to a plan, units in ascending order, the pieces of an item one behind the other; an item
+// that is cut gets its partial slots and its entry for the merge on the way.
+struct Writer {
+  HostPlan& hp;
+  const std::vector<int32_t>& tiles;
+  int last_unit = -1;
+
+  Writer(HostPlan& plan, const std::vector<int32_t>& t, size_t segments, size_t units, size_t cut) : hp(plan), tiles(t) {
+    hp.segs.clear();
+    hp.segs.reserve(segments);
+    hp.unit_seg.clear();
+    hp.unit_seg.reserve(units + 1);
+    hp.combine.clear();
+    hp.combine.reserve(cut);
+    hp.n_slots = 0;
+    hp.max_splits = 1;
+  }
+  void operator()(int b, int hb, int lo, int hi, int unit) {
+    if (unit != last_unit) hp.unit_seg.push_back((int32_t)hp.segs.size());
+    last_unit = unit;
+    int slot = -1;
+    if (hi - lo < tiles[b]) {
+      slot = hp.n_slots++;
+      if (lo == 0) hp.combine.push_back({b, hb, slot, 0});
+      hp.max_splits = std::max(hp.max_splits, ++hp.combine.back().nslots);
+    }
+    hp.segs.push_back({b, hb, lo, hi, slot, unit, hp.seq_lens[b], tiles[b]});
+  }
+  void finish() { hp.unit_seg.push_back((int32_t)hp.segs.size()); }
+};
+
+void lay_out(const Shape& shape, const Items& items, int n_hb, int num_cus, const KernelCost& cost, HostPlan& hp) {
+  const std::vector<int32_t>& tiles = items.tiles;
+  Writer add(hp, tiles, tiles.size() * n_hb + (size_t)shape.slots, num_cus, (size_t)shape.slots / 2);
   const int batch = (int)tiles.size(), n = batch * n_hb;
   if (shape.kind == Shape::kFill) {
-    fill_units(tiles, n_hb, shape.size, cost.seg, add);
+    fill_units(items, n_hb, shape.size, cost.seg, INT_MAX, [&](int b, int hb, int lo, int hi, int u) { add(b, hb, lo, hi, u); });
   } else if (shape.kind == Shape::kEven) {
     int unit = 0;
     for (int b = 0; b < batch; ++b) {
@@ -274,19 +379,46 @@ void lay_out(const Shape& shape, const std::vector<int32_t>& tiles, int n_hb, in
       for (int hb = 0; hb < n_hb; ++hb)
         for (int s = 0; s < k; ++s) add(b, hb, (int)((int64_t)t * s / k), (int)((int64_t)t * (s + 1) / k), unit++);
     }
-  } else if (shape.unit_of.empty()) {
+  } else if (n <= num_cus) {
     for (int i = 0; i < n; ++i) add(i / n_hb, i % n_hb, 0, tiles[i / n_hb], i);
   } else {
+    // sequences by size, as deal_whole takes them
+    std::vector<int32_t> at_size(items.most + 2, 0), order(batch);
+    for (int t : tiles) ++at_size[items.most - t + 1];
+    for (int k = 0; k <= items.most; ++k) at_size[k + 1] += at_size[k];
+    for (int b = 0; b < batch; ++b) order[at_size[items.most - tiles[b]]++] = b;
+    // units in lists by their load, first in, first out
+    struct List { int32_t head, tail; };
+    std::vector<List> at_load(most_load(items, n_hb, num_cus, cost.seg) + 1, List{-1, -1});
+    std::vector<int32_t> behind(num_cus, -1), first(num_cus + 1, 0), unit_of(n), item_at(n);
+    auto append = [&](int unit, size_t load) {
+      List& l = at_load[load];
+      behind[unit] = -1;
+      (l.head < 0 ? l.head : behind[l.tail]) = unit;
+      l.tail = unit;
+    };
+    for (int u = 0; u < num_cus; ++u) append(u, 0);
+    size_t least = 0;
+    for (int b : order)
+      for (int hb = 0; hb < n_hb; ++hb) {
+        while (at_load[least].head < 0) ++least;
+        const int unit = at_load[least].head;
+        at_load[least].head = behind[unit];
+        append(unit, least + tiles[b] + cost.seg);
+        unit_of[b * n_hb + hb] = unit;
+        ++first[unit + 1];
+      }
     // units in order, each with its items
-    std::vector<int32_t> first(num_cus + 1, 0), at(n);
-    for (int i = 0; i < n; ++i) ++first[shape.unit_of[i] + 1];
     for (int u = 0; u < num_cus; ++u) first[u + 1] += first[u];
     std::vector<int32_t> next(first.begin(), first.end() - 1);
-    for (int i = 0; i < n; ++i) at[next[shape.unit_of[i]]++] = i;
+    for (int i = 0; i < n; ++i) item_at[next[unit_of[i]]++] = i;
     for (int u = 0; u < num_cus; ++u)
-      for (int k = first[u]; k < first[u + 1]; ++k) add(at[k] / n_hb, at[k] % n_hb, 0, tiles[at[k] / n_hb], u);
+      for (int k = first[u]; k < first[u + 1]; ++k) {
+        const int b = item_at[k] / n_hb;
+        add(b, item_at[k] - b * n_hb, 0, tiles[b], u);
+      }
   }
-  unit_seg.push_back((int32_t)segs.size());
+  add.finish();
 }
 
 }  // namespace
@@ -315,23 +447,29 @@ int build_host_plan(HostPlan& hp, const omniattn_problem_t& prob, const int32_t*
   hp.num_cus = num_cus;
   hp.seq_lens.assign(seq_lens, seq_lens + prob.batch);
   hp.q_len = q_len;
-  hp.tile = prob.kv_dtype == OMNIATTN_FP8_E4M3 ? kTileFp8 : kTile;
+  const bool fp8 = prob.kv_dtype == OMNIATTN_FP8_E4M3;
+  hp.tile = fp8 ? kTileFp8 : kTile;
   hp.heads_total = prob.num_heads * q_len;
   // Several causal queries: query t keeps [0, S) and the W positions ending at its own token.
   // Over all queries that is [0, S) and (for W > 0) the W + q_len - 1 positions ending at L:
   // tiles are laid out for that union, the kernel masks per query.
   hp.window_union = prob.window > 0 ? (int)std::min<int64_t>((int64_t)prob.window + q_len - 1, INT32_MAX) : 0;
   const size_t elt = prob.out_dtype == OMNIATTN_FP32 ? 4 : 2;
-  std::vector<int32_t> tiles(prob.batch);
-  int64_t sum_tiles = 0;
+  Items items;
+  std::vector<int32_t>& tiles = items.tiles;
+  tiles.resize(prob.batch);
+  items.least = INT_MAX;
   hp.retained_tokens = 0;
   for (int b = 0; b < prob.batch; ++b) {
     int L = seq_lens[b];
     int64_t sink_end = std::min<int64_t>(prob.sink, L);
     int64_t win_lo = std::max<int64_t>((int64_t)L - hp.window_union, 0);
     hp.retained_tokens += (win_lo <= sink_end) ? L : sink_end + (L - win_lo);
-    tiles[b] = tile_layout(L, prob.sink, hp.window_union, hp.tile).count();
-    sum_tiles += tiles[b];
+    // (divisions by constants)
+    tiles[b] = (fp8 ? tile_layout(L, prob.sink, hp.window_union, kTileFp8) : tile_layout(L, prob.sink, hp.window_union, kTile)).count();
+    items.sum += tiles[b];
+    items.most = std::max(items.most, tiles[b]);
+    items.least = std::min(items.least, tiles[b]);
   }
   // (segments are listed sequence-major: the head blocks of one sequence read the same tiles; as
   // neighbours they land on one XCD (see the unit mapping in the kernel) and share its L2)
@@ -340,7 +478,6 @@ int build_host_plan(HostPlan& hp, const omniattn_problem_t& prob, const int32_t*
   // The kernels that this problem can run on.  One block of 32 rows: only the narrow kernel, which does
   // the same work in fewer instructions whatever the lengths (128 sequences of 2176 kept tokens, 16
   // heads: 88 -> 62 us, fp8 94 -> 43 us).
-  const bool fp8 = prob.kv_dtype == OMNIATTN_FP8_E4M3;
   const KernelCost& wide = fp8 ? kWideFp8 : kWideBf16;
   std::vector<const KernelCost*> kernels;
   if (hp.heads_total > kHeadsPerWave) {
@@ -354,19 +491,17 @@ int build_host_plan(HostPlan& hp, const omniattn_problem_t& prob, const int32_t*
     for (const KernelCost* k : kernels)
       if (hp.heads_total <= k->head_block) block = k->head_block;
     hp.head_block = block;
-    hp.segs.clear();
-    hp.unit_seg.assign(1, 0);
+    const int n_hb = blocks_of(block);
+    Writer add(hp, tiles, tiles.size() * n_hb, tiles.size() * n_hb, 0);
+    int unit = 0;
     for (int b = 0; b < prob.batch; ++b)
-      for (int hb = 0; hb < blocks_of(block); ++hb) {
+      for (int hb = 0; hb < n_hb; ++hb) {
         int pieces = std::max(1, std::min(prob.num_splits_hint, tiles[b]));
         pieces = std::max(pieces, (tiles[b] + kMaxSegTiles - 1) / kMaxSegTiles);
-        for (int s = 0; s < pieces; ++s) {
-          int lo = (int)((int64_t)tiles[b] * s / pieces);
-          int hi = (int)((int64_t)tiles[b] * (s + 1) / pieces);
-          hp.segs.push_back({b, hb, lo, hi, -1, (int32_t)hp.unit_seg.size() - 1, 0, tiles[b]});
-          hp.unit_seg.push_back((int32_t)hp.segs.size());
-        }
+        for (int s = 0; s < pieces; ++s)
+          add(b, hb, (int)((int64_t)tiles[b] * s / pieces), (int)((int64_t)tiles[b] * (s + 1) / pieces), unit++);
       }
+    add.finish();
   } else {
     // The kernel with the smallest estimate is taken.  Narrow: few sequences, whose pieces would be short
     // (one sequence of 2176 kept tokens, 128 heads: 69 pieces of one tile and 69 partial rows to merge, or
@@ -376,55 +511,43 @@ int build_host_plan(HostPlan& hp, const omniattn_problem_t& prob, const int32_t*
     const auto most_slots = [&](int head_block) {  // (+ 1: room for alignment)
       return (int)(OMNIATTN_STATIC_SCRATCH_BYTES / ((size_t)head_block * (sizeof(float) + kV * elt) + 1));
     };
+    items.count();
+    // (the one that may be cheapest first: its estimate often rules out the others)
+    auto least_us = [&](const KernelCost* k) { return least_tiles(items, blocks_of(k->head_block), num_cus, *k) * k->tile_us; };
+    const KernelCost* order[3];
+    const int n_kernels = (int)kernels.size();
+    std::copy(kernels.begin(), kernels.end(), order);
+    std::stable_sort(order, order + n_kernels, [&](const KernelCost* a, const KernelCost* b) { return least_us(a) < least_us(b); });
     Shape best;
     KernelCost kernel{};
-    for (const KernelCost* k : kernels) {
-      const int n_hb = blocks_of(k->head_block);
-      Shape s = choose_shape(tiles, n_hb, num_cus, *k, most_slots(k->head_block), best.us);
+    for (int i = 0; i < n_kernels; ++i) {
+      const KernelCost& k = *order[i];
+      Shape s = choose_shape(items, blocks_of(k.head_block), num_cus, k, most_slots(k.head_block), best.us);
       if (s.us >= best.us) continue;
       // (not at the price of a plan that omniattn_decode_static would refuse)
-      if (k != kernels[0] && s.slots > most_slots(k->head_block)) continue;
-      best = std::move(s);
-      kernel = *k;
+      if (&k != kernels[0] && s.slots > most_slots(k.head_block)) continue;
+      best = s;
+      kernel = k;
     }
     // Units filled by tiles alone: a segment that costs as much as several tiles moves the cuts, and now and then
     // (two of 3000 random problems) that makes a few partial rows more than the built-in scratch buffer holds.
     // Then the cuts stay where one tile a segment puts them, if those fit.
     if (best.slots > most_slots(kernel.head_block)) {
       const int n_hb = blocks_of(wide.head_block), n = prob.batch * n_hb;
-      int cap = std::max((int)std::min<int64_t>((sum_tiles * n_hb + n + num_cus - 1) / num_cus, INT32_MAX / 2), 2);
-      for (int i = 0; i < 64 && fill_units(tiles, n_hb, cap, 1, [](int, int, int, int, int) {}) > num_cus; ++i) ++cap;
-      int64_t slots = 0;
-      fill_units(tiles, n_hb, cap, 1, [&](int b, int, int lo, int hi, int) { slots += hi - lo < tiles[b]; });
-      if (slots <= most_slots(wide.head_block)) {
+      int cap = std::max((int)std::min<int64_t>((items.sum * n_hb + n + num_cus - 1) / num_cus, INT32_MAX / 2), 2);
+      Filled f = measure_fill(items, n_hb, cap, 1, num_cus);
+      for (int i = 0; i < 64 && f.units > num_cus; ++i) f = measure_fill(items, n_hb, ++cap, 1, num_cus);
+      if (f.units <= num_cus && f.slots <= most_slots(wide.head_block)) {
         best.size = cap;
         kernel = wide;
         kernel.seg = 1;
       }
     }
     hp.head_block = kernel.head_block;
-    lay_out(best, tiles, blocks_of(hp.head_block), num_cus, kernel, hp.segs, hp.unit_seg);
+    lay_out(best, items, blocks_of(hp.head_block), num_cus, kernel, hp);
   }
   hp.n_hb = blocks_of(hp.head_block);
 
-  // partial slots for every (sequence, head block) cut into more than one segment
-  hp.combine.clear();
-  hp.n_slots = 0;
-  hp.max_splits = 1;
-  size_t i = 0;
-  // segments of one item are consecutive in hp.segs by construction
-  while (i < hp.segs.size()) {
-    size_t j = i + 1;
-    while (j < hp.segs.size() && hp.segs[j].b == hp.segs[i].b && hp.segs[j].hb == hp.segs[i].hb) ++j;
-    int n = (int)(j - i);
-    if (n > 1) {
-      hp.combine.push_back({hp.segs[i].b, hp.segs[i].hb, hp.n_slots, n});
-      for (size_t k = i; k < j; ++k) hp.segs[k].slot = hp.n_slots++;
-      hp.max_splits = std::max(hp.max_splits, n);
-    }
-    i = j;
-  }
-  for (Segment& s : hp.segs) s.L = seq_lens[s.b];
   // workspace: lse of every partial row (fp32), then the partial rows in the output type
   const size_t rows = (size_t)hp.n_slots * hp.head_block;
   hp.part_rows_offset = (rows * sizeof(float) + 255) & ~(size_t)255;
