@@ -853,16 +853,23 @@ hipError_t launch_decode(const DecodeParams& p, int waves, int n_units, hipStrea
   return hipGetLastError();
 }
 
-// Four waves to a row from nine partials on: 69 partials of one sequence 32.8 -> 23.9 us per decode, 9
-// partials of four sequences 15.6 -> 14.4; with 8 or 6 partials of 32 to 40 sequences of 128 heads the
-// rows alone fill the chip and the exchange costs 1 us.
-constexpr int kWideSlots = 8;
+// Four waves to a row where the chain of round trips (four partials each, 0.73 us) is what the merge waits
+// for: from nine partials on, while the rows are few.  69 partials of one sequence 32.8 -> 23.9 us per decode, 9
+// partials of four sequences 15.6 -> 14.4.  Many rows fill the chip by themselves, and every row pays for the
+// exchange.  us with one and with four waves: 896 rows of at most 9 partials 20.3 and 19.5, 1024 of 15 20.9 and
+// 19.8, 1792 of 30 49.9 and 49.3; 1408 of 19 42.5 and 43.4, 2048 of 25 63.6 and 65.2, 7808 of 9 73.8 and 76.9.
+constexpr int kWideSlots = 8, kRowsPerTrip = 450;
+
+static bool merge_wide(int max_slots, int64_t rows) {
+  const int saved = (max_slots + 3) / 4 - (max_slots + 15) / 16;  // round trips
+  return max_slots > kWideSlots && rows <= (int64_t)saved * kRowsPerTrip;
+}
 
 hipError_t launch_combine(const CombineParams& p, int n_items, hipStream_t stream) {
   if (n_items <= 0) return hipSuccess;
   const int rows = p.head_block < p.H ? p.head_block : p.H;
   const dim3 block(256);
-  if (p.max_slots > kWideSlots) {
+  if (merge_wide(p.max_slots, (int64_t)n_items * rows)) {
     const dim3 grid(n_items, rows);
     if (p.out_fp32) hipLaunchKernelGGL((combine_kernel<true, 4>), grid, block, 0, stream, p);
     else hipLaunchKernelGGL((combine_kernel<false, 4>), grid, block, 0, stream, p);

@@ -100,6 +100,18 @@ def test_kernel_for_few_rows_or_few_sequences():
     assert check_plan([20011] * 64, 128, 2048).head_block == 128
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("out_dtype", [None, torch.float32])
+@pytest.mark.parametrize("b", [9, 10, 11, 24])
+def test_merge_of_many_rows(b, out_dtype):
+    """13 partials save three round trips: up to 1350 rows (10 sequences of 128 heads) four waves share each row, more
+    are left to a wave each."""
+    inp = parity.to_device(make_custom(b, 128, [33 + 32 * (i % 13) for i in range(b - 1)] + [13 * 32], 0, 1024, seed=b, q_std=1.0, kv_std=1.0))
+    out, lse, plan = parity.run_gpu(inp, out_dtype=out_dtype, num_splits_hint=13)
+    assert plan.max_splits == 13
+    parity.assert_parity(inp, out, lse, row_rel_l2=1e-2, what=f"{b} sequences of up to 13 partials")
+
+
 def _nan_at(inp, b, position):
     inp.kv_cache[int(inp.page_table[b, position // 128]), position % 128, 100] = float("nan")
 
