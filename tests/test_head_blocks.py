@@ -1,13 +1,17 @@
 """The kernels for blocks of 32, 64 and 128 head rows on the same short, ragged problems: no
 tile, one, two or three tiles (fewer than are requested ahead), ragged ends, windows that open inside a
-tile, several segments per unit, several queries per sequence, rows past the last head."""
+tile, several queries per sequence, rows past the last head; one segment per unit first, then (as the planner
+has them for large batches) several, in blocks that it chooses."""
+import dataclasses
+import random
+
 import pytest
 import torch
 
 import paper_2511_22481_amd as oa
 import parity
 from test_multi_query import _check, _run
-from workloads import make_custom
+from workloads import make_custom, poison_unretained
 from workloads.generate import quantize_fp8_per_token
 
 
@@ -40,6 +44,101 @@ def test_larger_blocks(kv, heads, q_len):
             out, lse, plan = _run(inp, q_len, heads, num_splits_hint=1, out_dtype=out_dtype)
             assert plan.head_block == (64 if kv == "fp8" and heads * q_len <= 64 else 128)
             _check(inp, out, lse, q_len, f"{heads} heads, {sink}/{window}")
+
+
+# (sequences, shortest, longest, sink, window)
+SHORT, MIDDLE, LONG = (500, 1, 200, 16, 96), (150, 1, 1500, 16, 600), (90, 1, 4000, 64, 2048)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kv, heads, q_len, lengths, block", [
+    ("fp8", 33, 1, SHORT, 64), ("fp8", 64, 1, SHORT, 64), ("fp8", 16, 3, SHORT, 64),
+    ("fp8", 65, 1, MIDDLE, 64), ("fp8", 80, 1, MIDDLE, 64), ("fp8", 96, 1, MIDDLE, 64), ("fp8", 128, 1, MIDDLE, 64),
+    ("fp8", 40, 2, MIDDLE, 64), ("fp8", 37, 3, MIDDLE, 64), ("fp8", 160, 1, LONG, 64),
+    ("fp8", 80, 1, SHORT, 128), ("fp8", 128, 1, SHORT, 128), ("fp8", 160, 1, SHORT, 128), ("fp8", 40, 2, SHORT, 128),
+    ("bf16", 80, 1, SHORT, 128), ("bf16", 48, 3, SHORT, 128),
+    ("fp8", 16, 1, SHORT, 32), ("bf16", 16, 1, SHORT, 32), ("bf16", 11, 2, SHORT, 32), ("fp8", 48, 1, MIDDLE, 32),
+    ("fp8", 80, 1, LONG, 32)])
+def test_several_segments_per_unit(kv, heads, q_len, lengths, block):
+    """The planner's own choice of kernel, units that run two to four segments of none, one, two and more tiles, last
+    blocks of a few rows (a second block of 1, 16, 32 of 64, a third of 32), queries that end inside a block."""
+    n, lo, hi, sink, window = lengths
+    rng = random.Random(n)
+    lens = [0 if rng.random() < 0.05 else max(q_len, rng.randint(lo, hi)) for _ in range(n)]
+    inp = parity.to_device(make_custom(n, heads * q_len, lens, sink, window, seed=heads + n, kv_dtype=kv, q_std=0.7, kv_std=0.7))
+    exact, exact_lse, plan = _run(inp, q_len, heads, out_dtype=torch.float32)
+    assert plan.head_block == block and plan.num_segments > plan.num_units
+    assert {0, 1, 2, 3} <= {s["tile_hi"] - s["tile_lo"] for s in plan.segments()}
+    _check(inp, exact, exact_lse, q_len, f"{heads} heads, {lengths}")
+    # bf16 results: the same numbers rounded where no partial rows lie in between
+    out, lse, plan = _run(inp, q_len, heads)
+    assert plan.head_block == block and plan.num_segments > plan.num_units
+    if plan.num_partials == 0:
+        assert torch.equal(exact.to(torch.bfloat16), out) and torch.equal(exact_lse, lse)
+    else:
+        _check(inp, out, lse, q_len, f"{heads} heads, {lengths}, bf16 results")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("heads, q_len", [(128, 1), (60, 2)])
+def test_filled_units_of_64_rows(heads, q_len):
+    """Partial rows and whole ones from the same unit: sequences cut wherever a unit is full."""
+    n, lo, hi, sink, window = LONG
+    rng = random.Random(n)
+    lens = [0 if rng.random() < 0.05 else rng.randint(q_len, hi) for _ in range(n)]
+    inp = parity.to_device(make_custom(n, heads * q_len, lens, sink, window, seed=heads, kv_dtype="fp8", q_std=0.7, kv_std=0.7))
+    out, lse, plan = _run(inp, q_len, heads)
+    assert plan.head_block == 64 and plan.num_segments > plan.num_units and plan.num_segments > plan.num_partials > 256
+    _check(inp, out, lse, q_len, f"{heads} heads")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kv", ["bf16", "fp8"])
+@pytest.mark.parametrize("heads", [16, 64, 128])
+def test_poison_and_page_order_in_every_kernel(kv, heads):
+    """One work unit per sequence and head block, as in test_larger_blocks: what is not kept, and where its pages lie,
+    has no influence."""
+    lens, sink, window = [1000, 77, 400, 2600], 40, 150
+    inp = make_custom(4, heads, lens, sink, window, seed=8, kv_dtype=kv, q_std=1.0, kv_std=1.0, spare_pages=4)
+    perm = torch.randperm(inp.num_pages, generator=torch.Generator().manual_seed(99))
+    table = inp.page_table.clone()
+    table[table >= 0] = perm[inp.page_table[inp.page_table >= 0].long()].to(torch.int32)
+    moved = dataclasses.replace(inp, page_table=table, kv_cache=torch.empty_like(inp.kv_cache), kv_scales=None)
+    moved.kv_cache[perm] = inp.kv_cache
+    if kv == "fp8":
+        moved.kv_scales = torch.empty_like(inp.kv_scales)
+        moved.kv_scales[perm] = inp.kv_scales
+    inp = parity.to_device(inp)
+    out, lse, plan = parity.run_gpu(inp, num_splits_hint=1)
+    assert plan.head_block == {16: 32, 64: 64 if kv == "fp8" else 128, 128: 128}[heads]
+    parity.assert_parity(inp, out, lse, row_rel_l2=1e-2, what=f"{kv}, {heads} heads")
+    keep = [[j < L and (j < sink or j >= L - window) for j in range(-(-L // 128) * 128)] for L in lens]
+    for other in (inp, parity.to_device(moved)):
+        poison_unretained(other, keep)
+        out1, lse1, _ = parity.run_gpu(other, plan=plan)
+        assert torch.equal(out, out1) and torch.equal(lse, lse1)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("heads", [16, 64, 128])
+def test_a_large_product_costs_only_its_own_64_dims(heads):
+    """fp8: the matrix instruction aligns the products of 64 dims to the largest, also the one of 128 dims in
+    the kernel for 32 rows: dim 0 carries a logit of 115 (166 in log2 units), dims 64 .. 127 all that differs.
+    Bound on lse: 18 sums of up to 2^8, each rounded to 2^-17: 1.4e-4 in log2 units, 1e-4 in natural ones (seen:
+    1.2e-5; dims 1 .. 63 in their place lose 1.5e-3)."""
+    inp = make_custom(2, heads, [1024, 987], 0, 4096, seed=7, kv_dtype="fp8", q_std=0.5, kv_std=1.0)
+    inp.q[..., :64] = 0
+    inp.q[..., 128:] = 0
+    inp.q[..., 0] = 200.0
+    rows = inp.kv_cache.float()
+    rows[..., 0] = 448.0
+    inp.kv_cache = rows.to(inp.kv_cache.dtype)
+    inp.kv_scales[...] = 8.0 / 448.0
+    inp = parity.to_device(inp)
+    out, lse, plan = parity.run_gpu(inp, out_dtype=torch.float32, num_splits_hint=1)
+    assert plan.head_block == {16: 32}.get(heads, heads)
+    e = parity.assert_parity(inp, out, lse, row_rel_l2=2e-2, what=f"{heads} heads")
+    assert e["lse_abs"] <= 1e-4, e
 
 
 @pytest.mark.gpu
