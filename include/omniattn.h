@@ -179,8 +179,8 @@ int omniattn_plan_tile_range(const omniattn_plan_t* plan, int32_t b, int32_t til
  * logits and lse carry fp32 accumulation error only; the softmax weights, with the token's
  * scale folded in, are rounded to e4m3 (relative 2^-4 per weight) and out is normalised by
  * the sum of the rounded weights.  A token whose scale is more than 2^10 below the largest
- * scale of its 64-token tile has its value row taken at 2^-10 of that largest scale (its
- * softmax weight counts in full).
+ * scale of its 64-token tile (with blocks of 64 heads: of its half of the tile, 32 tokens)
+ * has its value row taken at 2^-10 of that largest scale (its softmax weight counts in full).
  */
 int omniattn_decode(const omniattn_plan_t* plan, const void* q, const void* kv_cache,
                     const float* kv_scales, const int32_t* page_table, void* out,

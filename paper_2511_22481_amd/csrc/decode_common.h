@@ -77,7 +77,7 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t b) {
   return ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(b >> 32)) << 32) |
          (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)b);
 }
-template <bool NT>  // nt: rows read once (see dma16)
+template <bool NT>  // nt: rows read once per work unit (see dma16), also where several head blocks read them
 __device__ __forceinline__ void load_lds16(uint32_t lds, const uint8_t* base, uint32_t off) {
   const uint64_t b = uniform64((uint64_t)(uintptr_t)base);
   const uint32_t m = __builtin_amdgcn_readfirstlane(lds);

@@ -4,18 +4,19 @@
 // Number formats are those of the kernel for blocks of 128 rows (decode_fp8_kernel.hip): the query in two
 // e4m3 terms, weights in e4m3 with one block exponent per head and 32 tokens, normalised by their
 // rounded sum.  That kernel gives each wave 32 heads of its own: every wave reads all of K and transposes
-// all of V, and one wave per SIMD waits out a softmax that nothing covers; it takes 8.9 K cycles per tile of
-// 64 tokens where its matrix instructions take 3.3 K.  Here the four waves share 64 heads:
+// all of V, and one wave per SIMD waits out a softmax that nothing covers; in the long loop it takes 7.5 K
+// cycles per tile of 64 tokens where its matrix instructions take 3.3 K.  Here the four waves share 64 heads:
 //   S^T  wave (th, hg): 32 tokens x 32 heads, the query (144 registers) as before;
 //   P    the weights meet in LDS, in the operand order of PV;
 //   PV   wave w: output columns 128 w .. of all 64 heads (128 accumulators instead of 256).
 // V is transposed once per tile, K read twice, and the registers this frees let S^T of the next tile
-// run ahead, so the softmax of a tile stands behind matrix instructions that do not wait for it: 3.3 K
-// cycles per tile and 64 heads (6.6 K per 128) against 1.66 K of matrix instructions.  What bounds it is the
-// instruction issue of a lone wave per SIMD: about 290 vector, 100 scalar and 60 LDS instructions a tile at
-// 5 to 6 cycles each; loads switched off the loop takes 3.1 K, without PV 3.3 K, without half of S^T 3.5 K.
-// us per decode, 128 rows unless stated: 32 sequences of 8320 tokens 83 -> 73; 93 mixed 127 -> 124; 64 of
-// 2176 59 -> 51, two queries each 91 -> 75; 128 of 2176, 64 rows 87 -> 56.
+// run ahead, so the softmax of a tile stands behind matrix instructions that do not wait for it: 3.14 K
+// cycles per tile and 64 heads (6.3 K per 128) in the long loop, where its matrix instructions take 1.66 K and
+// LDS is busy for 0.77 K.  What bounds it is the instruction issue of a lone wave per SIMD: 215 vector, 26
+// matrix, 78 scalar and 58 LDS instructions a tile.
+// us per decode with blocks of 128 -> 64 rows, each in its best partition, 128 rows per sequence unless stated: 32
+// sequences of 8320 tokens 83 -> 73; 93 mixed 127 -> 124; 64 of 2176 59 -> 51, two queries each 91 -> 75;
+// 128 of 2176, 64 rows 87 -> 56.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -62,8 +63,8 @@ __host__ __device__ constexpr int swq_main(int r) { return ((r & 3) << 2) | ((r 
 __host__ __device__ constexpr int swq_tail(int r) { return (r >> 1) & 7; }
 
 // Matrix instructions as assembly: only so does their place among the other instructions stay what is
-// written.  Operands by register file: O^T (128 registers), K, V^T and the weights in accumulation
-// registers, S^T and the query (144) in vector registers.  A vector-ALU
+// written.  Operands by register file: O^T (128 registers) and the query's low term (72) in accumulation
+// registers; K, V^T, the weights, S^T and the query's high term in vector registers.  A vector-ALU
 // read of a result needs 19 wait states (settle_*; checked on the generated code).  one, lo: E8M0 scales.
 __device__ __forceinline__ void mfma_s_first(f32x16& s, i32x8 a, i32x8 b) {
   asm volatile("v_mfma_f32_32x32x64_f8f6f4 %0, %1, %2, 0" : "=&v"(s) : "v"(a), "v"(b));
