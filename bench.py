@@ -42,7 +42,7 @@ MEASURED_TRAFFIC = {
                    "sources": ("decode_kernels.hip", "decode_common.h"),
                    "kernel_sha256": "1b77e74abe070e7df8cdf13be4dc5d65368ad82601668dc3b4ddd1cb4b34c3c7"},
     "fp8_b32_128k": {"bytes": 167_095_165 + 16_842_752,
-                     "sources": ("decode_fp8_64_kernel.hip", "decode_common.h"),
+                     "sources": ("decode_mid_kernel.hip", "decode_common.h"),
                      "kernel_sha256": "4540c7aaf671efdfe2f7ff9d53fa4341e6b4779a89c92087263710e574b6b933"},
 }
 CSRC = os.path.join(ROOT, "paper_2511_22481_amd", "csrc")
@@ -58,13 +58,11 @@ def measured_traffic(workload):
     return rec["bytes"] if h.hexdigest() == rec["kernel_sha256"] else None
 
 
-def main_kernel(head_block, fp8):
-    """Name of the kernel that serves blocks of that many head rows."""
-    if head_block == 32:
+def main_kernel(plan):
+    """Name of the kernel that serves the plan's blocks of head rows."""
+    if plan.head_block == 32:
         return "decode_narrow_kernel"
-    if fp8:
-        return "decode_fp8_64_kernel" if head_block == 64 else "decode_fp8_kernel"
-    return "decode_kernel"
+    return "decode_mid_kernel" if plan.head_block // plan.unit_groups == 64 else "decode_kernel"
 
 
 def algorithmic_bytes(retained_tokens, batch, heads, kv_dtype):
@@ -253,7 +251,7 @@ def main():
         },
         "roofline": {
             "bound": "hbm",
-            "kernel": main_kernel(plan.head_block, fp8) + " (main pass; combine excluded)",
+            "kernel": main_kernel(plan) + " (main pass; combine excluded)",
             "achieved": achieved,
             "peak": HBM_PEAK_GBPS,
             "unit": "GB/s",

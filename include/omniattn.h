@@ -130,6 +130,7 @@ int32_t omniattn_plan_max_splits(const omniattn_plan_t* plan);     /* most piece
 int32_t omniattn_plan_num_splits(const omniattn_plan_t* plan);     /* the same number under its other name */
 int32_t omniattn_plan_tile_tokens(const omniattn_plan_t* plan);    /* KV tokens per tile */
 int32_t omniattn_plan_head_block(const omniattn_plan_t* plan);     /* heads per work unit */
+int32_t omniattn_plan_unit_groups(const omniattn_plan_t* plan);    /* work groups that share a unit's heads: 1 or 2 */
 
 /*
  * Copy out the plan's segments, 8 int32 each:

@@ -63,7 +63,7 @@ def load_library():
     lib.omniattn_plan_retained_tokens.restype = ctypes.c_int64
     lib.omniattn_plan_retained_tokens.argtypes = [P]
     for name in ("num_units", "num_segments", "num_partials", "max_splits", "num_splits",
-                 "tile_tokens", "head_block"):
+                 "tile_tokens", "head_block", "unit_groups"):
         f = getattr(lib, "omniattn_plan_" + name)
         f.restype = ctypes.c_int32
         f.argtypes = [P]
@@ -137,6 +137,7 @@ class Plan:
     num_splits = property(lambda self: self._get("num_splits"))
     tile_tokens = property(lambda self: self._get("tile_tokens"))
     head_block = property(lambda self: self._get("head_block"))
+    unit_groups = property(lambda self: self._get("unit_groups"))
 
     def segments(self):
         n = self.num_segments

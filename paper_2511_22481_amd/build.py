@@ -6,7 +6,7 @@ import subprocess
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libomniattn.so")
-SOURCES = ["decode_kernels.hip", "decode_fp8_kernel.hip", "decode_fp8_64_kernel.hip", "decode_narrow_kernel.hip", "append_kernels.hip", "api.cpp", "plan.cpp"]
+SOURCES = ["decode_kernels.hip", "decode_mid_kernel.hip", "decode_narrow_kernel.hip", "append_kernels.hip", "api.cpp", "plan.cpp"]
 HEADERS = ["kernels.h", "plan.h", "decode_common.h", os.path.join("..", "..", "include", "omniattn.h")]
 
 
@@ -71,9 +71,9 @@ def check_generated_code(verbose=False):
     from .check_isa import check
     problems = []
     with tempfile.TemporaryDirectory() as tmp:
-        for src, kernel in (("decode_kernels.hip", "decode_kernel"), ("decode_fp8_kernel.hip", "decode_fp8_kernel"),
-                            ("decode_fp8_64_kernel.hip", "decode_fp8_64_kernel"),
-                            ("decode_narrow_kernel.hip", "decode_narrow_kernel")):
+        for src, kernel, builtins in (("decode_kernels.hip", "decode_kernel", False),
+                                      ("decode_mid_kernel.hip", "decode_mid_kernel", True),
+                                      ("decode_narrow_kernel.hip", "decode_narrow_kernel", False)):
             out = os.path.join(tmp, src + ".s")
             cmd = [hipcc(), "--offload-arch=gfx950", "-O3", "-std=c++20",
                    "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -82,7 +82,7 @@ def check_generated_code(verbose=False):
             res = subprocess.run(cmd, capture_output=True, text=True)
             if res.returncode != 0:
                 raise RuntimeError("hipcc -S failed:\n" + res.stderr[-2000:])
-            problems += check(open(out).read(), kernel)
+            problems += check(open(out).read(), kernel, builtins)
     if problems:
         raise RuntimeError("generated code reads MFMA results too early:\n" + "\n".join(problems[:20]))
     if verbose:

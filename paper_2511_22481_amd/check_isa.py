@@ -45,8 +45,9 @@ def _sregs(text):
     return out
 
 
-def check(asm_text, kernel_filter="decode_kernel"):
-    """Returns a list of violation strings (empty = fine)."""
+def check(asm_text, kernel_filter="decode_kernel", builtins=False):
+    """Returns a list of violation strings (empty = fine).  builtins: the kernel's MFMAs are compiler builtins, whose
+    results the compiler itself waits for (with the exact counts, which are smaller than those here)."""
     problems = []
     # 1. no register spill traffic inside a basic block that runs part of the MFMA stream: a
     #    spill reload waits on the vector-memory counter and would drain the tile prefetch.
@@ -85,6 +86,8 @@ def check(asm_text, kernel_filter="decode_kernel"):
             age[r] += int(rest.strip()) + 1 if op == "s_nop" else 1
         if op.startswith("v_readfirstlane") or op.startswith("v_readlane"):
             age.update((r, 0) for r in _sregs(rest.split(",")[0]))
+    if builtins:
+        return problems
     # 3. MFMA results read too early
     in_kernel = False
     pending = {}  # register -> wait states elapsed since the MFMA that writes it

@@ -81,8 +81,7 @@ int init_device(int dev) {
   std::lock_guard<std::mutex> lock(g_init_mutex);
   if (g_init_done[dev]) return OMNIATTN_OK;
   hipError_t e = init_kernels();
-  if (e == hipSuccess) e = init_fp8_kernel();
-  if (e == hipSuccess) e = init_fp8_64_kernel();
+  if (e == hipSuccess) e = init_mid_kernels();
   if (e == hipSuccess) e = init_narrow_kernels();
   if (e != hipSuccess) return hip_fail(e, "kernel attribute setup");
   // (the caller made `dev` current: the address is that of this device's copy)
@@ -335,6 +334,7 @@ int32_t omniattn_plan_max_splits(const omniattn_plan_t* plan) { return plan ? pl
 int32_t omniattn_plan_num_splits(const omniattn_plan_t* plan) { return omniattn_plan_max_splits(plan); }
 int32_t omniattn_plan_tile_tokens(const omniattn_plan_t* plan) { return plan ? plan->hp.tile : 0; }
 int32_t omniattn_plan_head_block(const omniattn_plan_t* plan) { return plan ? plan->hp.head_block : 0; }
+int32_t omniattn_plan_unit_groups(const omniattn_plan_t* plan) { return plan ? plan->hp.groups : 0; }
 
 int32_t omniattn_plan_get_segments(const omniattn_plan_t* plan, int32_t* buf, int32_t cap) {
   if (!plan || (!buf && cap > 0) || cap < 0) return OMNIATTN_EINVAL;
@@ -409,8 +409,7 @@ int omniattn_decode_timed(const omniattn_plan_t* plan, const void* q, const void
   if (dp.scale_log2 == 0.f) dp.scale_log2 = 1e-30f;
   if (ev_begin) OA_HIP(hipEventRecord((hipEvent_t)ev_begin, stream));
   if (hp.head_block == kHeadsPerWave) OA_HIP(launch_decode_narrow(dp, fp8, (int)hp.unit_seg.size() - 1, stream));
-  else if (fp8 && hp.head_block == kHeadBlockFp8) OA_HIP(launch_decode_fp8_64(dp, (int)hp.unit_seg.size() - 1, stream));
-  else if (fp8) OA_HIP(launch_decode_fp8(dp, (int)hp.unit_seg.size() - 1, stream));
+  else if (hp.head_block / hp.groups == kHeadBlockMid) OA_HIP(launch_decode_mid(dp, fp8, (int)hp.unit_seg.size() - 1, stream));
   else OA_HIP(launch_decode(dp, hp.waves, (int)hp.unit_seg.size() - 1, stream));
   if (ev_main_end) OA_HIP(hipEventRecord((hipEvent_t)ev_main_end, stream));
 

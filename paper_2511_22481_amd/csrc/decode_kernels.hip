@@ -1,7 +1,7 @@
 // gfx950 kernels for sparse MLA decode over the OmniAttn retained set
 // (paper section 3.2.1: softmax(q K_M^T * scale) V_M with M = sinks + recents):
-// the main kernel for a bf16 cache and blocks of 128 head rows (an fp8 cache has its own,
-// decode_fp8_kernel.hip, and so have blocks of 32 rows, decode_narrow_kernel.hip), the combine
+// the main kernel for a bf16 cache and blocks of 128 head rows, one wave's 32 at a time (an fp8 cache and
+// work groups of 64 rows: decode_mid_kernel.hip, of 32: decode_narrow_kernel.hip), the combine
 // kernel and small helpers.
 //
 // Main kernel: one work group per work unit, WAVES waves, one wave per SIMD; each

@@ -47,7 +47,7 @@ constexpr int kLdsNarrowFp8 = kOffScales + kWavesN * kStagesN * kScaleStageN;
 static_assert(kLdsNarrowFp8 <= 160 * 1024, "LDS of one compute unit");
 
 constexpr float kRefSlackN = 64.f;  // see the bf16 kernel: fixed softmax reference with retry
-constexpr int kQLoShiftN = 4;       // see the fp8 kernel: the query's low term is stored 16 times too large
+constexpr int kQLoShiftN = 4;       // see decode_mid_kernel.hip: the query's low term is stored 16 times too large
 
 // LDS layout of a stage: the value part of the rows, then their rope parts; 16-byte chunks XORed with a
 // function of the row, as in the kernels for full head blocks (16 consecutive rows at one chunk index
@@ -225,7 +225,7 @@ __global__ __launch_bounds__(kWavesN * 64, 1) void decode_narrow_kernel(DecodePa
     }
     // The B operand of S^T, 16 heads.  bf16: lane (head n16, q4) holds dims 32 ks + 8 q4 .. + 7, ks = 0..17.
     // fp8: dims 128 ks + 32 q4 .. + 31, ks = 0..4 (ks = 4: q4 >= 2 is past the row and zero), as two
-    // e4m3 terms (see the fp8 kernel).
+    // e4m3 terms (see decode_mid_kernel.hip).
     constexpr int kKS = FP8 ? 5 : kQK / 32;
     bf16x8 qf[FP8 ? 1 : kKS];
     i32x8 qh[FP8 ? kKS : 1], ql[FP8 ? kKS : 1];
@@ -252,7 +252,7 @@ __global__ __launch_bounds__(kWavesN * 64, 1) void decode_narrow_kernel(DecodePa
       }
     }
     if constexpr (FP8) {
-      // split of the query row, see the fp8 kernel: q = 2^e (hi + lo / 16), row maximum in [128, 256)
+      // split of the query row, see decode_mid_kernel.hip: q = 2^e (hi + lo / 16), row maximum in [128, 256)
       uint32_t m = 0;
 #pragma unroll
       for (int ks = 0; ks < kKS; ++ks)
@@ -446,7 +446,7 @@ __global__ __launch_bounds__(kWavesN * 64, 1) void decode_narrow_kernel(DecodePa
           ref = ref_exact == ref_exact ? ref_exact : (m2 == -INFINITY || m2 != m2) ? 0.f : ceilf(m2);
         }
         if constexpr (FP8) {
-          // every token scale of the tile < 2^es; weight scales at least 2^(es - 10) (see the fp8 kernel)
+          // every token scale of the tile < 2^es; weight scales at least 2^(es - 10) (see decode_mid_kernel.hip)
           uint32_t m = __builtin_bit_cast(uint32_t, sc_max) & 0x7fffffffu;
 #define OA_ROW_SHR_MAX(n)                                                                             \
   {                                                                                                   \

@@ -65,14 +65,11 @@ hipError_t launch_append(const AppendParams& p, int batch, hipStream_t stream);
 
 // One-time per-process kernel attribute setup (large dynamic LDS).
 hipError_t init_kernels();
-// bf16 cache.  waves must be 4; grid = number of work units.
+// bf16 cache, blocks of 128 rows.  waves must be 4; grid = number of work units.
 hipError_t launch_decode(const DecodeParams& p, int waves, int n_units, hipStream_t stream);
-// fp8 cache: its own kernel (decode_fp8_kernel.hip), tiles of kTileFp8 tokens.
-hipError_t init_fp8_kernel();
-hipError_t launch_decode_fp8(const DecodeParams& p, int n_units, hipStream_t stream);
-// Blocks of 64 head rows, fp8 cache (decode_fp8_64_kernel.hip).
-hipError_t init_fp8_64_kernel();
-hipError_t launch_decode_fp8_64(const DecodeParams& p, int n_units, hipStream_t stream);
+// Blocks of 64 head rows, bf16 or fp8 cache, or of 128, two work groups to a unit (decode_mid_kernel.hip).
+hipError_t init_mid_kernels();
+hipError_t launch_decode_mid(const DecodeParams& p, bool fp8, int n_units, hipStream_t stream);
 // Blocks of 32 head rows, bf16 or fp8 cache (decode_narrow_kernel.hip).
 hipError_t init_narrow_kernels();
 hipError_t launch_decode_narrow(const DecodeParams& p, bool fp8, int n_units, hipStream_t stream);

@@ -13,29 +13,29 @@ namespace omniattn {
 namespace {
 
 // What a partition costs with one of the kernels (measured on MI355X):
-//   head_block  head rows per work unit;
+//   head_block, groups  head rows per work unit, and work groups that share them;
+//   cus         compute units that a unit takes at a time: its groups run side by side or one after the other;
 //   tile_us  a KV tile in the long loop when all compute units work;
 //   seg      a segment (page-table entries, query block, first tile, last PV, result rows), in tiles;
 //   combine  the second launch that merges partial rows, with the gap in front of it (6 us), in tiles;
 //   slots_per_tile  partial rows of how many slots are written and read back in a tile's time by
 //            the whole chip (131 KB each per 128 rows, both ways, at 5 TB/s).
 struct KernelCost {
-  int head_block;
+  int head_block, groups, cus;
   double tile_us;
   int seg;
   double combine;
   double slots_per_tile;
 };
-// The kernels for blocks of 128 rows: 9 us and 13 us a segment.
-constexpr KernelCost kWideBf16 = {4 * kHeadsPerWave, 1.8, 5, 3.3, 36.0};
-constexpr KernelCost kWideFp8 = {4 * kHeadsPerWave, 3.5, 4, 1.8, 65.0};
-// Blocks of 64 (fp8 cache) and 32 rows: every tile passes through once per block.
-// Over 480 random problems (1 to 700 sequences, 1 to 160 heads, 1 to 7 queries) the estimate for the kernel taken
-// was 0.75 to 1.07 of the time measured in the median, kernel by kernel, and scattered by 7 to 20 % about that;
-// of the 15 problems that got slower than with blocks of 128 rows filled to the brim, none by more than 7 %.
-constexpr KernelCost kMidFp8 = {kHeadBlockFp8, 1.7, 8, 2.4, 65.0};
-constexpr KernelCost kNarrowBf16 = {kHeadsPerWave, 1.4, 4, 4.3, 112.0};
-constexpr KernelCost kNarrowFp8 = {kHeadsPerWave, 1.5, 7, 2.7, 114.0};
+// decode_kernel, 128 rows: 9 us a segment.
+constexpr KernelCost kWideBf16 = {4 * kHeadsPerWave, 1, 1, 1.8, 5, 3.3, 36.0};
+// decode_mid_kernel, 64 rows to a work group: blocks of 64, or two groups to a block of 128, one behind the other: as many
+// units as there are compute units.
+constexpr KernelCost kPairFp8 = {2 * kHeadBlockMid, 2, 1, 3.5, 4, 1.8, 65.0};
+constexpr KernelCost kMidFp8 = {kHeadBlockMid, 1, 1, 1.7, 8, 2.4, 65.0};
+// decode_narrow_kernel, 32 rows: every tile passes through once per block.
+constexpr KernelCost kNarrowBf16 = {kHeadsPerWave, 1, 1, 1.4, 4, 4.3, 112.0};
+constexpr KernelCost kNarrowFp8 = {kHeadsPerWave, 1, 1, 1.5, 7, 2.7, 114.0};
 // Do not leave slivers shorter than this many tiles unless the item itself is shorter.
 constexpr int kMinSegTiles = 2;
 
@@ -480,7 +480,7 @@ int build_host_plan(HostPlan& hp, const omniattn_problem_t& prob, const int32_t*
   // The kernels that this problem can run on.  One block of 32 rows: only the narrow kernel, which does
   // the same work in fewer instructions whatever the lengths (128 sequences of 2176 kept tokens, 16
   // heads: 88 -> 62 us, fp8 94 -> 43 us).
-  const KernelCost& wide = fp8 ? kWideFp8 : kWideBf16;
+  const KernelCost& wide = fp8 ? kPairFp8 : kWideBf16;
   std::vector<const KernelCost*> kernels;
   if (hp.heads_total > kHeadsPerWave) {
     kernels.push_back(&wide);
@@ -489,10 +489,11 @@ int build_host_plan(HostPlan& hp, const omniattn_problem_t& prob, const int32_t*
   kernels.push_back(fp8 ? &kNarrowFp8 : &kNarrowBf16);
   if (prob.num_splits_hint > 0) {
     // forced splits: the smallest block that takes all rows, or the largest
-    int block = kernels[0]->head_block;
+    const KernelCost* kernel = kernels[0];
     for (const KernelCost* k : kernels)
-      if (hp.heads_total <= k->head_block) block = k->head_block;
-    hp.head_block = block;
+      if (hp.heads_total <= k->head_block) kernel = k;
+    const int block = hp.head_block = kernel->head_block;
+    hp.groups = kernel->groups;
     const int n_hb = blocks_of(block);
     Writer add(hp, tiles, tiles.size() * n_hb, tiles.size() * n_hb, 0);
     int unit = 0;
@@ -507,15 +508,14 @@ int build_host_plan(HostPlan& hp, const omniattn_problem_t& prob, const int32_t*
   } else {
     // The kernel with the smallest estimate is taken.  Narrow: few sequences, whose pieces would be short
     // (one sequence of 2176 kept tokens, 128 heads: 69 pieces of one tile and 69 partial rows to merge, or
-    // 4 x 35 pieces of two tiles: 24.1 -> 15.4 us).  64 rows, fp8: most of the rest (32 sequences of 8320
-    // tokens, 128 heads: 83 -> 73 us; 128 of 2176, 64 heads: 87 -> 56).  128 rows: bf16, and fp8 with many short
-    // sequences (256 of 1024 tokens: 76 against 93 us).
+    // 4 x 35 pieces of two tiles: 24.1 -> 15.4 us).  64 rows to a group: fp8 (32 sequences of 8320 tokens, 128 heads:
+    // 83 -> 67 us).  decode_kernel: bf16.
     const auto most_slots = [&](int head_block) {  // (+ 1: room for alignment)
       return (int)(OMNIATTN_STATIC_SCRATCH_BYTES / ((size_t)head_block * (sizeof(float) + kV * elt) + 1));
     };
     items.count();
     // (the one that may be cheapest first: its estimate often rules out the others)
-    auto least_us = [&](const KernelCost* k) { return least_tiles(items, blocks_of(k->head_block), num_cus, *k) * k->tile_us; };
+    auto least_us = [&](const KernelCost* k) { return least_tiles(items, blocks_of(k->head_block), num_cus / k->cus, *k) * k->tile_us; };
     const KernelCost* order[3];
     const int n_kernels = (int)kernels.size();
     std::copy(kernels.begin(), kernels.end(), order);
@@ -524,7 +524,7 @@ int build_host_plan(HostPlan& hp, const omniattn_problem_t& prob, const int32_t*
     KernelCost kernel{};
     for (int i = 0; i < n_kernels; ++i) {
       const KernelCost& k = *order[i];
-      Shape s = choose_shape(items, blocks_of(k.head_block), num_cus, k, most_slots(k.head_block), best.us);
+      Shape s = choose_shape(items, blocks_of(k.head_block), num_cus / k.cus, k, most_slots(k.head_block), best.us);
       if (s.us >= best.us) continue;
       // (not at the price of a plan that omniattn_decode_static would refuse)
       if (&k != kernels[0] && s.slots > most_slots(k.head_block)) continue;
@@ -546,7 +546,8 @@ int build_host_plan(HostPlan& hp, const omniattn_problem_t& prob, const int32_t*
       }
     }
     hp.head_block = kernel.head_block;
-    lay_out(best, items, blocks_of(hp.head_block), num_cus, kernel, hp);
+    hp.groups = kernel.groups;
+    lay_out(best, items, blocks_of(hp.head_block), num_cus / kernel.cus, kernel, hp);
   }
   hp.n_hb = blocks_of(hp.head_block);
 

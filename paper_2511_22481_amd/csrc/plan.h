@@ -28,7 +28,7 @@ constexpr int kQK = OMNIATTN_QK_DIM;
 constexpr int kV = OMNIATTN_V_DIM;
 constexpr int kPage = OMNIATTN_PAGE;
 constexpr int kHeadsPerWave = 32;
-constexpr int kHeadBlockFp8 = 64;    // rows per work unit of decode_fp8_64_kernel
+constexpr int kHeadBlockMid = 64;    // rows per work group of decode_mid_kernel
 constexpr int kMaxSegTiles = 1024;  // tiles per segment (the kernel keeps a table of them in LDS)
 
 struct TileLayout {
@@ -81,7 +81,8 @@ struct HostPlan {
   omniattn_problem_t prob;
   int num_cus = 0;
   int waves = 4;        // waves per work group (one per SIMD)
-  int head_block = 0;   // heads per work unit: 128 (each wave owns 32), 64 (decode_fp8_64_kernel) or 32 (decode_narrow_kernel)
+  int head_block = 0;   // heads per work unit: 128 (decode_kernel, or two work groups of decode_mid_kernel), 64 (decode_mid_kernel) or 32 (decode_narrow_kernel)
+  int groups = 1;       // work groups of a unit, which share its heads
   int n_hb = 0;         // head blocks per sequence
   int tile = kTile;       // KV tokens per tile (kTile, or kTileFp8 for an fp8 cache)
   int q_len = 1;          // queries per sequence
