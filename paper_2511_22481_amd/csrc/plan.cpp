@@ -29,8 +29,11 @@ struct KernelCost {
 };
 // decode_kernel, 128 rows: 9 us a segment.
 constexpr KernelCost kWideBf16 = {4 * kHeadsPerWave, 1, 1, 1.8, 5, 3.3, 36.0};
-// decode_mid_kernel, 64 rows to a work group: blocks of 64, or two groups to a block of 128, one behind the other: as many
-// units as there are compute units.
+// decode_mid_kernel, 64 rows to a work group: blocks of 64, or two groups to a block of 128.  bf16: side by side, so that
+// the second finds the tiles in its XCD's L2 and a sequence needs half the pieces; fp8: one behind the other, as many units
+// as there are compute units.
+constexpr KernelCost kPairBf16 = {2 * kHeadBlockMid, 2, 2, 1.03, 8, 5.0, 20.0};
+constexpr KernelCost kMidBf16 = {kHeadBlockMid, 1, 1, 1.5, 5, 3.5, 58.0};
 constexpr KernelCost kPairFp8 = {2 * kHeadBlockMid, 2, 1, 3.5, 4, 1.8, 65.0};
 constexpr KernelCost kMidFp8 = {kHeadBlockMid, 1, 1, 1.7, 8, 2.4, 65.0};
 // decode_narrow_kernel, 32 rows: every tile passes through once per block.
@@ -484,14 +487,21 @@ int build_host_plan(HostPlan& hp, const omniattn_problem_t& prob, const int32_t*
   std::vector<const KernelCost*> kernels;
   if (hp.heads_total > kHeadsPerWave) {
     kernels.push_back(&wide);
+    // bf16, two groups of 64 rows side by side: up to 256 rows, of which the last block's second half has more than 16.
+    // (More rows: six or eight groups pull every tile through one L2.  384 rows, 64 sequences 144 -> 141 us, 40 82 -> 76;
+    // 512 rows, 64 143 -> 158, 20 64 -> 70.)
+    const int last_rows = (hp.heads_total - 1) % kPairBf16.head_block + 1;
     if (fp8) kernels.push_back(&kMidFp8);
+    else if (hp.heads_total <= kHeadBlockMid) kernels.push_back(&kMidBf16);
+    else if (num_cus >= kPairBf16.cus && hp.heads_total <= 2 * kPairBf16.head_block && last_rows > kHeadBlockMid + 16)
+      kernels.push_back(&kPairBf16);
   }
   kernels.push_back(fp8 ? &kNarrowFp8 : &kNarrowBf16);
   if (prob.num_splits_hint > 0) {
-    // forced splits: the smallest block that takes all rows, or the largest
+    // forced splits: the smallest block that takes all rows, or the largest (bf16: 32 rows, or decode_kernel's 128)
     const KernelCost* kernel = kernels[0];
     for (const KernelCost* k : kernels)
-      if (hp.heads_total <= k->head_block) kernel = k;
+      if (hp.heads_total <= k->head_block && k != &kMidBf16 && k != &kPairBf16) kernel = k;
     const int block = hp.head_block = kernel->head_block;
     hp.groups = kernel->groups;
     const int n_hb = blocks_of(block);
@@ -509,7 +519,10 @@ int build_host_plan(HostPlan& hp, const omniattn_problem_t& prob, const int32_t*
     // The kernel with the smallest estimate is taken.  Narrow: few sequences, whose pieces would be short
     // (one sequence of 2176 kept tokens, 128 heads: 69 pieces of one tile and 69 partial rows to merge, or
     // 4 x 35 pieces of two tiles: 24.1 -> 15.4 us).  64 rows to a group: fp8 (32 sequences of 8320 tokens, 128 heads:
-    // 83 -> 67 us).  decode_kernel: bf16.
+    // 83 -> 67 us), bf16 where decode_kernel would cut sequences into four and more
+    // pieces, or has half a block of rows (64 of 2176, 128 heads 58 -> 53.5; 81 of 650 50 -> 33; 128 of 2176, 64 heads
+    // 88 -> 66).  decode_kernel: long bf16 sequences that fill the units, half the loads (256 of 4256 tokens: 300 against
+    // 318 us).
     const auto most_slots = [&](int head_block) {  // (+ 1: room for alignment)
       return (int)(OMNIATTN_STATIC_SCRATCH_BYTES / ((size_t)head_block * (sizeof(float) + kV * elt) + 1));
     };

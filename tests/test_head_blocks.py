@@ -188,3 +188,57 @@ def test_smaller_blocks_never_cost_the_static_scratch(batch):
                                           max_pages_per_seq=320, num_pages=1 << 16, sink=100, window=4096, softmax_scale=0.1,
                                           kv_dtype=kv, out_dtype=out)
                 assert p.head_block == 128 or p.workspace_bytes <= oa.omniattn_static_scratch_bytes()
+
+
+# Batches for which the planner takes decode_mid_kernel on a bf16 cache: one group of 64 rows, or two that share a block.
+TILE_EDGES = [1, 31, 32, 33, 63, 64, 65, 95, 96, 97, 127, 128, 129, 160, 161, 192, 250, 333, 500, 650]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("heads, q_len, groups", [(128, 1, 2), (100, 1, 2), (64, 2, 2), (110, 2, 2), (85, 3, 2), (64, 1, 1), (33, 1, 1), (20, 2, 1)])
+def test_groups_of_64_rows_over_a_bf16_cache(heads, q_len, groups):
+    """Every tile count from none to twenty (fewer than the four stages, each stage reused), windows that open inside a
+    tile, a second group of a few rows, queries that end inside a group; what is not kept has no influence."""
+    lens = [0] + [max(L, q_len) for L in TILE_EDGES] * (4 if groups == 2 else 10)
+    inp = make_custom(len(lens), heads * q_len, lens, 40, 600, seed=heads, kv_dtype="bf16", q_std=0.7, kv_std=0.7)
+    inp = parity.to_device(inp)
+    out, lse, plan = _run(inp, q_len, heads, out_dtype=torch.float32)
+    assert plan.unit_groups == groups and plan.head_block == 64 * groups
+    _check(inp, out, lse, q_len, f"{heads} heads, {q_len} queries")
+    keep = [[j < L and (j < 40 or j >= L - 600 - (q_len - 1)) for j in range(-(-L // 128) * 128)] for L in lens]
+    poison_unretained(inp, keep)
+    again, lse2, _ = _run(inp, q_len, heads, out_dtype=torch.float32)
+    assert torch.equal(out, again) and torch.equal(lse, lse2)
+    out16, _, _ = _run(inp, q_len, heads)
+    if plan.num_partials == 0:
+        assert torch.equal(out.to(torch.bfloat16), out16)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("heads", [64, 128])
+def test_reference_retry_with_groups_of_64_rows(heads):
+    """As test_reference_retry_in_every_kernel, in a batch that runs on decode_mid_kernel with a bf16 cache."""
+    B, L = 81, 640
+    inp = make_custom(B, heads, [L] * B, 0, 4096, seed=4, kv_dtype="bf16", q_std=0.0, kv_std=0.0)
+    inp.q.zero_()
+    inp.q[:, :, 512:] = 1.0
+    rows = torch.zeros(L, 576)
+    rows[:, 512:] = torch.linspace(0.0, 20.0, L)[:, None]
+    rows[:, :512] = 0.25 * (torch.arange(L) % 5)[:, None]
+    for b in range(0, B, 2):                               # (every other sequence runs twice)
+        for pg in range(L // 128):
+            inp.kv_cache[int(inp.page_table[b, pg])] = rows[pg * 128:(pg + 1) * 128].to(inp.kv_cache.dtype)
+    inp = parity.to_device(inp)
+    out, lse, plan = parity.run_gpu(inp, out_dtype=torch.float32)
+    assert plan.head_block // plan.unit_groups == 64
+    assert torch.isfinite(out).all() and torch.isfinite(lse).all()
+    parity.assert_parity(inp, out, lse, what=f"retry, {heads} heads")
+
+
+def test_two_groups_to_a_block_where_a_sequence_would_be_cut_more():
+    def plan(batch, heads, window, q_len=1):
+        return oa.omniattn_plan_host([32768] * batch, batch=batch, num_heads=heads, max_pages_per_seq=256, num_pages=1 << 16,
+                                     sink=128, window=window, softmax_scale=0.1, q_len=q_len)
+    assert [plan(64, h, 2048).unit_groups for h in (64, 96, 128)] == [1, 2, 2] and plan(64, 128, 2048, 2).unit_groups == 2
+    assert plan(64, 128, 2048).num_units == 128 and plan(64, 128, 2048, 2).num_partials == 0
+    assert plan(256, 128, 4096).unit_groups == 1 and plan(64, 128, 2048, 4).unit_groups == 1
