@@ -10,11 +10,12 @@
 //         instructions, K from the LDS tile, Q of 16 heads in registers);
 //   P     the softmax weights of the tile meet in LDS (2 KB), already in the operand order of
 //   PV    where wave w accumulates output columns 128 w .. 128 w + 127 of all 32 heads.
-// That leaves the loop bound by the cache rows it streams, 1.45 us per tile and compute unit (6.5 TB/s
-// chip-wide; the kernels for full head blocks take 2.1 us bf16, 4.2 us fp8 at 16 heads), four LDS stages of 36,864 bytes (32
+// That leaves the loop bound by the cache rows it streams, 1.4 us per tile and compute unit (6.7 TB/s
+// chip-wide; a kernel for full head blocks takes 2.1 us bf16 at 16 heads).  Four LDS stages of 36,864 bytes (32
 // bf16 or 64 fp8 tokens) are filled by direct global->LDS loads, three tiles ahead of the one in
-// use, with two barriers per tile.  The matrix and vector work of a tile takes about a third of the
-// time its bytes need, so it is written with compiler builtins and not scheduled by hand.
+// use, with two barriers per tile.  It is written with compiler builtins; bf16: all K fragments of a tile, and its V
+// fragments, are requested ahead of the matrix instructions that use them (128 sequences of 2176 tokens, 16 heads: 60.7 -> 58.4
+// us; one sequence of 128 heads 15.0 -> 14.6; four of 16 heads 10.7 -> 10.4).
 // us per decode, 128 sequences of 2176 kept tokens: 16 heads bf16 88 -> 62, fp8 94 -> 43; 64 heads fp8
 // 102 -> 64 (two blocks; bf16 stays with full head blocks); one sequence of 128 heads 26 -> 15.4.
 // Softmax reference (fixed per segment, second run if a logit leaves its range), weight formats,
@@ -22,6 +23,8 @@
 // each 64 of them to their largest, as the one of 64 dims does: the logits carry the same error.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "decode_common.h"
 
@@ -358,10 +361,47 @@ __global__ __launch_bounds__(kWavesN * 64, 1) void decode_narrow_kernel(DecodePa
         wait_tile(it);
         // tile it is visible; every wave is done with tile it - 1 (its stage) and with its weights
         __syncthreads();
-        if (it + 3 < n_tiles) issue_tile(it + 3);
         const uint32_t st = stage_base(it);
         const int pos0 = tile_pos(it);
         const bool full = tile_full(pos0);
+
+        // ---- bf16: K fragments, all of them ahead of the first matrix instruction; left to itself the compiler reads,
+        // waits and multiplies one by one.  The next tile's requests go out while they arrive.  (fp8: 2 % slower so.) ----
+        bf16x8 kf[FP8 ? 1 : kKS];
+        if constexpr (!FP8) {
+#pragma unroll
+          for (int ks = 0; ks < kKS; ++ks)
+            kf[ks] = *LDS_PTR(bf16x8, st + (ks < 16 ? (am[0] ^ ((ks & 3) << 6)) + (ks >> 2) * 256 : at[0] ^ ((ks & 1) << 6)));
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if (it + 3 < n_tiles) issue_tile(it + 3);
+        // V^T fragments of the wave's 128 columns; bf16: also ahead of the weights (a tile that is not kept whole: again,
+        // once its cleared rows are visible)
+        std::conditional_t<FP8, i32x8, bf16x8> v[FP8 ? 4 : 8];
+        auto load_v = [&]() {
+          if constexpr (FP8) {
+#pragma unroll
+            for (int cb = 0; cb < 4; ++cb) {
+              const int cg = 4 * wave + cb;  // its 32 columns are chunks 2 cg, 2 cg + 1 of a row
+              const uint32_t a = st + (vb[0] ^ ((cg & 7) << 5)) + (cg >> 3) * 256;
+#pragma unroll
+              for (int pt = 0; pt < 4; ++pt) {
+                const i32x2 t = __builtin_amdgcn_ds_read_tr8_b64_v2i32(LDS_PTR(i32x2, a + pt * 16 * Y::kMain));
+                v[cb][2 * pt] = t[0];
+                v[cb][2 * pt + 1] = t[1];
+              }
+            }
+          } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+              const uint32_t a = st + (j >> 2) * 16 * Y::kMain + wave * 256, x = (j & 3) << 6;
+              const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, a + (vb[0] ^ x)));
+              const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, a + (vb[1] ^ x)));
+              v[j] = __builtin_bit_cast(bf16x8, s16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]});
+            }
+          }
+        };
+        __builtin_amdgcn_sched_barrier(0);
 
         // ---- S^T ----
         f32x4 s[kGroups];
@@ -383,12 +423,11 @@ __global__ __launch_bounds__(kWavesN * 64, 1) void decode_narrow_kernel(DecodePa
           s[0] = f32x4{0, 0, 0, 0};
 #pragma unroll
           for (int ks = 0; ks < kKS; ks += 2) {
-            const uint32_t a0 = st + (ks < 16 ? (am[0] ^ ((ks & 3) << 6)) + (ks >> 2) * 256 : at[0]);
-            const uint32_t a1 = st + (ks < 16 ? (am[0] ^ (((ks + 1) & 3) << 6)) + (ks >> 2) * 256 : at[0] ^ 64u);
-            s[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*LDS_PTR(bf16x8, a0), qf[ks], s[0], 0, 0, 0);
-            s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*LDS_PTR(bf16x8, a1), qf[ks + 1], s1, 0, 0, 0);
+            s[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[ks], qf[ks], s[0], 0, 0, 0);
+            s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[ks + 1], qf[ks + 1], s1, 0, 0, 0);
           }
           s[0] += s1;
+          load_v();
         }
         // element i of group a: token tok0 + 16 a + i of the tile
         const int tok0 = (FP8 ? 32 : 16) * th + 4 * q4;
@@ -505,35 +544,18 @@ __global__ __launch_bounds__(kWavesN * 64, 1) void decode_narrow_kernel(DecodePa
         __syncthreads();  // the tile's weights are visible (and its cleared rows)
 
         // ---- PV: columns 128 wave .. + 127 of all 32 heads ----
+        if (FP8 || !full) load_v();
         if constexpr (FP8) {
           const i32x4 p0 = *LDS_PTR(i32x4, p_read), p1 = *LDS_PTR(i32x4, p_read + 16);
           const i32x8 pf = {p0[0], p0[1], p0[2], p0[3], p1[0], p1[1], p1[2], p1[3]};
           const int sb = *LDS_PTR(int, lds_kk + (g * kHeadsPerWave + n32) * 4);  // (half g from lane (head, g))
 #pragma unroll
-          for (int cb = 0; cb < 4; ++cb) {
-            const int cg = 4 * wave + cb;  // its 32 columns are chunks 2 cg, 2 cg + 1 of a row
-            const uint32_t a = st + (vb[0] ^ ((cg & 7) << 5)) + (cg >> 3) * 256;
-            i32x8 v;
-#pragma unroll
-            for (int pt = 0; pt < 4; ++pt) {
-              const i32x2 t = __builtin_amdgcn_ds_read_tr8_b64_v2i32(LDS_PTR(i32x2, a + pt * 16 * Y::kMain));
-              v[2 * pt] = t[0];
-              v[2 * pt + 1] = t[1];
-            }
-            acc[cb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(v, pf, acc[cb], 0, 0, 0, 127, 0, sb);
-          }
+          for (int cb = 0; cb < 4; ++cb)
+            acc[cb] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(v[cb], pf, acc[cb], 0, 0, 0, 127, 0, sb);
         } else {
           const bf16x8 pf0 = *LDS_PTR(bf16x8, p_read), pf1 = *LDS_PTR(bf16x8, p_read + 32);
 #pragma unroll
-          for (int t2 = 0; t2 < 2; ++t2)
-#pragma unroll
-            for (int cb = 0; cb < 4; ++cb) {
-              const uint32_t a = st + t2 * 16 * Y::kMain + wave * 256;
-              const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, a + (vb[0] ^ (cb << 6))));
-              const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(s16x4, a + (vb[1] ^ (cb << 6))));
-              const bf16x8 v = __builtin_bit_cast(bf16x8, s16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]});
-              acc[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, t2 ? pf1 : pf0, acc[cb], 0, 0, 0);
-            }
+          for (int j = 0; j < 8; ++j) acc[j & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v[j], j < 4 ? pf0 : pf1, acc[j & 3], 0, 0, 0);
         }
       }
 
