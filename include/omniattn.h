@@ -114,10 +114,18 @@ typedef struct omniattn_plan_s omniattn_plan_t; /* opaque, library-owned */
  */
 int omniattn_plan(omniattn_plan_t** plan_out, const omniattn_problem_t* prob,
                   const int32_t* seq_lens_host, void* hip_stream);
+/*
+ * omniattn_plan with the metadata's device copy in `buffer` (device memory of the caller's, 16-byte aligned) if it holds
+ * them, else in memory of the plan's own, as also after an update that outgrows it.  The buffer stays the caller's: it
+ * has to live until the decodes of this plan are done, and destroying the plan then neither frees device memory nor
+ * waits for any.
+ */
+int omniattn_plan_in(omniattn_plan_t** plan_out, const omniattn_problem_t* prob, const int32_t* seq_lens_host,
+                     void* buffer, size_t buffer_bytes, void* hip_stream);
 int omniattn_plan_update(omniattn_plan_t* plan, const int32_t* seq_lens_host, void* hip_stream);
 int omniattn_plan_host(omniattn_plan_t** plan_out, const omniattn_problem_t* prob,
                        const int32_t* seq_lens_host, int32_t num_cus);
-/* NULL is allowed.  Frees the plan's device metadata, which waits for the work of the device. */
+/* NULL is allowed.  Frees the plan's own device metadata, which waits for the work of the device. */
 void omniattn_plan_destroy(omniattn_plan_t* plan);
 
 /* Introspection (host only, cheap). */

@@ -52,6 +52,8 @@ def load_library():
     P = ctypes.c_void_p
     lib.omniattn_plan.restype = ctypes.c_int
     lib.omniattn_plan.argtypes = [ctypes.POINTER(P), ctypes.POINTER(Problem), P, P]
+    lib.omniattn_plan_in.restype = ctypes.c_int
+    lib.omniattn_plan_in.argtypes = [ctypes.POINTER(P), ctypes.POINTER(Problem), P, P, ctypes.c_size_t, P]
     lib.omniattn_plan_update.restype = ctypes.c_int
     lib.omniattn_plan_update.argtypes = [P, P, P]
     lib.omniattn_plan_host.restype = ctypes.c_int
@@ -110,6 +112,8 @@ class Plan:
     def __init__(self, handle, problem):
         self._h = handle
         self.problem = problem
+        self._buffer = None   # a torch tensor that may hold the plan's device copy (see decode), and its stream
+        self._buffer_stream = None
         # kept on the object: at interpreter shutdown module globals may be gone before __del__ runs
         self._destroy = load_library().omniattn_plan_destroy
 
@@ -210,6 +214,8 @@ def omniattn_plan_update(plan, seq_lens, stream=None):
         lens, address = seq_lens, ctypes.addressof(seq_lens)
     else:
         lens, address = _lens_array(seq_lens)
+    if plan._buffer is not None:
+        _stream_of(plan, stream)
     _check(load_library().omniattn_plan_update(plan.handle, address, _stream_handle(stream)))
     return plan
 
@@ -223,6 +229,16 @@ def omniattn_plan_host(seq_lens, num_cus=256, **problem_fields):
     return Plan(h, prob)
 
 
+def _stream_of(plan, stream):
+    """Handle of the stream that a call with this plan runs on.  A plan's copy in a torch tensor belongs to the stream
+    that it was made on: the allocator is told of any other, so that it waits for it before it gives the memory away."""
+    handle = _current_stream() if stream is None else stream.cuda_stream
+    if plan._buffer is not None and handle != plan._buffer_stream:
+        import torch
+        plan._buffer.record_stream(torch.cuda.current_stream() if stream is None else stream)
+    return handle
+
+
 def _ptr(t):
     return t.data_ptr() if t is not None else None
 
@@ -234,7 +250,7 @@ def omniattn_decode(plan, q, kv_cache, kv_scales, page_table, out, lse, workspac
     ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
     _check(load_library().omniattn_decode(
         plan.handle, _ptr(q), _ptr(kv_cache), _ptr(kv_scales), _ptr(page_table), _ptr(out),
-        _ptr(lse), _ptr(workspace), ws_bytes, _current_stream() if stream is None else stream.cuda_stream))
+        _ptr(lse), _ptr(workspace), ws_bytes, _stream_of(plan, stream)))
 
 
 def omniattn_decode_timed(plan, q, kv_cache, kv_scales, page_table, out, lse, workspace, stream,
@@ -243,7 +259,7 @@ def omniattn_decode_timed(plan, q, kv_cache, kv_scales, page_table, out, lse, wo
     ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
     _check(load_library().omniattn_decode_timed(
         plan.handle, _ptr(q), _ptr(kv_cache), _ptr(kv_scales), _ptr(page_table), _ptr(out),
-        _ptr(lse), _ptr(workspace), ws_bytes, ctypes.c_void_p(stream.cuda_stream),
+        _ptr(lse), _ptr(workspace), ws_bytes, ctypes.c_void_p(_stream_of(plan, stream)),
         ev_begin, ev_main_end, ev_end))
 
 
@@ -252,7 +268,7 @@ def omniattn_decode_static(plan, q, kv_cache, kv_scales, page_table, out, lse, s
     device buffer (omniattn_static_scratch_bytes() bytes); nothing is allocated."""
     _check(load_library().omniattn_decode_static(
         plan.handle, _ptr(q), _ptr(kv_cache), _ptr(kv_scales), _ptr(page_table), _ptr(out),
-        _ptr(lse), _current_stream() if stream is None else stream.cuda_stream))
+        _ptr(lse), _stream_of(plan, stream)))
 
 
 def omniattn_static_scratch_bytes():
@@ -294,6 +310,9 @@ def omniattn_ring_append(seq_lens, new_rows, new_scales, seq_pages, kv_cache, kv
         _ptr(kv_cache), _ptr(kv_scales), _ptr(page_table), _current_stream() if stream is None else stream.cuda_stream))
 
 
+_PLAN_BYTES = 1 << 16   # most plans need 10 to 40 KB
+
+
 def decode(q, kv_cache, kv_scales, page_table, seq_lens_host, sink, window, softmax_scale,
            out_dtype=None, num_splits_hint=0, plan=None):
     """Convenience wrapper: plan (unless given), allocate outputs/workspace with torch,
@@ -308,12 +327,24 @@ def decode(q, kv_cache, kv_scales, page_table, seq_lens_host, sink, window, soft
     fp8 = kv_cache.dtype == torch.float8_e4m3fn
     odt = torch.bfloat16 if out_dtype is None else out_dtype
     if plan is None:
-        plan = omniattn_plan(seq_lens_host, batch=B, num_heads=H,
-                             max_pages_per_seq=page_table.shape[1], num_pages=kv_cache.shape[0],
-                             sink=sink, window=window, softmax_scale=softmax_scale,
-                             kv_dtype=FP8_E4M3 if fp8 else BF16,
-                             out_dtype=FP32 if odt == torch.float32 else BF16,
-                             num_splits_hint=num_splits_hint, q_len=q_len)
+        prob = _problem(batch=B, num_heads=H, max_pages_per_seq=page_table.shape[1], num_pages=kv_cache.shape[0],
+                        sink=sink, window=window, softmax_scale=softmax_scale,
+                        kv_dtype=FP8_E4M3 if fp8 else BF16,
+                        out_dtype=FP32 if odt == torch.float32 else BF16,
+                        num_splits_hint=num_splits_hint, q_len=q_len)
+        # The plan's device copy goes to a torch tensor: a plan with device memory of its own is mostly gone again when
+        # this call's results are, and freeing that waits for the whole decode (47 us a call, 28 without).  Not while
+        # the stream captures: a graph reads the plan's buffers at every replay, so what can't be made then is refused.
+        buffer = None
+        if q.device.index == torch._C._cuda_getDevice() and not torch.cuda.is_current_stream_capturing():
+            buffer = torch.empty(_PLAN_BYTES, dtype=torch.uint8, device=q.device)
+        h = ctypes.c_void_p()
+        lens, address = _lens_array(seq_lens_host)
+        stream = _current_stream()
+        _check(load_library().omniattn_plan_in(ctypes.byref(h), ctypes.byref(prob), address, _ptr(buffer),
+                                               _PLAN_BYTES if buffer is not None else 0, stream))
+        plan = Plan(h, prob)
+        plan._buffer, plan._buffer_stream = buffer, stream
     out = torch.empty(lead + (512,), dtype=odt, device=q.device)
     lse = torch.empty(lead, dtype=torch.float32, device=q.device)
     ws = None

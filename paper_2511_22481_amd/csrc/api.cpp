@@ -22,15 +22,17 @@ struct HostBuffers {
   uint8_t* h[2] = {nullptr, nullptr};
   hipEvent_t done[2] = {nullptr, nullptr};
   bool busy[2] = {false, false};
+  hipStream_t stream[2] = {nullptr, nullptr};  // of that copy (compared, not used)
   int next = 0;
   size_t cap = 0;         // 0 until all of the above are made
   bool in_graph = false;  // a captured copy reads them at every replay
 };
-// Device copy of a plan's metadata: one allocation holding the unit headers, the segments and the combine
-// items, filled by one asynchronous copy from a host buffer of the same layout.
+// Device copy of a plan's metadata: one allocation (or a buffer of the caller's) holding the unit headers, the segments
+// and the combine items, filled by one asynchronous copy from a host buffer of the same layout.
 struct MetaBuffers {
   uint8_t* d = nullptr;
   size_t cap = 0;
+  bool callers = false;
   HostBuffers host;
 };
 }  // namespace
@@ -107,7 +109,7 @@ void free_host(HostBuffers& b) {
 
 // Host buffers of destroyed plans, kept for the next one: a program that plans anew for each call paid two
 // pinned allocations, two events and their release each time (a plan made and destroyed: 70 us, now 16; with
-// the decode of 3 sequences of 48 heads: 119, now 46).  At most kSpare per device, of at most kSpareBytes
+// the decode of 3 sequences of 48 heads: 119, now 46, and 28 with the device copy in a buffer of the caller's).  At most kSpare per device, of at most kSpareBytes
 // each; the rest is freed at once.  The device copy is not kept, though that would save 7 us more: kernels of
 // any stream, and graphs, may still read a destroyed plan's copy.  Its release waits for them; a wait of
 // our own (hipDeviceSynchronize) breaks a capture under way on any thread.
@@ -116,11 +118,19 @@ std::mutex g_spare_mutex;
 HostBuffers g_spare[kMaxDevices][kSpare];
 size_t g_spares[kMaxDevices] = {};
 
-bool take_spare(int dev, size_t bytes, HostBuffers& b) {
+// A buffer whose last copy is still under way is taken by plans of the same stream only: they would wait for what
+// their own stream does anyway, two plans back.  (A plan whose device copy is the caller's is destroyed without a wait.)
+bool take_spare(int dev, size_t bytes, hipStream_t stream, HostBuffers& b) {
   std::lock_guard<std::mutex> lock(g_spare_mutex);
   size_t& n = g_spares[dev];
+  auto ready = [&](const HostBuffers& s) {
+    const int k = s.next;
+    if (!s.busy[k] || s.stream[k] == stream || hipEventQuery(s.done[k]) == hipSuccess) return true;
+    (void)hipGetLastError();
+    return false;
+  };
   for (size_t i = 0; i < n; ++i)
-    if (g_spare[dev][i].cap >= bytes) {
+    if (g_spare[dev][i].cap >= bytes && ready(g_spare[dev][i])) {
       b = g_spare[dev][i];
       g_spare[dev][i] = g_spare[dev][--n];
       return true;
@@ -129,9 +139,11 @@ bool take_spare(int dev, size_t bytes, HostBuffers& b) {
 }
 
 void free_device(omniattn_plan_s* pl) {
-  const bool waited = !pl->meta.d || hipFree(pl->meta.d) == hipSuccess;
+  const bool waited = !pl->meta.d || pl->meta.callers || hipFree(pl->meta.d) == hipSuccess;
+  const bool callers = pl->meta.callers;
   pl->meta.d = nullptr;
   pl->meta.cap = 0;
+  pl->meta.callers = false;
   HostBuffers& b = pl->meta.host;
   const int dev = pl->device;
   if (waited && b.cap > 0 && b.cap <= kSpareBytes && !b.in_graph && dev >= 0 && dev < kMaxDevices) {
@@ -144,6 +156,8 @@ void free_device(omniattn_plan_s* pl) {
         if (kept.cap < b.cap) std::swap(kept, b);
     }
   }
+  for (int i = 0; callers && i < 2; ++i)  // (nothing has waited for their copies)
+    if (b.busy[i] && b.done[i]) (void)hipEventSynchronize(b.done[i]);
   free_host(b);
 }
 
@@ -183,23 +197,24 @@ int upload_plan(omniattn_plan_s* pl, hipStream_t stream) {
   const size_t bytes = pl->off_combine + align16(n_items * sizeof(CombineItem));
   MetaBuffers& m = pl->meta;
   HostBuffers& hb = m.host;
+  if (hb.cap < bytes && !(!hb.h[0] && take_spare(pl->device, bytes, stream, hb))) {
+    const size_t cap = std::max<size_t>(bytes + bytes / 2 + 4096, 64 * 1024);  // (most plans need 10 to 40 KB)
+    hb.cap = 0;
+    for (int i = 0; i < 2; ++i) {
+      if (hb.h[i]) (void)hipHostFree(hb.h[i]);
+      hb.h[i] = nullptr;
+      hb.busy[i] = false;
+      OA_HIP(hipHostMalloc((void**)&hb.h[i], cap, hipHostMallocDefault));
+      if (!hb.done[i]) OA_HIP(hipEventCreateWithFlags(&hb.done[i], hipEventDisableTiming));
+    }
+    hb.cap = cap;
+  }
   if (bytes > m.cap) {
     // (rare: a plan larger than any before it; freeing waits for the device)
-    if (m.d) (void)hipFree(m.d);
+    if (m.d && !m.callers) (void)hipFree(m.d);
     m.d = nullptr;
     m.cap = 0;
-    if (hb.cap < bytes && !(!hb.h[0] && take_spare(pl->device, bytes, hb))) {
-      const size_t cap = std::max<size_t>(bytes + bytes / 2 + 4096, 64 * 1024);  // (most plans need 10 to 40 KB)
-      hb.cap = 0;
-      for (int i = 0; i < 2; ++i) {
-        if (hb.h[i]) (void)hipHostFree(hb.h[i]);
-        hb.h[i] = nullptr;
-        hb.busy[i] = false;
-        OA_HIP(hipHostMalloc((void**)&hb.h[i], cap, hipHostMallocDefault));
-        if (!hb.done[i]) OA_HIP(hipEventCreateWithFlags(&hb.done[i], hipEventDisableTiming));
-      }
-      hb.cap = cap;
-    }
+    m.callers = false;
     OA_HIP(hipMalloc((void**)&m.d, hb.cap));
     m.cap = hb.cap;
   }
@@ -239,6 +254,7 @@ int upload_plan(omniattn_plan_s* pl, hipStream_t stream) {
   OA_HIP(launch_copy16(m.d, h, bytes, stream));
   OA_HIP(hipEventRecord(hb.done[hi], stream));
   hb.busy[hi] = true;
+  hb.stream[hi] = stream;
   return OMNIATTN_OK;
 }
 
@@ -256,9 +272,15 @@ int omniattn_plan_host(omniattn_plan_t** plan_out, const omniattn_problem_t* pro
 
 int omniattn_plan(omniattn_plan_t** plan_out, const omniattn_problem_t* prob,
                   const int32_t* seq_lens_host, void* hip_stream) {
+  return omniattn_plan_in(plan_out, prob, seq_lens_host, nullptr, 0, hip_stream);
+}
+
+int omniattn_plan_in(omniattn_plan_t** plan_out, const omniattn_problem_t* prob, const int32_t* seq_lens_host,
+                     void* buffer, size_t buffer_bytes, void* hip_stream) {
   if (!plan_out) return OMNIATTN_EINVAL;
   *plan_out = nullptr;
   if (!prob || !seq_lens_host) return OMNIATTN_EINVAL;
+  if (((uintptr_t)buffer & 15) != 0) return OMNIATTN_EINVAL;
   int dev = 0;
   OA_HIP(hipGetDevice(&dev));
   int cus = 0;
@@ -271,6 +293,11 @@ int omniattn_plan(omniattn_plan_t** plan_out, const omniattn_problem_t* prob,
   if (rc != OMNIATTN_OK) return rc;
   pl->device = dev;
   pl->xcds = g_xcds[dev] > 0 ? g_xcds[dev] : 1;
+  if (buffer && buffer_bytes > 0) {
+    pl->meta.d = (uint8_t*)buffer;
+    pl->meta.cap = buffer_bytes & ~(size_t)15;
+    pl->meta.callers = true;
+  }
   try {
     rc = upload_plan(pl, (hipStream_t)hip_stream);
   } catch (const std::bad_alloc&) {

@@ -100,3 +100,58 @@ def test_making_a_plan_waits_for_no_stream():
     still_running = not done.query()
     torch.cuda.synchronize()
     assert still_running and plan.num_units > 0
+
+
+def _busy(stream, n=60):
+    a = torch.randn(8192, 8192, device="cuda", dtype=torch.bfloat16)
+    torch.cuda.synchronize()
+    done = torch.cuda.Event()
+    with torch.cuda.stream(stream):
+        for _ in range(n):                               # 1 ms each
+            a @ a
+        done.record()
+    return done
+
+
+@pytest.mark.gpu
+def test_a_one_call_decode_waits_for_nothing():
+    """Its plan is gone when it returns, and with it went device memory whose release waits for all streams."""
+    inp = parity.to_device(make_custom(3, 48, [700, 90, 2000], 64, 512, seed=1, q_std=0.7, kv_std=0.7))
+    want = parity.run_gpu(inp)
+    _spare_buffers()
+    done = _busy(torch.cuda.Stream())
+    args = (inp.q, inp.kv_cache, inp.kv_scales, inp.page_table, inp.seq_lens_host, inp.sink, inp.window, inp.softmax_scale)
+    got = [oa.decode(*args)[:2] for _ in range(5)]
+    still_running = not done.query()
+    torch.cuda.synchronize()
+    assert still_running
+    for out, lse in got:
+        assert torch.equal(out, want[0]) and torch.equal(lse, want[1])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("big", [False, True])
+def test_plan_of_a_one_call_decode_on_another_stream(big):
+    """The plan that the call returns is used on a second, busy stream and dropped at once: its device copy stays whole
+    until that decode is done, whatever is allocated in the meantime.  (big: a plan that outgrows the wrapper's buffer.)"""
+    n = 2000 if big else 5
+    inp = parity.to_device(make_custom(n, 64, [1 + (37 * i) % 400 for i in range(n)], 16, 128, seed=2, q_std=0.7, kv_std=0.7))
+    want, want_lse, keep = parity.run_gpu(inp)
+    assert (keep.num_units * 48 + keep.num_segments * 32 > 1 << 16) == big
+    args = (inp.q, inp.kv_cache, inp.kv_scales, inp.page_table)
+    other, results = torch.cuda.Stream(), []
+    ws = torch.empty(max(keep.workspace_bytes, 256), dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    for rep in range(4):
+        plan = oa.decode(*args, inp.seq_lens_host, inp.sink, inp.window, inp.softmax_scale)[2]
+        torch.cuda.synchronize()
+        _busy(other, 5)
+        out, lse = torch.zeros_like(want), torch.zeros_like(want_lse)
+        other.wait_stream(torch.cuda.current_stream())
+        oa.omniattn_decode(plan, *args, out, lse, ws, stream=other)
+        del plan
+        junk = [torch.full((1 << 16,), 255, dtype=torch.uint8, device="cuda") for _ in range(8)]
+        torch.cuda.synchronize()
+        results.append((out, lse, len(junk)))
+    for out, lse, _ in results:
+        assert torch.equal(out, want) and torch.equal(lse, want_lse)
