@@ -31,14 +31,16 @@ struct KernelCost {
 constexpr KernelCost kWideBf16 = {4 * kHeadsPerWave, 1, 1, 1.8, 5, 3.3, 36.0};
 // decode_mid_kernel, 64 rows to a work group: blocks of 64, or two groups to a block of 128.  bf16: side by side, so that
 // the second finds the tiles in its XCD's L2 and a sequence needs half the pieces; fp8: one behind the other, as many units
-// as there are compute units.
+// as there are compute units.  fp8: a segment costs as much as ten tiles of the loop (Q split into two terms, 64 rows
+// normalised and written), so sequences are cut only where that saves more: 93 mixed ones of 67 tiles at most go whole to
+// 186 units, 94 us, where 255 units filled to 54 tiles with 416 partial rows' slots took 114; 287 of 10 tiles 130 -> 94.
 constexpr KernelCost kPairBf16 = {2 * kHeadBlockMid, 2, 2, 1.03, 8, 5.0, 20.0};
 constexpr KernelCost kMidBf16 = {kHeadBlockMid, 1, 1, 1.5, 5, 3.5, 58.0};
-constexpr KernelCost kPairFp8 = {2 * kHeadBlockMid, 2, 1, 3.5, 4, 1.8, 65.0};
-constexpr KernelCost kMidFp8 = {kHeadBlockMid, 1, 1, 1.7, 8, 2.4, 65.0};
+constexpr KernelCost kPairFp8 = {2 * kHeadBlockMid, 2, 1, 3.6, 4, 1.8, 65.0};
+constexpr KernelCost kMidFp8 = {kHeadBlockMid, 1, 1, 1.5, 10, 2.5, 40.0};
 // decode_narrow_kernel, 32 rows: every tile passes through once per block.
 constexpr KernelCost kNarrowBf16 = {kHeadsPerWave, 1, 1, 1.4, 4, 4.3, 112.0};
-constexpr KernelCost kNarrowFp8 = {kHeadsPerWave, 1, 1, 1.5, 7, 2.7, 114.0};
+constexpr KernelCost kNarrowFp8 = {kHeadsPerWave, 1, 1, 1.5, 8, 4.0, 100.0};
 // Do not leave slivers shorter than this many tiles unless the item itself is shorter.
 constexpr int kMinSegTiles = 2;
 
