@@ -560,6 +560,20 @@ int build_host_plan(HostPlan& hp, const omniattn_problem_t& prob, const int32_t*
         kernel.seg = 1;
       }
     }
+    // Else, fp8 with fp32 results (partial rows twice as large): blocks of 64 rows, if there are no more of them than units and
+    // they cost no more by the estimate, with cuts as for the largest segment cost that leaves few enough partial rows.
+    // us with 59 to 76 MB of partial rows -> with 42: 49 sequences of 6800 tokens at most 115 -> 99, 9 of 2845 with 640 rows
+    // 66 -> 55, 66 of 8400 at most 105 -> 92.  (More blocks than units, 642 sequences of 9 tiles with 256 rows: 352 -> 383.)
+    if (fp8 && elt == 4 && kernels.size() == 3 && kernel.seg == kernels[0]->seg && best.slots > most_slots(kernel.head_block) &&
+        (int64_t)prob.batch * blocks_of(kMidFp8.head_block) <= num_cus) {
+      for (KernelCost k = kMidFp8; k.seg > 0; --k.seg) {
+        const Shape s = choose_shape(items, blocks_of(k.head_block), num_cus, k, most_slots(k.head_block), best.us);
+        if (s.us >= best.us || s.slots > most_slots(k.head_block)) continue;
+        best = s;
+        kernel = k;
+        break;
+      }
+    }
     hp.head_block = kernel.head_block;
     hp.groups = kernel.groups;
     lay_out(best, items, blocks_of(hp.head_block), num_cus / kernel.cus, kernel, hp);

@@ -53,6 +53,19 @@ def test_filled_units_stay_inside_the_static_scratch(batch, length, heads, q_len
     check_segments(p, batch)
 
 
+@pytest.mark.parametrize("batch, heads, q_len, lo, hi, sink, window, seed",
+                         [(9, 160, 4, 2845, 2845, 64, 16409, 284), (66, 48, 2, 14, 8379, 0, 8981, 3743),
+                          (49, 128, 1, 366, 63163, 130, 6693, 1762), (53, 128, 1, 7337, 23298, 128, 5266, 515)])
+def test_fp8_with_fp32_results_stays_inside_the_static_scratch(batch, heads, q_len, lo, hi, sink, window, seed):
+    """The 128-row plans of these, cheapest by the estimate, need 59 to 76 MB of fp32 partial rows; 64-row plans fit."""
+    rng = random.Random(seed)
+    lens = [rng.randint(lo, hi) for _ in range(batch)]
+    p = oa.omniattn_plan_host(lens, batch=batch, num_heads=heads, max_pages_per_seq=512, num_pages=1 << 16, sink=sink,
+                              window=window, softmax_scale=0.1, kv_dtype=oa.FP8_E4M3, out_dtype=oa.FP32, q_len=q_len)
+    assert 0 < p.workspace_bytes <= oa.omniattn_static_scratch_bytes() and p.num_units <= 256
+    check_segments(p, batch)
+
+
 def _planning_us(lens, **problem):
     def once():
         t = time.perf_counter()
