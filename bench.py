@@ -40,10 +40,10 @@ WORKLOAD = "r1_b64_32k"
 MEASURED_TRAFFIC = {
     "r1_b64_32k": {"bytes": 173_808_919 + 16_842_752,
                    "sources": ("decode_mid_kernel.hip", "decode_common.h"),
-                   "kernel_sha256": "4b25d584274d346271f0f2d1878e8fe2f9cc46a1b72a156e4b9af34465044500"},
+                   "kernel_sha256": "c1e7800a1337d4730f70991dec6e8a8be869d0fe0ea10af7a24bc43fc2d9a54d"},
     "fp8_b32_128k": {"bytes": 164_153_647 + 17_367_040,
                      "sources": ("decode_mid_kernel.hip", "decode_common.h"),
-                     "kernel_sha256": "4b25d584274d346271f0f2d1878e8fe2f9cc46a1b72a156e4b9af34465044500"},
+                     "kernel_sha256": "c1e7800a1337d4730f70991dec6e8a8be869d0fe0ea10af7a24bc43fc2d9a54d"},
 }
 CSRC = os.path.join(ROOT, "paper_2511_22481_amd", "csrc")
 

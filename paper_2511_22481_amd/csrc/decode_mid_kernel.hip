@@ -33,9 +33,10 @@
 // per SIMD and all of it in one hand-written stream: fp8 3,140, bf16 2,300.  Under load the clock is what gives way:
 // 2.25 GHz in a copy that leaves the loads out, 1.6 .. 1.9 with them, at the same cycle count; deeper prefetch (three
 // tiles in flight) and wave priorities change nothing.
-// us per decode, before -> now: fp8, 128 rows: 32 sequences of 8320 tokens 75 -> 67, 93 mixed 127 -> 116, 64 of
-// 32768 477 -> 413, 500 of up to 200 tokens 82 -> 73; bf16, 128 rows (two groups, one decode_kernel before): 64 of 2176
-// 58 -> 53.5, two queries each 92 -> 81; 32 of 4096 55 -> 51; 64 rows: 128 of 2176 88 -> 66.
+// us per decode, before -> now: fp8, 128 rows: 32 sequences of 8320 tokens 75 -> 67, 93 mixed 127 -> 116 (94 where the
+// planner leaves sequences whole), 64 of 32768 477 -> 413, 500 of up to 200 tokens 82 -> 73; bf16, 128 rows (two groups,
+// one decode_kernel before): 64 of 2176 58 -> 53.5, two queries each 92 -> 81; 32 of 4096 55 -> 51; 64 rows: 128 of 2176
+// 88 -> 66.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

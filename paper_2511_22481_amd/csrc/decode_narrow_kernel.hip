@@ -16,8 +16,8 @@
 // use, with two barriers per tile.  It is written with compiler builtins; bf16: all K fragments of a tile, and its V
 // fragments, are requested ahead of the matrix instructions that use them (128 sequences of 2176 tokens, 16 heads: 60.7 -> 58.4
 // us; one sequence of 128 heads 15.0 -> 14.6; four of 16 heads 10.7 -> 10.4).
-// us per decode, 128 sequences of 2176 kept tokens: 16 heads bf16 88 -> 62, fp8 94 -> 43; 64 heads fp8
-// 102 -> 64 (two blocks; bf16 stays with full head blocks); one sequence of 128 heads 26 -> 15.4.
+// us per decode against blocks of 128 rows: 128 sequences of 2176 kept tokens, 16 heads bf16 88 -> 59, fp8 94 -> 43; one
+// sequence of 128 heads 26 -> 14.9.  (64 heads are decode_mid_kernel's.)
 // Softmax reference (fixed per segment, second run if a logit leaves its range), weight formats,
 // masking and partial rows are those of the kernels for full head blocks.  The 8-bit product of 128 dims aligns
 // each 64 of them to their largest, as the one of 64 dims does: the logits carry the same error.
