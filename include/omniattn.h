@@ -125,7 +125,7 @@ int omniattn_plan_in(omniattn_plan_t** plan_out, const omniattn_problem_t* prob,
 int omniattn_plan_update(omniattn_plan_t* plan, const int32_t* seq_lens_host, void* hip_stream);
 int omniattn_plan_host(omniattn_plan_t** plan_out, const omniattn_problem_t* prob,
                        const int32_t* seq_lens_host, int32_t num_cus);
-/* NULL is allowed.  Frees the plan's own device metadata, which waits for the work of the device. */
+/* NULL is allowed.  Frees the plan's own device metadata, which waits for the work of the device (see omniattn_plan_in). */
 void omniattn_plan_destroy(omniattn_plan_t* plan);
 
 /* Introspection (host only, cheap). */

@@ -333,7 +333,8 @@ def decode(q, kv_cache, kv_scales, page_table, seq_lens_host, sink, window, soft
                         out_dtype=FP32 if odt == torch.float32 else BF16,
                         num_splits_hint=num_splits_hint, q_len=q_len)
         # The plan's device copy goes to a torch tensor: a plan with device memory of its own is mostly gone again when
-        # this call's results are, and freeing that waits for the whole decode (47 us a call, 28 without).  Not while
+        # this call's results are, and freeing that waits for the whole decode (47 us a call, 28 without; more than 16 of
+        # them dropped at a time wait all the same, for their pinned host buffers).  Not while
         # the stream captures: a graph reads the plan's buffers at every replay, so what can't be made then is refused.
         buffer = None
         if q.device.index == torch._C._cuda_getDevice() and not torch.cuda.is_current_stream_capturing():

@@ -101,6 +101,7 @@ int init_device(int dev) {
 
 void free_host(HostBuffers& b) {
   for (int i = 0; i < 2; ++i) {
+    if (b.busy[i] && !b.in_graph) (void)hipEventSynchronize(b.done[i]);
     if (b.h[i]) (void)hipHostFree(b.h[i]);
     if (b.done[i]) (void)hipEventDestroy(b.done[i]);
   }
@@ -109,44 +110,58 @@ void free_host(HostBuffers& b) {
 
 // Host buffers of destroyed plans, kept for the next one: a program that plans anew for each call paid two
 // pinned allocations, two events and their release each time (a plan made and destroyed: 70 us, now 16; with
-// the decode of 3 sequences of 48 heads: 119, now 46, and 28 with the device copy in a buffer of the caller's).  At most kSpare per device, of at most kSpareBytes
-// each; the rest is freed at once.  The device copy is not kept, though that would save 7 us more: kernels of
+// the decode of 3 sequences of 48 heads: 119, now 46, and 28 with the device copy in a buffer of the caller's).
+// At most kSpare pairs per device, of at most kSpareBytes each buffer; the rest is freed at once, which waits for the
+// device.  (16: a program that drops a dozen one-call plans, or runs that many calls ahead of its stream, waits for
+// nothing; 2 MB of host memory while plans fit 64 KB, as most do.)
+// The device copy is not kept, though that would save 7 us more: kernels of
 // any stream, and graphs, may still read a destroyed plan's copy.  Its release waits for them; a wait of
 // our own (hipDeviceSynchronize) breaks a capture under way on any thread.
-constexpr size_t kSpare = 2, kSpareBytes = 256 * 1024;
+constexpr size_t kSpare = 16, kSpareBytes = 256 * 1024;
 std::mutex g_spare_mutex;
 HostBuffers g_spare[kMaxDevices][kSpare];
 size_t g_spares[kMaxDevices] = {};
 
-// A buffer whose last copy is still under way is taken by plans of the same stream only: they would wait for what
-// their own stream does anyway, two plans back.  (A plan whose device copy is the caller's is destroyed without a wait.)
+// Buffers whose last copy is done come first.  (A plan whose device copy is the caller's is destroyed without a wait.)  One
+// whose copy is still under way is taken only when no more can be kept, and by plans of the same stream only: they would
+// wait for what their own stream does anyway, at least kSpare plans back.
 bool take_spare(int dev, size_t bytes, hipStream_t stream, HostBuffers& b) {
   std::lock_guard<std::mutex> lock(g_spare_mutex);
   size_t& n = g_spares[dev];
-  auto ready = [&](const HostBuffers& s) {
+  auto ready = [](const HostBuffers& s) {
     const int k = s.next;
-    if (!s.busy[k] || s.stream[k] == stream || hipEventQuery(s.done[k]) == hipSuccess) return true;
+    if (!s.busy[k] || hipEventQuery(s.done[k]) == hipSuccess) return true;
     (void)hipGetLastError();
     return false;
   };
-  for (size_t i = 0; i < n; ++i)
-    if (g_spare[dev][i].cap >= bytes && ready(g_spare[dev][i])) {
-      b = g_spare[dev][i];
-      g_spare[dev][i] = g_spare[dev][--n];
-      return true;
+  size_t own = kSpare;
+  for (size_t i = 0; i < n; ++i) {
+    const HostBuffers& s = g_spare[dev][i];
+    if (s.cap < bytes) continue;
+    if (ready(s)) {
+      own = i;
+      break;
     }
-  return false;
+    if (n == kSpare && own == kSpare && s.stream[s.next] == stream) own = i;
+  }
+  if (own == kSpare) return false;
+  b = g_spare[dev][own];
+  // (the others move up: the one given back first is taken first, its copy is the likeliest to be done)
+  std::copy(g_spare[dev] + own + 1, g_spare[dev] + n, g_spare[dev] + own);
+  --n;
+  return true;
 }
 
 void free_device(omniattn_plan_s* pl) {
-  const bool waited = !pl->meta.d || pl->meta.callers || hipFree(pl->meta.d) == hipSuccess;
-  const bool callers = pl->meta.callers;
+  const bool own = pl->meta.d && !pl->meta.callers;
+  const bool released = !own || hipFree(pl->meta.d) == hipSuccess;
   pl->meta.d = nullptr;
   pl->meta.cap = 0;
   pl->meta.callers = false;
   HostBuffers& b = pl->meta.host;
+  if (own && released) b.busy[0] = b.busy[1] = false;  // (hipFree has waited for the device)
   const int dev = pl->device;
-  if (waited && b.cap > 0 && b.cap <= kSpareBytes && !b.in_graph && dev >= 0 && dev < kMaxDevices) {
+  if (released && b.cap > 0 && b.cap <= kSpareBytes && !b.in_graph && dev >= 0 && dev < kMaxDevices) {
     std::lock_guard<std::mutex> lock(g_spare_mutex);
     if (g_spares[dev] < kSpare) {
       g_spare[dev][g_spares[dev]++] = b;
@@ -156,8 +171,6 @@ void free_device(omniattn_plan_s* pl) {
         if (kept.cap < b.cap) std::swap(kept, b);
     }
   }
-  for (int i = 0; callers && i < 2; ++i)  // (nothing has waited for their copies)
-    if (b.busy[i] && b.done[i]) (void)hipEventSynchronize(b.done[i]);
   free_host(b);
 }
 

@@ -155,3 +155,60 @@ def test_plan_of_a_one_call_decode_on_another_stream(big):
         results.append((out, lse, len(junk)))
     for out, lse, _ in results:
         assert torch.equal(out, want) and torch.equal(lse, want_lse)
+
+
+def _one_call(window=512):
+    inp = parity.to_device(make_custom(3, 48, [700, 90, 2000], 64, window, seed=1, q_std=0.7, kv_std=0.7))
+    return (inp.q, inp.kv_cache, inp.kv_scales, inp.page_table, inp.seq_lens_host, inp.sink, inp.window, inp.softmax_scale)
+
+
+@pytest.mark.gpu
+def test_dropping_several_one_call_plans_waits_for_nothing():
+    """More of them than the three that leave their pinned buffers behind, as a program has that keeps what the call returns."""
+    args = _one_call()
+    want = oa.decode(*args)[:2]
+    _spare_buffers()
+    held = [oa.decode(*args) for _ in range(6)]
+    torch.cuda.synchronize()
+    done = _busy(torch.cuda.Stream())
+    got = [r[:2] for r in held]
+    del held
+    still_running = not done.query()
+    torch.cuda.synchronize()
+    assert still_running
+    for out, lse in got:
+        assert torch.equal(out, want[0]) and torch.equal(lse, want[1])
+
+
+@pytest.mark.gpu
+def test_one_call_decodes_run_ahead_of_their_stream():
+    args = _one_call()
+    want = oa.decode(*args)[:2]
+    _spare_buffers()
+    done = _busy(torch.cuda.current_stream())
+    got = [oa.decode(*args)[:2] for _ in range(12)]
+    still_running = not done.query()
+    torch.cuda.synchronize()
+    assert still_running
+    for out, lse in got:
+        assert torch.equal(out, want[0]) and torch.equal(lse, want[1])
+
+
+@pytest.mark.gpu
+def test_more_plans_than_are_kept():
+    """Made and dropped while their stream is busy, of two sizes, so that kept buffers give way to larger ones whose place
+    they take, and are freed with their copies still under way."""
+    big = parity.to_device(make_custom(1300, 16, [1 + (37 * i) % 400 for i in range(1300)], 16, 128, seed=2, q_std=0.7, kv_std=0.7))
+    big_args = (big.q, big.kv_cache, big.kv_scales, big.page_table, big.seq_lens_host, big.sink, big.window, big.softmax_scale)
+    args = _one_call()
+    want, want_big = oa.decode(*args)[:2], oa.decode(*big_args)[:2]
+    torch.cuda.synchronize()
+    _busy(torch.cuda.current_stream(), 5)
+    held = [oa.decode(*args) for _ in range(24)] + [oa.decode(*big_args) for _ in range(4)]
+    got = [r[:2] for r in held]
+    del held
+    got += [oa.decode(*args)[:2] for _ in range(40)]
+    torch.cuda.synchronize()
+    for out, lse in got:
+        w = want if out.shape == want[0].shape else want_big
+        assert torch.equal(out, w[0]) and torch.equal(lse, w[1])
