@@ -1,5 +1,6 @@
 """Plans that come and go: the buffers of a destroyed plan serve the next one, also while another stream
 still decodes with the destroyed plan's copy.  Making a plan waits for no stream and breaks no capture."""
+import ctypes
 import threading
 
 import pytest
@@ -212,3 +213,50 @@ def test_more_plans_than_are_kept():
     for out, lse in got:
         w = want if out.shape == want[0].shape else want_big
         assert torch.equal(out, w[0]) and torch.equal(lse, w[1])
+
+
+@pytest.mark.gpu
+def test_update_of_a_one_call_plan_that_outgrows_its_buffer():
+    """Pieces of one tile first, 24 KB of metadata in the wrapper's 64 KB; then eight pieces a sequence, in memory of the
+    plan's own; then short sequences again."""
+    n = 300
+    short, long = [20 + i % 12 for i in range(n)], [400 + i % 100 for i in range(n)]
+    inp = parity.to_device(make_custom(n, 64, long, 16, 1024, seed=2, q_std=0.7, kv_std=0.7))
+    args = (inp.q, inp.kv_cache, inp.kv_scales, inp.page_table)
+    rest = (inp.sink, inp.window, inp.softmax_scale)
+    small, small_lse, plan = oa.decode(*args, short, *rest, num_splits_hint=8)
+    want, want_lse, ref = oa.decode(*args, long, *rest, num_splits_hint=8)
+    size = lambda p: p.num_units * 48 + p.num_segments * 32
+    assert size(plan) < 1 << 16 < size(ref)
+    for lens, w, w_lse in ((long, want, want_lse), (short, small, small_lse), (long, want, want_lse)):
+        oa.omniattn_plan_update(plan, lens)
+        ws = torch.empty(max(plan.workspace_bytes, 256), dtype=torch.uint8, device="cuda")
+        out, lse = torch.zeros_like(want), torch.zeros_like(want_lse)
+        oa.omniattn_decode(plan, *args, out, lse, ws)
+        torch.cuda.synchronize()
+        assert torch.equal(out, w) and torch.equal(lse, w_lse)
+
+
+def _plan_in(buffer, size):
+    prob = oa.binding._problem(batch=2, num_heads=64, max_pages_per_seq=8, num_pages=16, sink=16, window=256, softmax_scale=0.1)
+    lens, address = oa.binding._lens_array([700, 900])
+    h = ctypes.c_void_p()
+    return oa.load_library().omniattn_plan_in(ctypes.byref(h), ctypes.byref(prob), address, buffer, size, None), h
+
+
+@pytest.mark.parametrize("offset", [1, 4, 8, 15])
+def test_a_misaligned_plan_buffer_is_refused(offset):
+    rc, h = _plan_in(4096 + offset, 1 << 16)
+    assert rc == -1 and not h.value
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("size", [0, 15, 16, 1 << 16])
+def test_plan_buffer_of_any_size(size):
+    """One that does not hold the metadata is left alone: memory of the plan's own instead."""
+    buffer = torch.full((1 << 16,), 77, dtype=torch.uint8, device="cuda")
+    rc, h = _plan_in(buffer.data_ptr(), size)
+    assert rc == 0 and h.value
+    torch.cuda.synchronize()
+    assert bool((buffer == 77).all()) == (size < 1 << 16)
+    oa.load_library().omniattn_plan_destroy(h)
