@@ -209,9 +209,12 @@ def test_groups_of_64_rows_over_a_bf16_cache(heads, q_len, groups):
     poison_unretained(inp, keep)
     again, lse2, _ = _run(inp, q_len, heads, out_dtype=torch.float32)
     assert torch.equal(out, again) and torch.equal(lse, lse2)
-    out16, _, _ = _run(inp, q_len, heads)
-    if plan.num_partials == 0:
-        assert torch.equal(out.to(torch.bfloat16), out16)
+    out16, lse16, plan16 = _run(inp, q_len, heads)
+    assert plan16.unit_groups == groups and plan16.head_block == 64 * groups
+    if plan.num_partials == plan16.num_partials == 0:
+        assert torch.equal(out.to(torch.bfloat16), out16) and torch.equal(lse, lse16)
+    else:
+        _check(inp, out16, lse16, q_len, f"{heads} heads, {q_len} queries, bf16 results")
 
 
 @pytest.mark.gpu
@@ -242,3 +245,47 @@ def test_two_groups_to_a_block_where_a_sequence_would_be_cut_more():
     assert [plan(64, h, 2048).unit_groups for h in (64, 96, 128)] == [1, 2, 2] and plan(64, 128, 2048, 2).unit_groups == 2
     assert plan(64, 128, 2048).num_units == 128 and plan(64, 128, 2048, 2).num_partials == 0
     assert plan(256, 128, 4096).unit_groups == 1 and plan(64, 128, 2048, 4).unit_groups == 1
+
+
+def _long_problem(kv, heads, lens, seed):
+    """Sequences of tens of thousands of tokens, all kept, whose pages are drawn from a pool that they share."""
+    pool, longest = 700, max(lens)
+    inp = make_custom(len(lens), heads, [1] * len(lens), 0, longest, seed=seed, kv_dtype=kv, q_std=0.25, kv_std=0.7,
+                      spare_pages=pool - len(lens))
+    g = torch.Generator().manual_seed(seed)
+    table = torch.stack([torch.randperm(pool, generator=g)[:-(-longest // 128)] for _ in lens]).to(torch.int32)
+    return parity.to_device(dataclasses.replace(inp, page_table=table, seq_lens_host=lens, seq_lens=torch.tensor(lens, dtype=torch.int32)))
+
+
+@pytest.mark.gpu
+def test_segments_of_a_thousand_tiles_over_a_bf16_cache():
+    """Segments of 64 rows and up to 1024 tiles, as many as a segment may have: two rounds of page-table entries to a
+    thread, and every wave has some.  (One tile from another page shifts a row by 4 %.)"""
+    lens = [32768 - 37 * (i % 5) for i in range(256)]
+    inp = _long_problem("bf16", 64, lens, 5)
+    out, lse, plan = parity.run_gpu(inp, out_dtype=torch.float32)
+    sizes = [s["tile_hi"] - s["tile_lo"] for s in plan.segments()]
+    assert plan.head_block == 64 and plan.num_partials == 0 and set(sizes) == {1020, 1021, 1022, 1023, 1024}
+    rng = random.Random(1)
+    pairs = [(b, rng.randrange(64)) for b in (0, 255, *(rng.randrange(256) for _ in range(22)))]
+    parity.assert_parity(inp, out, lse, pairs=pairs, row_rel_l2=1e-2, what="bf16")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("heads", [64, 128])
+def test_segments_of_a_thousand_tiles_over_an_fp8_cache(heads):
+    """Whole sequences of up to 1024 tiles, also against the same ones in 16 pieces.  Both round the same weights; a piece is
+    normalised by the sum of its rounded ones, which is within 2^-4 / sqrt(its tokens) < 2e-3 of the exact sum by which it is
+    merged (20,000 tokens: 1,250 to a piece)."""
+    lens = [65536, 40001, 33333, 65501, 20000]
+    inp = _long_problem("fp8", heads, lens, 6)
+    out, lse, plan = parity.run_gpu(inp, out_dtype=torch.float32, num_splits_hint=1)
+    assert plan.head_block == heads and plan.head_block // plan.unit_groups == 64 and plan.num_partials == 0
+    assert sorted(s["tile_hi"] - s["tile_lo"] for s in plan.segments()) == [313, 521, 626, 1024, 1024]
+    rng = random.Random(2)
+    pairs = [(b, rng.randrange(heads)) for b in range(5) for _ in range(4)]
+    parity.assert_parity(inp, out, lse, pairs=pairs, row_rel_l2=2e-2, what=f"fp8, {heads} heads")
+    cut, cut_lse, plan = parity.run_gpu(inp, out_dtype=torch.float32, num_splits_hint=16)
+    assert plan.head_block == heads and plan.max_splits == 16
+    rows = (out - cut).norm(dim=-1) / cut.norm(dim=-1)
+    assert float(rows.max()) <= 4e-3 and float((lse - cut_lse).abs().max()) <= 1e-4, (float(rows.max()), float((lse - cut_lse).abs().max()))
