@@ -259,7 +259,9 @@ __global__ __launch_bounds__(kWavesM * 64, 2) void decode_mid_kernel(DecodeParam
     int ex = m >> 7;
     ex = ex == 0 ? 0 : (ex > 254 ? 254 : ex) - 127 - 7;
     const float inv_s = __builtin_amdgcn_ldexpf(p.scale_log2 < 0.f ? -1.0f : 1.0f, -ex);
-    if (part == 0) *LDS_PTR(float, lds_max + (8 * wave8 + (lane >> 3)) * 4) = __builtin_amdgcn_ldexpf(fabsf(p.scale_log2), ex);
+    // (never 0: a masked position's -infinity has to survive it)
+    if (part == 0)
+      *LDS_PTR(float, lds_max + (8 * wave8 + (lane >> 3)) * 4) = fmaxf(__builtin_amdgcn_ldexpf(fabsf(p.scale_log2), ex), 1.1754944e-38f);
     constexpr float kLo = (float)(1 << kQLoShiftM);
 #pragma unroll
     for (int i = 0; i < 9; ++i) {

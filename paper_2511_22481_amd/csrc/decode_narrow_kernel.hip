@@ -272,7 +272,7 @@ __global__ __launch_bounds__(kWavesN * 64, 1) void decode_narrow_kernel(DecodePa
       int ex = (int)(m >> 7);
       ex = ex == 0 ? 0 : (ex > 254 ? 254 : ex) - 127 - 7;
       const float inv_s = __builtin_amdgcn_ldexpf(p.scale_log2 < 0.f ? -1.0f : 1.0f, -ex);
-      c_head = __builtin_amdgcn_ldexpf(fabsf(p.scale_log2), ex);
+      c_head = fmaxf(__builtin_amdgcn_ldexpf(fabsf(p.scale_log2), ex), 1.1754944e-38f);  // (never 0: a masked position's -infinity has to survive it)
       constexpr float kLo = (float)(1 << kQLoShiftN);
 #pragma unroll
       for (int ks = 0; ks < kKS; ++ks)

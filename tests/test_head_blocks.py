@@ -289,3 +289,15 @@ def test_segments_of_a_thousand_tiles_over_an_fp8_cache(heads):
     assert plan.head_block == heads and plan.max_splits == 16
     rows = (out - cut).norm(dim=-1) / cut.norm(dim=-1)
     assert float(rows.max()) <= 4e-3 and float((lse - cut_lse).abs().max()) <= 1e-4, (float(rows.max()), float((lse - cut_lse).abs().max()))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("heads", [16, 64, 128])
+def test_zero_softmax_scale_with_tiny_queries_over_an_fp8_cache(heads):
+    """The scale taken times a query row's power of two is below the smallest float: masked positions stay masked."""
+    inp = make_custom(3, heads, [333, 70, 5], 3, 100, seed=9, kv_dtype="fp8", q_std=1.0, kv_std=0.7, softmax_scale=0.0)
+    inp.q = (inp.q.float() * 2.0 ** -60).to(torch.bfloat16)
+    inp = parity.to_device(inp)
+    out, lse, plan = parity.run_gpu(inp, out_dtype=torch.float32, num_splits_hint=1)
+    assert plan.head_block == {16: 32}.get(heads, heads)
+    parity.assert_parity(inp, out, lse, row_rel_l2=1e-2, what=f"{heads} heads")
