@@ -103,7 +103,9 @@ typedef struct omniattn_plan_s omniattn_plan_t; /* opaque, library-owned */
  *                    asynchronous copy from the plan's pinned buffer and one small
  *                    kernel on `hip_stream`; nothing is allocated and nothing
  *                    synchronises unless the new plan needs more metadata than any
- *                    before it.  The plan must not be in use by a decode on another
+ *                    before it.  (There are two pinned buffers: an update waits until
+ *                    the copy two updates back is done, so the host runs at most two
+ *                    updates ahead.)  The plan must not be in use by a decode on another
  *                    stream.  The workspace size may change: ask again.  On failure
  *                    for bad lengths the plan is unchanged.  A plan made by
  *                    omniattn_plan_host is planned again on the host only.
@@ -117,8 +119,9 @@ int omniattn_plan(omniattn_plan_t** plan_out, const omniattn_problem_t* prob,
 /*
  * omniattn_plan with the metadata's device copy in `buffer` (device memory of the caller's, 16-byte aligned) if it holds
  * them, else in memory of the plan's own, as also after an update that outgrows it.  The buffer stays the caller's: it
- * has to live until the decodes of this plan are done, and destroying the plan then neither frees device memory nor
- * waits for any.
+ * has to live until the decodes of this plan are done, and destroying the plan then frees no device memory.  Nor does it
+ * wait for any work, unless its pinned host buffers have to be freed: those of up to 16 destroyed plans per device are kept
+ * for plans to come; those of further ones, those above 256 KB and those that a captured omniattn_plan_update reads are freed.
  */
 int omniattn_plan_in(omniattn_plan_t** plan_out, const omniattn_problem_t* prob, const int32_t* seq_lens_host,
                      void* buffer, size_t buffer_bytes, void* hip_stream);
@@ -188,7 +191,7 @@ int omniattn_plan_tile_range(const omniattn_plan_t* plan, int32_t b, int32_t til
  * logits and lse carry fp32 accumulation error only; the softmax weights, with the token's
  * scale folded in, are rounded to e4m3 (relative 2^-4 per weight) and out is normalised by
  * the sum of the rounded weights.  A token whose scale is more than 2^10 below the largest
- * scale of its 64-token tile (with blocks of 64 heads: of its half of the tile, 32 tokens)
+ * scale of its half of a 64-token tile (with blocks of 32 heads: of the whole tile)
  * has its value row taken at 2^-10 of that largest scale (its softmax weight counts in full).
  */
 int omniattn_decode(const omniattn_plan_t* plan, const void* q, const void* kv_cache,

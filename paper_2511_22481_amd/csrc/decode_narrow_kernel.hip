@@ -500,7 +500,7 @@ __global__ __launch_bounds__(kWavesN * 64, 1) void decode_narrow_kernel(DecodePa
           int es = (int)((r01 > r23 ? r01 : r23) >> 23) - 126;
           es = es < -100 ? -100 : es;
           const float floor_w = __builtin_amdgcn_ldexpf(1.0f, es - 10);
-          // block exponent of the head's 32 weights: the largest lands in [2^7, 2^8)
+          // block exponent of the head's 32 weights: all are below 2^8 (see decode_mid_kernel.hip)
           const float mt = mx - ref;
           int kk = mt == -INFINITY ? 0 : (int)ceilf(mt) - 8 + es;
           kk = mt == -INFINITY ? 0 : kk < -126 ? -126 : kk > 126 ? 126 : kk;

@@ -34,6 +34,8 @@ constexpr KernelCost kWideBf16 = {4 * kHeadsPerWave, 1, 1, 1.8, 5, 3.3, 36.0};
 // as there are compute units.  fp8: a segment costs as much as ten tiles of the loop (Q split into two terms, 64 rows
 // normalised and written), so sequences are cut only where that saves more: 93 mixed ones of 67 tiles at most go whole to
 // 186 units, 94 us, where 255 units filled to 54 tiles with 416 partial rows' slots took 114; 287 of 10 tiles 130 -> 94.
+// bf16 pair: the costs hold for rows in HBM (input sets in turn, 1.2 GB together) as for repeated calls, within 2 %; rows that
+// another kernel has just written are another matter (see decode_mid_kernel.hip), but a decode's rows are older than that.
 constexpr KernelCost kPairBf16 = {2 * kHeadBlockMid, 2, 2, 1.03, 8, 5.0, 20.0};
 constexpr KernelCost kMidBf16 = {kHeadBlockMid, 1, 1, 1.5, 5, 3.5, 58.0};
 constexpr KernelCost kPairFp8 = {2 * kHeadBlockMid, 2, 1, 3.6, 4, 1.8, 65.0};
@@ -490,8 +492,11 @@ int build_host_plan(HostPlan& hp, const omniattn_problem_t& prob, const int32_t*
   if (hp.heads_total > kHeadsPerWave) {
     kernels.push_back(&wide);
     // bf16, two groups of 64 rows side by side: up to 256 rows, of which the last block's second half has more than 16.
-    // (More rows: six or eight groups pull every tile through one L2.  384 rows, 64 sequences 144 -> 141 us, 40 82 -> 76;
-    // 512 rows, 64 143 -> 158, 20 64 -> 70.)
+    // us with decode_kernel / with the pair, on rows that no cache holds.  Inside: 128 rows, 64 sequences of 2176 kept tokens
+    // 58.7 / 52.3, 32 of 4096 56.6 / 50.6, 128 of 2176 93 / 84; 256 rows, 64 of 2176 87 / 79.  Outside the pair is not offered,
+    // though most of these would gain too: 72 rows, 64 of 600 34 / 26, 64 of 2176 51 / 50; 192 rows, 64 of 600 41 / 27, 64 of 2176
+    // 90 / 69, 40 of 2176 64 / 63; 208 rows, 128 of 2176 149 / 167; 384 rows, 40 of 2176 84 / 77, 64 of 2176 143 / 141, 64 of 600
+    // 45 / 56; 512 rows, 64 of 2176 140 / 158, 64 of 600 52 / 58 (six or eight groups pull every tile through one L2).
     const int last_rows = (hp.heads_total - 1) % kPairBf16.head_block + 1;
     if (fp8) kernels.push_back(&kMidFp8);
     else if (hp.heads_total <= kHeadBlockMid) kernels.push_back(&kMidBf16);
@@ -560,8 +565,11 @@ int build_host_plan(HostPlan& hp, const omniattn_problem_t& prob, const int32_t*
         kernel.seg = 1;
       }
     }
-    // Else, fp8 with fp32 results (partial rows twice as large): blocks of 64 rows, if there are no more of them than units and
-    // they cost no more by the estimate, with cuts as for the largest segment cost that leaves few enough partial rows.
+    // Else, fp8 with fp32 results (partial rows twice as large): blocks of 64 rows, if there are no more of them than units,
+    // with cuts as for the largest segment cost that leaves few enough partial rows, and if by the estimate at that cost, which
+    // understates it (a segment costs ten tiles whatever the cuts assume), they take no longer: a plan that fits is worth that.
+    // (Of 780,000 random problems 3,310 come here; at ten tiles 11 are estimated to take up to 10 % longer, and three of those that
+    // were timed took 104.8 -> 102.9, 94 -> 77 and 107 -> 98 us.)
     // us with 59 to 76 MB of partial rows -> with 42: 49 sequences of 6800 tokens at most 115 -> 99, 9 of 2845 with 640 rows
     // 66 -> 55, 66 of 8400 at most 105 -> 92.  (More blocks than units, 642 sequences of 9 tiles with 256 rows: 352 -> 383.)
     if (fp8 && elt == 4 && kernels.size() == 3 && kernel.seg == kernels[0]->seg && best.slots > most_slots(kernel.head_block) &&
