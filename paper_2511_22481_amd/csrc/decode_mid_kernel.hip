@@ -40,7 +40,7 @@
 // one decode_kernel before): 64 of 2176 58 -> 53.5, two queries each 92 -> 81; 32 of 4096 55 -> 51; 64 rows: 128 of 2176
 // 88 -> 66.  The same with input sets in turn, 1.2 GB together (58.7 -> 52.3, 56.6 -> 50.6, 84 -> 64).
 // Two groups to a block where every row has just been written by another kernel, which leaves them in the last-level cache:
-// 32 of 4096 read 226 MB instead of 158, the second group's tiles are no longer in L2 when it asks for them; 57 -> 66 us,
+// 32 of 4096 read 230 MB instead of 162, the second group's tiles are no longer in L2 when it asks for them; 57 -> 66 us,
 // 64 of 2176 59 -> 71, 128 of 4096 148 -> 207 (32 of 2176 42 -> 41, 256 rows 91 -> 85).  Reading the rows without `nt` ends that
 // (main kernel 57 -> 49 us) and costs everything else 3 to 15 % (64 rows, 256 of 2176: 108 -> 124 us); `nt` for one of the groups, or
 // the second group started 1 us later, does no better.
