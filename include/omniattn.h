@@ -122,6 +122,8 @@ int omniattn_plan(omniattn_plan_t** plan_out, const omniattn_problem_t* prob,
  * has to live until the decodes of this plan are done, and destroying the plan then frees no device memory.  Nor does it
  * wait for any work, unless its pinned host buffers have to be freed: those of up to 16 destroyed plans per device are kept
  * for plans to come; those of further ones, those above 256 KB and those that a captured omniattn_plan_update reads are freed.
+ * Making a plan, here or by omniattn_plan, waits for no stream but its own, and for that only where 16 are kept and the last
+ * copy from each of them is still under way.
  */
 int omniattn_plan_in(omniattn_plan_t** plan_out, const omniattn_problem_t* prob, const int32_t* seq_lens_host,
                      void* buffer, size_t buffer_bytes, void* hip_stream);
