@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "kernels.h"
 
 namespace omniattn {
@@ -112,6 +114,32 @@ __device__ __forceinline__ void swap16(float& a, float& b) {
 }
 __device__ __forceinline__ void swap32(float& a, float& b) {
   asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
+}
+
+// Four bf16 query elements (two words) in two e4m3 terms, q = 2^ex (hi + lo / 16): .x the high terms, .y the low ones.
+// scale = 2^ex, inv = 2^-ex, both normal.  Seven instructions for two elements: the scaled conversion takes the bf16 pair
+// as it is, and the remainder is one fused multiply-add (the product with a power of two is exact).
+constexpr int kQLoShift = 4;  // the low term is stored 16 times too large
+__device__ __forceinline__ u32x2 split_q4(uint32_t w0, uint32_t w1, float scale, float inv) {
+  typedef __attribute__((ext_vector_type(2))) short s16x2;
+  s16x2 hi = {0, 0}, lo = {0, 0};
+  auto two = [&](uint32_t w, auto upper_tag) {
+    constexpr bool upper = decltype(upper_tag)::value;
+    hi = __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(hi, __builtin_bit_cast(bf16x2, w), scale, upper);
+    const f32x2 back = __builtin_amdgcn_cvt_pk_f32_fp8(__builtin_bit_cast(int, hi), upper);
+    lo = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(lo, fmaf(__builtin_bit_cast(float, w << 16), inv, -back[0]),
+                                                  fmaf(__builtin_bit_cast(float, w & 0xffff0000u), inv, -back[1]), 1.0f / (1 << kQLoShift), upper);
+  };
+  two(w0, std::false_type{});
+  two(w1, std::true_type{});
+  return u32x2{__builtin_bit_cast(uint32_t, hi), __builtin_bit_cast(uint32_t, lo)};
+}
+// The exponent for a row whose largest magnitude has the bits m: that goes to [128, 256), as far as scale and inv are normal.
+__device__ __forceinline__ int split_q_exponent(int m) {
+  const int e = m >> 7;
+  if (e == 0) return 0;
+  const int ex = (e > 254 ? 254 : e) - 127 - 7;
+  return ex < -126 ? -126 : ex;
 }
 
 // The XCD (accelerator complex die) this wave runs on: compute units of one XCD share an L2.

@@ -56,8 +56,6 @@ namespace omniattn {
 
 namespace {
 
-typedef __attribute__((ext_vector_type(2))) unsigned short u16x2;
-
 constexpr int kHB = kHeadBlockMid;  // 64
 constexpr int kStagesM = 4;
 constexpr int kStageM = 36864;
@@ -81,7 +79,6 @@ constexpr int kLdsMidFp8 = kOffScalesM + kStagesM * kScaleM;
 static_assert(3 * kStatM * 4 <= kRoleWaves * 2 * kScaleM && kLdsMidFp8 <= 160 * 1024, "LDS of one compute unit");
 
 constexpr float kRefSlackM = 64.f;  // see the kernel for blocks of 128 rows: fixed softmax reference with retry
-constexpr int kQLoShiftM = 4;       // the query's low term is stored 16 times too large
 
 // LDS layout of a stage: the value part of the rows, then their rope parts; 16-byte chunks XORed with a
 // function of the row, as in the other kernels.
@@ -238,8 +235,10 @@ __global__ __launch_bounds__(kWavesM * 64, 2) void decode_mid_kernel(DecodeParam
     __syncthreads();
     return true;
   };
-  // fp8: the query rows that the wave has fetched, in two e4m3 terms.  In place: 16 bytes that held 8 dims hold their high, then their low terms.  Eight lanes to a
-  // row.  (Once for each row: in the four waves of S^T, each for its 32 rows, it took 9 K cycles more per segment.)
+  // fp8: the query rows that the wave has fetched, in two e4m3 terms.  In place: 16 bytes that held 8 dims hold their high, then
+  // their low terms.  Eight lanes to a row.  Bound by vector instructions, two waves to a SIMD: 5,200 -> 3,100 cycles with seven of
+  // them for two elements instead of eleven (split_q4) and a maximum that costs half of one.  (Once for each row: in the four
+  // waves of S^T, each for its 32 rows, it took 9 K cycles more per segment.)
   auto split_q = [&]() {
     const int lane = fresh_lane(), part = lane & 7, r = 8 * (wave8 & 3) + (lane >> 3);
     const uint32_t base = lds0 + (2 + (wave8 >> 2)) * kStageM;
@@ -248,14 +247,19 @@ __global__ __launch_bounds__(kWavesM * 64, 2) void decode_mid_kernel(DecodeParam
                    : base + kTailBaseM + r * QY::kTail + ((part ^ QY::sw_tail(r)) << 4);
     };
     u32x4 raw[9];
-    u16x2 mx = {0, 0};
+    float mx = 0.f;
 #pragma unroll
     for (int i = 0; i < 9; ++i) raw[i] = *LDS_PTR(u32x4, chunk(i));
+    // (a word as a float is its upper number, the lower ones are needed shifted up in any case; NaN is passed over)
 #pragma unroll
     for (int i = 0; i < 9; ++i)
 #pragma unroll
-      for (int k = 0; k < 4; ++k) mx = __builtin_elementwise_max(mx, __builtin_bit_cast(u16x2, raw[i][k] & 0x7fff7fffu));
-    int m = mx[0] > mx[1] ? mx[0] : mx[1];
+      for (int k = 0; k < 4; k += 2) {
+        const uint32_t w0 = raw[i][k], w1 = raw[i][k + 1];  // (a bit cast of the element itself reads element 0)
+        mx = fmaxf(fmaxf(mx, fabsf(__builtin_bit_cast(float, w0))), fabsf(__builtin_bit_cast(float, w1)));
+        mx = fmaxf(fmaxf(mx, fabsf(__builtin_bit_cast(float, w0 << 16))), fabsf(__builtin_bit_cast(float, w1 << 16)));
+      }
+    int m = __builtin_bit_cast(uint32_t, mx) >> 16;
 #define OA_DPP_MAX(ctrl)                                                        \
   {                                                                             \
     const int o = __builtin_amdgcn_update_dpp(0, m, (ctrl), 0xf, 0xf, true);    \
@@ -263,35 +267,18 @@ __global__ __launch_bounds__(kWavesM * 64, 2) void decode_mid_kernel(DecodeParam
   }
     OA_DPP_MAX(0xb1) OA_DPP_MAX(0x4e) OA_DPP_MAX(0x141)  // lanes ^ 1, ^ 2, and the mirror of the eight
 #undef OA_DPP_MAX
-    int ex = m >> 7;
-    ex = ex == 0 ? 0 : (ex > 254 ? 254 : ex) - 127 - 7;
-    const float inv_s = __builtin_amdgcn_ldexpf(p.scale_log2 < 0.f ? -1.0f : 1.0f, -ex);
+    const int ex = split_q_exponent(m);
+    const float scale = __builtin_amdgcn_ldexpf(1.0f, ex), inv = __builtin_amdgcn_ldexpf(1.0f, -ex);
     // (never 0: a masked position's -infinity has to survive it)
     if (part == 0)
       *LDS_PTR(float, lds_max + (8 * wave8 + (lane >> 3)) * 4) = fmaxf(__builtin_amdgcn_ldexpf(fabsf(p.scale_log2), ex), 1.1754944e-38f);
-    constexpr float kLo = (float)(1 << kQLoShiftM);
+    if (p.scale_log2 < 0.f)
+#pragma unroll
+      for (int i = 0; i < 9; ++i) raw[i] ^= 0x80008000u;
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
-      u32x4 t;
-#pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        int hi = 0, lo = 0;
-        {
-          const float x0 = __builtin_bit_cast(float, raw[i][2 * k] << 16) * inv_s, x1 = __builtin_bit_cast(float, raw[i][2 * k] & 0xffff0000u) * inv_s;
-          hi = __builtin_amdgcn_cvt_pk_fp8_f32(x0, x1, hi, false);
-          const f32x2 back = __builtin_amdgcn_cvt_pk_f32_fp8(hi, false);
-          lo = __builtin_amdgcn_cvt_pk_fp8_f32((x0 - back[0]) * kLo, (x1 - back[1]) * kLo, lo, false);
-        }
-        {
-          const float x0 = __builtin_bit_cast(float, raw[i][2 * k + 1] << 16) * inv_s, x1 = __builtin_bit_cast(float, raw[i][2 * k + 1] & 0xffff0000u) * inv_s;
-          hi = __builtin_amdgcn_cvt_pk_fp8_f32(x0, x1, hi, true);
-          const f32x2 back = __builtin_amdgcn_cvt_pk_f32_fp8(hi, true);
-          lo = __builtin_amdgcn_cvt_pk_fp8_f32((x0 - back[0]) * kLo, (x1 - back[1]) * kLo, lo, true);
-        }
-        t[k] = hi;
-        t[2 + k] = lo;
-      }
-      *LDS_PTR(u32x4, chunk(i)) = t;
+      const u32x2 a = split_q4(raw[i][0], raw[i][1], scale, inv), b = split_q4(raw[i][2], raw[i][3], scale, inv);
+      *LDS_PTR(u32x4, chunk(i)) = u32x4{a[0], b[0], a[1], b[1]};
     }
   };
   // (every wave looks at all 64 heads, so all take the same way)
@@ -320,24 +307,35 @@ __global__ __launch_bounds__(kWavesM * 64, 2) void decode_mid_kernel(DecodeParam
         bf16x8 qf[FP8 ? 1 : 2][FP8 ? 1 : kKS];
         i32x8 qh[FP8 ? kKS : 1], ql[FP8 ? kKS : 1];
         float c = p.scale_log2;  // logits are raw products times c, in the log2 domain
+        // Chunk c of row r lies at r * 1024 + ((c ^ sw_main(r)) << 4), and the swizzle touches only the low four bits of c: an address
+        // per value of those bits, the rest are immediate offsets.  (An address for each of the 36 reads took 340 vector
+        // instructions and 1,000 cycles more.)
         const uint32_t lq = lds0 + (2 + hg) * kStageM;
-        auto q_chunk = [&](int r, int ch) -> u32x4 {
-          return *LDS_PTR(u32x4, lq + (ch < 64 ? r * QY::kMain + ((ch ^ QY::sw_main(r)) << 4)
-                                               : kTailBaseM + r * QY::kTail + (((ch - 64) ^ QY::sw_tail(r)) << 4)));
-        };
+        auto q_read = [&](uint32_t at, int imm) { return *LDS_PTR(u32x4, at + imm); };
         if constexpr (!FP8) {
+          // (the swizzles of rows r and r + 16 are alike)
+          uint32_t am[4], at[2];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) am[k] = lq + n16 * QY::kMain + (((4 * k + q4) ^ QY::sw_main(n16)) << 4);
+#pragma unroll
+          for (int k = 0; k < 2; ++k) at[k] = lq + kTailBaseM + n16 * QY::kTail + (((4 * k + q4) ^ QY::sw_tail(n16)) << 4);
 #pragma unroll
           for (int a = 0; a < 2; ++a)
 #pragma unroll
             for (int ks = 0; ks < kKS; ++ks)
-              qf[a][ks] = __builtin_bit_cast(bf16x8, ks < 16 ? q_chunk(16 * a + n16, 4 * ks + q4) : q_chunk(16 * a + n16, 64 + 4 * (ks - 16) + q4));
+              qf[a][ks] = __builtin_bit_cast(bf16x8, ks < 16 ? q_read(am[ks & 3], (ks >> 2) * 256 + a * 16 * QY::kMain)
+                                                             : q_read(at[ks & 1], a * 16 * QY::kTail));
         } else {
-          auto q_raw = [&](int ks, int j) { return ks < 8 ? q_chunk(n32, 8 * ks + 4 * g + j) : q_chunk(n32, 64 + 4 * g + j); };
+          uint32_t am[8], at[4];
+#pragma unroll
+          for (int k = 0; k < 8; ++k) am[k] = lq + n32 * QY::kMain + (((8 * (k >> 2) + 4 * g + (k & 3)) ^ QY::sw_main(n32)) << 4);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) at[k] = lq + kTailBaseM + n32 * QY::kTail + (((4 * g + k) ^ QY::sw_tail(n32)) << 4);
 #pragma unroll
           for (int ks = 0; ks < kKS; ++ks)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-              const u32x4 r = q_raw(ks, j);
+              const u32x4 r = ks < 8 ? q_read(am[4 * (ks & 1) + j], (ks >> 1) * 256) : q_read(at[j], 0);
               qh[ks][2 * j] = r[0];
               qh[ks][2 * j + 1] = r[1];
               ql[ks][2 * j] = r[2];
@@ -437,7 +435,7 @@ __global__ __launch_bounds__(kWavesM * 64, 2) void decode_mid_kernel(DecodeParam
               if constexpr ((m & 1) == 0) {
                 s = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fr[ks % kRing], qh[ks], s, 0, 0, 0, 127, 0, 127);
               } else {
-                s = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fr[ks % kRing], ql[ks], s, 0, 0, 0, 127, 0, 127 - kQLoShiftM);
+                s = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fr[ks % kRing], ql[ks], s, 0, 0, 0, 127, 0, 127 - kQLoShift);
                 if constexpr (ks + kRing < kKS) fr[ks % kRing] = load_k(ks + kRing);
               }
               if constexpr (!FIRST) {

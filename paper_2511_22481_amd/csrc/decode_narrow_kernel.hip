@@ -50,7 +50,6 @@ constexpr int kLdsNarrowFp8 = kOffScales + kWavesN * kStagesN * kScaleStageN;
 static_assert(kLdsNarrowFp8 <= 160 * 1024, "LDS of one compute unit");
 
 constexpr float kRefSlackN = 64.f;  // see the bf16 kernel: fixed softmax reference with retry
-constexpr int kQLoShiftN = 4;       // see decode_mid_kernel.hip: the query's low term is stored 16 times too large
 
 // LDS layout of a stage: the value part of the rows, then their rope parts; 16-byte chunks XORed with a
 // function of the row, as in the kernels for full head blocks (16 consecutive rows at one chunk index
@@ -255,50 +254,32 @@ __global__ __launch_bounds__(kWavesN * 64, 1) void decode_narrow_kernel(DecodePa
       }
     }
     if constexpr (FP8) {
-      // split of the query row, see decode_mid_kernel.hip: q = 2^e (hi + lo / 16), row maximum in [128, 256)
-      uint32_t m = 0;
+      // split of the query row: q = 2^ex (hi + lo / 16), row maximum in [128, 256) (see decode_common.h, and decode_mid_kernel.hip
+      // for the maximum: words as floats)
+      float mx_q = 0.f;
 #pragma unroll
       for (int ks = 0; ks < kKS; ++ks)
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            const uint32_t a = raw[ks][j][k] & 0x7fffu, b = (raw[ks][j][k] >> 16) & 0x7fffu;
-            m = m > a ? m : a;
-            m = m > b ? m : b;
+          for (int k = 0; k < 4; k += 2) {
+            const uint32_t w0 = raw[ks][j][k], w1 = raw[ks][j][k + 1];
+            mx_q = fmaxf(fmaxf(mx_q, fabsf(__builtin_bit_cast(float, w0))), fabsf(__builtin_bit_cast(float, w1)));
+            mx_q = fmaxf(fmaxf(mx_q, fabsf(__builtin_bit_cast(float, w0 << 16))), fabsf(__builtin_bit_cast(float, w1 << 16)));
           }
-      // bf16 magnitudes order like integers, and so do these (positive, finite) floats
-      m = (uint32_t)quad_max((float)m);
-      int ex = (int)(m >> 7);
-      ex = ex == 0 ? 0 : (ex > 254 ? 254 : ex) - 127 - 7;
-      const float inv_s = __builtin_amdgcn_ldexpf(p.scale_log2 < 0.f ? -1.0f : 1.0f, -ex);
+      const int ex = split_q_exponent(__builtin_bit_cast(uint32_t, quad_max(mx_q)) >> 16);
+      const float scale = __builtin_amdgcn_ldexpf(1.0f, ex), inv = __builtin_amdgcn_ldexpf(1.0f, -ex);
       c_head = fmaxf(__builtin_amdgcn_ldexpf(fabsf(p.scale_log2), ex), 1.1754944e-38f);  // (never 0: a masked position's -infinity has to survive it)
-      constexpr float kLo = (float)(1 << kQLoShiftN);
+      const uint32_t sign = p.scale_log2 < 0.f ? 0x80008000u : 0u;
 #pragma unroll
       for (int ks = 0; ks < kKS; ++ks)
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
           for (int k2 = 0; k2 < 2; ++k2) {
-            int hi = 0, lo = 0;
-            {
-              const uint32_t pr = raw[ks][j][k2 * 2];
-              const float x0 = __builtin_bit_cast(float, pr << 16) * inv_s;
-              const float x1 = __builtin_bit_cast(float, pr & 0xffff0000u) * inv_s;
-              hi = __builtin_amdgcn_cvt_pk_fp8_f32(x0, x1, hi, false);
-              const f32x2 back = __builtin_amdgcn_cvt_pk_f32_fp8(hi, false);
-              lo = __builtin_amdgcn_cvt_pk_fp8_f32((x0 - back[0]) * kLo, (x1 - back[1]) * kLo, lo, false);
-            }
-            {
-              const uint32_t pr = raw[ks][j][k2 * 2 + 1];
-              const float x0 = __builtin_bit_cast(float, pr << 16) * inv_s;
-              const float x1 = __builtin_bit_cast(float, pr & 0xffff0000u) * inv_s;
-              hi = __builtin_amdgcn_cvt_pk_fp8_f32(x0, x1, hi, true);
-              const f32x2 back = __builtin_amdgcn_cvt_pk_f32_fp8(hi, true);
-              lo = __builtin_amdgcn_cvt_pk_fp8_f32((x0 - back[0]) * kLo, (x1 - back[1]) * kLo, lo, true);
-            }
-            qh[ks][j * 2 + k2] = hi;
-            ql[ks][j * 2 + k2] = lo;
+            const u32x2 t = split_q4(raw[ks][j][k2 * 2] ^ sign, raw[ks][j][k2 * 2 + 1] ^ sign, scale, inv);
+            qh[ks][j * 2 + k2] = t[0];
+            ql[ks][j * 2 + k2] = t[1];
           }
     }
 
@@ -415,7 +396,7 @@ __global__ __launch_bounds__(kWavesN * 64, 1) void decode_narrow_kernel(DecodePa
               const i32x4 lo = *LDS_PTR(i32x4, ad), hi = *LDS_PTR(i32x4, ad ^ 16u);
               const i32x8 k8 = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
               s[a] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(k8, qh[ks], s[a], 0, 0, 0, 127, 0, 127);
-              s[a] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(k8, ql[ks], s[a], 0, 0, 0, 127, 0, 127 - kQLoShiftN);
+              s[a] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(k8, ql[ks], s[a], 0, 0, 0, 127, 0, 127 - kQLoShift);
             }
           }
         } else {
