@@ -15,7 +15,7 @@
 // bf16 or 64 fp8 tokens) are filled by direct global->LDS loads, three tiles ahead of the one in
 // use, with two barriers per tile.  It is written with compiler builtins; bf16: all K fragments of a tile, and its V
 // fragments, are requested ahead of the matrix instructions that use them (128 sequences of 2176 tokens, 16 heads: 60.7 -> 58.4
-// us; one sequence of 128 heads 15.0 -> 14.6; four of 16 heads 10.7 -> 10.4).
+// us; one sequence of 128 heads 15.0 -> 14.6; four of 16 heads 10.7 -> 10.4; their start is quicker since, see there).
 // us per decode against blocks of 128 rows: 128 sequences of 2176 kept tokens, 16 heads bf16 88 -> 59, fp8 94 -> 43; one
 // sequence of 128 heads 26 -> 14.9.  (64 heads are decode_mid_kernel's.)
 // Softmax reference (fixed per segment, second run if a logit leaves its range), weight formats,
@@ -43,7 +43,7 @@ constexpr int kOffP = kStagesN * kStageN;
 constexpr int kOffKK = kOffP + kHeadsPerWave * kPRow;
 constexpr int kOffStat = kOffKK + kStatN * 4;
 constexpr int kOffTiles = kOffStat + 4 * kStatN * 4;
-constexpr int kOffScales = kOffTiles + kMaxSegTiles * 8;
+constexpr int kOffScales = kOffTiles + kMaxSegTiles * 4;
 constexpr int kScaleStageN = kTileFp8 * 4;
 constexpr int kLdsNarrowBf16 = kOffScales;
 constexpr int kLdsNarrowFp8 = kOffScales + kWavesN * kStagesN * kScaleStageN;
@@ -148,39 +148,54 @@ __global__ __launch_bounds__(kWavesN * 64, 1) void decode_narrow_kernel(DecodePa
       return (pos0 + Y::kTok <= sink_end) || (pos0 >= L - p.W && pos0 + Y::kTok <= L0);
     };
 
-    // ---- tile table: first global byte of every tile, bit 0 = every position kept ----
+    // ---- tile table (unit of the cache that holds the tile, bit 0 = every position kept) and Q ----
+    // A call of a few tiles per unit is a chain of round trips: unit header, page-table entries, rows.  The entries go straight
+    // to the table and the block's 32 query rows (1152 bytes each, through stage 3, laid out like bf16 cache rows) right behind
+    // them, so that Q travels with them and is read, and split, while the first tiles are on their way; then each thread turns
+    // its own entries into the table's.  us per decode, entries through registers and Q requested with tile 0 -> now: one
+    // sequence, 128 heads, 2176 tokens 14.92 -> 14.54 (fp8 15.22 -> 15.02), four of 576 tokens, 16 heads 10.30 -> 10.17
+    // (fp8 11.68 -> 11.32), 128 of 2176, 16 heads 59.3 -> 59.0.
+    // (A segment without tiles reads no entry: its row of the table may hold nothing valid.  Query rows past the last head
+    // repeat it; their results are never written.)
     constexpr int kTabPerThread = kMaxSegTiles / (kWavesN * 64);
-    const int32_t* pt_row = p.page_table + (size_t)sg.b * p.max_pages;
-    int page_of[kTabPerThread];
-    // (a segment without tiles reads no entry: its row of the table may hold nothing valid)
+    constexpr int kQLoads = 9;
+    const uint32_t lds_q = lds0 + 3 * kStageN;
+    using QY = Lay<false>;
+    if (n_tiles > 0) {
+      const uint8_t* pt_row = (const uint8_t*)(p.page_table + (size_t)sg.b * p.max_pages);
 #pragma unroll
-    for (int u = 0; u < kTabPerThread; ++u) {
-      const int t = tid + u * kWavesN * 64;
-      page_of[u] = 0;
-      if (u * kWavesN * 64 < n_tiles) page_of[u] = pt_row[tile_pos(t < n_tiles ? t : n_tiles - 1) >> 7];
-    }
-
-#pragma unroll
-    for (int u = 0; u < kTabPerThread; ++u) {
-      const int t = tid + u * kWavesN * 64;
-      if (t < n_tiles) {
-        const int pos0 = tile_pos(t);
-        const uint64_t a = (uint64_t)(uintptr_t)p.kv + ((uint64_t)page_of[u] * kPage + (pos0 & (kPage - 1))) * Y::kRow;
-        *LDS_PTR(u32x2, lds_tiles + t * 8) = u32x2{(uint32_t)a | (uint32_t)tile_full(pos0), (uint32_t)(a >> 32)};
+      for (int u = 0; u < kTabPerThread; ++u) {
+        const int t = tid + u * kWavesN * 64, t0 = (u * kWavesN + wave) * 64;
+        if (t0 < n_tiles) load_lds4(lds_tiles + t0 * 4, pt_row, (uint32_t)(tile_pos(t < n_tiles ? t : n_tiles - 1) >> 7) << 2);
       }
+      const uint8_t* qbase = (const uint8_t*)p.q + (size_t)sg.b * p.H * QY::kRow;
+      auto q_head = [&](int r) -> uint32_t { return h0 + r < p.H ? h0 + r : p.H - 1; };
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const int r = 8 * wave + k;
+        load_lds16<false>(lds_q + r * QY::kMain, qbase, q_head(r) * QY::kRow + ((lane ^ QY::sw_main(r)) << 4));
+      }
+      const int r = 8 * wave + (lane >> 3);
+      load_lds16<false>(lds_q + kTailBaseN + wave * 1024, qbase, q_head(r) * QY::kRow + QY::kMain + (((lane & 7) ^ QY::sw_tail(r)) << 4));
+      wait_vm<kQLoads>();
+#pragma unroll
+      for (int u = 0; u < kTabPerThread; ++u) {
+        const int t = tid + u * kWavesN * 64;
+        if (t < n_tiles) {
+          const int pos0 = tile_pos(t);
+          const uint32_t page = *LDS_PTR(uint32_t, lds_tiles + t * 4);
+          *LDS_PTR(uint32_t, lds_tiles + t * 4) = (page * (kPage / Y::kTok) + ((pos0 / Y::kTok) & (kPage / Y::kTok - 1))) << 1 | (uint32_t)tile_full(pos0);
+        }
+      }
+      __syncthreads();
     }
-    __syncthreads();
 
     // ---- tile loader: wave w fetches rows [w * kRowsPerWave, ...) into stage it & 3 ----
     // All rows of a tile are fetched, kept or not (a tile lies inside one page, so they exist); what
     // is not kept is masked and cleared when the tile is used.
-    auto tile_entry = [&](int it) -> u32x2 {
-      return *LDS_PTR(u32x2, lds_tiles + (it < kMaxSegTiles ? it : kMaxSegTiles - 1) * 8);
-    };
     auto issue_tile = [&](int it) {
-      const u32x2 e = tile_entry(it);
-      const uint32_t e_lo = __builtin_amdgcn_readfirstlane(e.x), e_hi = __builtin_amdgcn_readfirstlane(e.y);
-      const uint8_t* gbase = (const uint8_t*)(uintptr_t)(((uint64_t)e_hi << 32) | (e_lo & ~1u));
+      const uint64_t unit_of_cache = (uint32_t)__builtin_amdgcn_readfirstlane(*LDS_PTR(uint32_t, lds_tiles + it * 4)) >> 1;
+      const uint8_t* gbase = p.kv + unit_of_cache * kStageN;
       const uint32_t st = stage_base(it);
       const int row0 = wave * kRowsPerWave;
 #pragma unroll
@@ -195,7 +210,7 @@ __global__ __launch_bounds__(kWavesN * 64, 1) void decode_narrow_kernel(DecodePa
                        row * Y::kRow + Y::kMain + (((lane % kTailChunks) ^ Y::sw_tail(row)) << 4));
       if constexpr (FP8)
         load_lds4(lds_scales + (wave * kStagesN + (it & (kStagesN - 1))) * kScaleStageN,
-                  (const uint8_t*)(p.kv_scales + (gbase - p.kv) / Y::kRow), lane << 2);
+                  (const uint8_t*)(p.kv_scales + unit_of_cache * Y::kTok), lane << 2);
     };
     // this wave's share of tile `it` has arrived; later tiles (at most two were requested) may be in flight
     auto wait_tile = [&](int it) {
@@ -205,24 +220,14 @@ __global__ __launch_bounds__(kWavesN * 64, 1) void decode_narrow_kernel(DecodePa
       else wait_vm<0>();
     };
 
-    // ---- Q: the block's 32 rows (1152 bytes each) pass through stage 3, laid out like bf16 cache rows ----
-    // (rows past the last head repeat it; their results are never written)
-    const uint32_t lds_q = lds0 + 3 * kStageN;
-    using QY = Lay<false>;
+    // Q, which is older than the tiles, is read (and split) while they are on their way.
     if (n_tiles > 0) {
-      const uint8_t* qbase = (const uint8_t*)p.q + (size_t)sg.b * p.H * QY::kRow;
-      auto q_head = [&](int r) -> uint32_t { return h0 + r < p.H ? h0 + r : p.H - 1; };
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const int r = 8 * wave + k;
-        load_lds16<false>(lds_q + r * QY::kMain, qbase, q_head(r) * QY::kRow + ((lane ^ QY::sw_main(r)) << 4));
-      }
-      const int r = 8 * wave + (lane >> 3);
-      load_lds16<false>(lds_q + kTailBaseN + wave * 1024, qbase, q_head(r) * QY::kRow + QY::kMain + (((lane & 7) ^ QY::sw_tail(r)) << 4));
       issue_tile(0);
       if (n_tiles > 1) issue_tile(1);
       if (n_tiles > 2) issue_tile(2);
-      wait_tile(0);  // and Q, which is older
+      if (n_tiles > 2) wait_vm<3 * kDmaPerTile>();
+      else if (n_tiles == 2) wait_vm<2 * kDmaPerTile>();
+      else wait_vm<kDmaPerTile>();
       __syncthreads();
     }
     // The B operand of S^T, 16 heads.  bf16: lane (head n16, q4) holds dims 32 ks + 8 q4 .. + 7, ks = 0..17.

@@ -292,6 +292,21 @@ def test_segments_of_a_thousand_tiles_over_an_fp8_cache(heads):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("kv", ["bf16", "fp8"])
+def test_segments_of_a_thousand_tiles_of_32_rows(kv):
+    """One round of page-table entries to a thread, or two to four, and waves without any in the last.  (As above: one tile from
+    another page shifts a row by 4 %; the rounding of the weights is that of the tests above.)"""
+    tile = 32 if kv == "bf16" else 64
+    lens = [tile * t - cut for t, cut in ((1024, 0), (769, 5), (513, 0), (257, tile - 1), (256, 0), (65, 1), (64, 0))]
+    inp = _long_problem(kv, 16, lens, 8)
+    out, lse, plan = parity.run_gpu(inp, out_dtype=torch.float32, num_splits_hint=1)
+    assert plan.head_block == 32 and plan.num_partials == 0
+    assert sorted(s["tile_hi"] - s["tile_lo"] for s in plan.segments()) == [64, 65, 256, 257, 513, 769, 1024]
+    pairs = [(b, h) for b in range(len(lens)) for h in (b, 15)]
+    parity.assert_parity(inp, out, lse, pairs=pairs, row_rel_l2=1e-2 if kv == "bf16" else 2e-2, what=kv)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("heads", [16, 64, 128])
 def test_zero_softmax_scale_with_tiny_queries_over_an_fp8_cache(heads):
     """The scale taken times a query row's power of two is below the smallest float: masked positions stay masked."""
