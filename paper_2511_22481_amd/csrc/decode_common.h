@@ -135,9 +135,9 @@ __device__ __forceinline__ u32x2 split_q4(uint32_t w0, uint32_t w1, float scale,
   return u32x2{__builtin_bit_cast(uint32_t, hi), __builtin_bit_cast(uint32_t, lo)};
 }
 // The exponent for a row whose largest magnitude has the bits m: that goes to [128, 256), as far as scale and inv are normal.
+// (A row of subnormal numbers, multiples of 2^-133 below 2^-126, becomes multiples of 2^-7 below 1: exact in the two terms.)
 __device__ __forceinline__ int split_q_exponent(int m) {
   const int e = m >> 7;
-  if (e == 0) return 0;
   const int ex = (e > 254 ? 254 : e) - 127 - 7;
   return ex < -126 ? -126 : ex;
 }

@@ -322,9 +322,10 @@ def test_zero_softmax_scale_with_tiny_queries_over_an_fp8_cache(heads):
 @pytest.mark.parametrize("heads", [16, 64, 128])
 @pytest.mark.parametrize("exponent", [-100, -118, -119, -120, -122, -126, -130])
 def test_tiny_queries_over_an_fp8_cache(heads, exponent):
-    """The power of two of a query row is kept to a normal number, and so is its reciprocal; negative softmax scales as well.  Logits
-    are zero to single precision: lse is the logarithm of the kept tokens, the output the mean of their values."""
-    for scale in (1.0, -0.5):
+    """The power of two of a query row is kept to a normal number, and so is its reciprocal; at 2^-130 all elements are subnormal.
+    Softmax scales of about one leave logits of zero to single precision: lse is the logarithm of the kept tokens, the output
+    the mean of their values.  Scales of 0.1 over the queries' size, of both signs, give the logits of ordinary queries."""
+    for scale in (1.0, -0.5, 0.1 * 2.0 ** -exponent, -0.1 * 2.0 ** -exponent):
         inp = make_custom(3, heads, [333, 70, 5], 3, 100, seed=9, kv_dtype="fp8", q_std=1.0, kv_std=0.7, softmax_scale=scale)
         inp.q = (inp.q.float() * 2.0 ** exponent).to(torch.bfloat16)
         inp = parity.to_device(inp)
