@@ -141,6 +141,11 @@ __device__ __forceinline__ int split_q_exponent(int m) {
   const int ex = (e > 254 ? 254 : e) - 127 - 7;
   return ex < -126 ? -126 : ex;
 }
+// What the row's raw products are multiplied by.  Never 0: a masked position's -infinity has to survive it.  (Subnormal, it is
+// off by at most 2^-150, a logit by 2^-22.)
+__device__ __forceinline__ float split_q_factor(float scale_log2, int ex) {
+  return fmaxf(__builtin_amdgcn_ldexpf(fabsf(scale_log2), ex), 0x1p-149f);
+}
 
 // The XCD (accelerator complex die) this wave runs on: compute units of one XCD share an L2.
 __device__ __forceinline__ uint32_t xcc_id() {

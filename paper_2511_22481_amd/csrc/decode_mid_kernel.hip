@@ -277,9 +277,7 @@ __global__ __launch_bounds__(kWavesM * 64, 2) void decode_mid_kernel(DecodeParam
 #undef OA_DPP_MAX
     const int ex = split_q_exponent(m);
     const float scale = __builtin_amdgcn_ldexpf(1.0f, ex), inv = __builtin_amdgcn_ldexpf(1.0f, -ex);
-    // (never 0: a masked position's -infinity has to survive it)
-    if (part == 0)
-      *LDS_PTR(float, lds_max + (8 * wave8 + (lane >> 3)) * 4) = fmaxf(__builtin_amdgcn_ldexpf(fabsf(p.scale_log2), ex), 1.1754944e-38f);
+    if (part == 0) *LDS_PTR(float, lds_max + (8 * wave8 + (lane >> 3)) * 4) = split_q_factor(p.scale_log2, ex);
     if (p.scale_log2 < 0.f)
 #pragma unroll
       for (int i = 0; i < 9; ++i) raw[i] ^= 0x80008000u;

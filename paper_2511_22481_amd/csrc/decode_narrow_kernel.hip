@@ -274,7 +274,7 @@ __global__ __launch_bounds__(kWavesN * 64, 1) void decode_narrow_kernel(DecodePa
           }
       const int ex = split_q_exponent(__builtin_bit_cast(uint32_t, quad_max(mx_q)) >> 16);
       const float scale = __builtin_amdgcn_ldexpf(1.0f, ex), inv = __builtin_amdgcn_ldexpf(1.0f, -ex);
-      c_head = fmaxf(__builtin_amdgcn_ldexpf(fabsf(p.scale_log2), ex), 1.1754944e-38f);  // (never 0: a masked position's -infinity has to survive it)
+      c_head = split_q_factor(p.scale_log2, ex);
       const uint32_t sign = p.scale_log2 < 0.f ? 0x80008000u : 0u;
 #pragma unroll
       for (int ks = 0; ks < kKS; ++ks)

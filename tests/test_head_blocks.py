@@ -332,3 +332,16 @@ def test_tiny_queries_over_an_fp8_cache(heads, exponent):
         out, lse, plan = parity.run_gpu(inp, out_dtype=torch.float32, num_splits_hint=1)
         assert plan.head_block == {16: 32}.get(heads, heads)
         parity.assert_parity(inp, out, lse, row_rel_l2=1e-2, what=f"{heads} heads, 2^{exponent}, scale {scale}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("heads", [16, 64, 128])
+@pytest.mark.parametrize("scale", [2.0 ** -124, -2.0 ** -124])
+def test_tiny_softmax_scales_with_huge_rows_over_an_fp8_cache(heads, scale):
+    """The softmax scale times a query row's power of two is subnormal, and raw products of up to 2^126 make logits of it."""
+    inp = make_custom(3, heads, [333, 70, 5], 3, 100, seed=9, kv_dtype="fp8", q_std=1.0, kv_std=0.7, softmax_scale=scale)
+    inp.kv_scales = inp.kv_scales * 2.0 ** 113
+    inp = parity.to_device(inp)
+    out, lse, plan = parity.run_gpu(inp, out_dtype=torch.float32, num_splits_hint=1)
+    assert plan.head_block == {16: 32}.get(heads, heads)
+    parity.assert_parity(inp, out, lse, row_rel_l2=1e-2, what=f"{heads} heads, scale {scale}")
