@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <limits>
 #include <mutex>
 #include <new>
 #include <string>
@@ -443,10 +444,10 @@ int omniattn_decode_timed(const omniattn_plan_t* plan, const void* q, const void
   dp.head_block = hp.head_block;
   dp.out_fp32 = hp.prob.out_dtype == OMNIATTN_FP32;
   dp.n_units = (int)hp.unit_seg.size() - 1;
-  // A zero scale (uniform attention) is replaced by one too small to matter: the kernel
-  // marks masked positions with an infinity that must survive the multiplication.
+  // A zero scale (uniform attention) is replaced by the smallest number, with which no finite product makes a
+  // logit above 2^-21: the kernel marks masked positions with an infinity that must survive the multiplication.
   dp.scale_log2 = hp.prob.softmax_scale * 1.4426950408889634f;
-  if (dp.scale_log2 == 0.f) dp.scale_log2 = 1e-30f;
+  if (dp.scale_log2 == 0.f) dp.scale_log2 = std::numeric_limits<float>::denorm_min();
   if (ev_begin) OA_HIP(hipEventRecord((hipEvent_t)ev_begin, stream));
   if (hp.head_block == kHeadsPerWave) OA_HIP(launch_decode_narrow(dp, fp8, (int)hp.unit_seg.size() - 1, stream));
   else if (hp.head_block / hp.groups == kHeadBlockMid) OA_HIP(launch_decode_mid(dp, fp8, (int)hp.unit_seg.size() - 1, stream));

@@ -345,3 +345,19 @@ def test_tiny_softmax_scales_with_huge_rows_over_an_fp8_cache(heads, scale):
     out, lse, plan = parity.run_gpu(inp, out_dtype=torch.float32, num_splits_hint=1)
     assert plan.head_block == {16: 32}.get(heads, heads)
     parity.assert_parity(inp, out, lse, row_rel_l2=1e-2, what=f"{heads} heads, scale {scale}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kv", ["bf16", "fp8"])
+@pytest.mark.parametrize("heads", [16, 64, 128])
+def test_zero_softmax_scale_with_huge_rows(kv, heads):
+    """All kept tokens weigh the same however large their products with the query are; masked positions stay masked."""
+    inp = make_custom(3, heads, [333, 70, 5], 3, 100, seed=9, kv_dtype=kv, q_std=1.0, kv_std=0.7, softmax_scale=0.0)
+    if kv == "fp8":
+        inp.kv_scales = inp.kv_scales * 2.0 ** 110
+    else:
+        inp.kv_cache = inp.kv_cache * 2.0 ** 110
+    inp = parity.to_device(inp)
+    for hint in (0, 1):
+        out, lse, _ = parity.run_gpu(inp, num_splits_hint=hint)
+        parity.assert_parity(inp, out, lse, row_rel_l2=1e-2, what=f"{kv}, {heads} heads, hint {hint}")
