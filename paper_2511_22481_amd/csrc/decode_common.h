@@ -118,7 +118,8 @@ __device__ __forceinline__ void swap32(float& a, float& b) {
 
 // Four bf16 query elements (two words) in two e4m3 terms, q = 2^ex (hi + lo / 16): .x the high terms, .y the low ones.
 // scale = 2^ex, inv = 2^-ex, both normal.  Seven instructions for two elements: the scaled conversion takes the bf16 pair
-// as it is, and the remainder is one fused multiply-add (the product with a power of two is exact).
+// as it is, and the remainder is one fused multiply-add (the product with a power of two is exact).  An element that is NaN or
+// an infinity leaves a NaN code in its terms (the conversions do not saturate), and the row's result is NaN.
 constexpr int kQLoShift = 4;  // the low term is stored 16 times too large
 __device__ __forceinline__ u32x2 split_q4(uint32_t w0, uint32_t w1, float scale, float inv) {
   typedef __attribute__((ext_vector_type(2))) short s16x2;

@@ -361,3 +361,24 @@ def test_zero_softmax_scale_with_huge_rows(kv, heads):
     for hint in (0, 1):
         out, lse, _ = parity.run_gpu(inp, num_splits_hint=hint)
         parity.assert_parity(inp, out, lse, row_rel_l2=1e-2, what=f"{kv}, {heads} heads, hint {hint}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kv", ["bf16", "fp8"])
+@pytest.mark.parametrize("heads", [16, 64, 128])
+def test_a_query_element_that_is_no_number(kv, heads):
+    """NaN or an infinity in one element, the lower and the upper one of a word, of the value and the rope part, beside numbers:
+    that row is NaN, all others are the same bits as without it.  (fp8 cache: the row's largest element passes over it.)"""
+    inp = parity.to_device(make_custom(3, heads, [333, 70, 200], 3, 100, seed=9, kv_dtype=kv, q_std=1.0, kv_std=0.7))
+    q, bad = inp.q, (1, heads // 2 + 1)
+    for hint in (0, 1, 4):
+        inp.q = q
+        out0, lse0, plan = parity.run_gpu(inp, num_splits_hint=hint)
+        for value in (float("nan"), float("inf"), float("-inf")):
+            for dim in (16, 17, 511, 512, 575):
+                inp.q = q.clone()
+                inp.q[bad + (dim,)] = value
+                out, lse, _ = parity.run_gpu(inp, plan=plan)
+                assert torch.isnan(out[bad]).all() and torch.isnan(lse[bad]), (hint, value, dim)
+                out[bad], lse[bad] = out0[bad], lse0[bad]
+                assert torch.equal(out, out0) and torch.equal(lse, lse0), (hint, value, dim)
