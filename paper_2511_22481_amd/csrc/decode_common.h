@@ -135,6 +135,13 @@ __device__ __forceinline__ u32x2 split_q4(uint32_t w0, uint32_t w1, float scale,
   two(w1, std::true_type{});
   return u32x2{__builtin_bit_cast(uint32_t, hi), __builtin_bit_cast(uint32_t, lo)};
 }
+// The larger of mx and the magnitudes of four bf16 numbers (two words), in the upper half of a float: a word as a float is its
+// upper number, the lower ones are needed shifted up in any case.  NaN is passed over, and so is an infinity whose word reads
+// as NaN (see above for what becomes of such a row).
+__device__ __forceinline__ float bf16_max4(float mx, uint32_t w0, uint32_t w1) {
+  mx = fmaxf(fmaxf(mx, fabsf(__builtin_bit_cast(float, w0))), fabsf(__builtin_bit_cast(float, w1)));
+  return fmaxf(fmaxf(mx, fabsf(__builtin_bit_cast(float, w0 << 16))), fabsf(__builtin_bit_cast(float, w1 << 16)));
+}
 // The exponent for a row whose largest magnitude has the bits m: that goes to [128, 256), as far as scale and inv are normal.
 // (A row of subnormal numbers, multiples of 2^-133 below 2^-126, becomes multiples of 2^-7 below 1: exact in the two terms.)
 __device__ __forceinline__ int split_q_exponent(int m) {

@@ -258,15 +258,10 @@ __global__ __launch_bounds__(kWavesM * 64, 2) void decode_mid_kernel(DecodeParam
     float mx = 0.f;
 #pragma unroll
     for (int i = 0; i < 9; ++i) raw[i] = *LDS_PTR(u32x4, chunk(i));
-    // (a word as a float is its upper number, the lower ones are needed shifted up in any case; NaN is passed over)
 #pragma unroll
     for (int i = 0; i < 9; ++i)
 #pragma unroll
-      for (int k = 0; k < 4; k += 2) {
-        const uint32_t w0 = raw[i][k], w1 = raw[i][k + 1];  // (a bit cast of the element itself reads element 0)
-        mx = fmaxf(fmaxf(mx, fabsf(__builtin_bit_cast(float, w0))), fabsf(__builtin_bit_cast(float, w1)));
-        mx = fmaxf(fmaxf(mx, fabsf(__builtin_bit_cast(float, w0 << 16))), fabsf(__builtin_bit_cast(float, w1 << 16)));
-      }
+      for (int k = 0; k < 4; k += 2) mx = bf16_max4(mx, raw[i][k], raw[i][k + 1]);
     int m = __builtin_bit_cast(uint32_t, mx) >> 16;
 #define OA_DPP_MAX(ctrl)                                                        \
   {                                                                             \

@@ -259,19 +259,14 @@ __global__ __launch_bounds__(kWavesN * 64, 1) void decode_narrow_kernel(DecodePa
       }
     }
     if constexpr (FP8) {
-      // split of the query row: q = 2^ex (hi + lo / 16), row maximum in [128, 256) (see decode_common.h, and decode_mid_kernel.hip
-      // for the maximum: words as floats)
+      // split of the query row: q = 2^ex (hi + lo / 16), row maximum in [128, 256) (see decode_common.h)
       float mx_q = 0.f;
 #pragma unroll
       for (int ks = 0; ks < kKS; ++ks)
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
-          for (int k = 0; k < 4; k += 2) {
-            const uint32_t w0 = raw[ks][j][k], w1 = raw[ks][j][k + 1];
-            mx_q = fmaxf(fmaxf(mx_q, fabsf(__builtin_bit_cast(float, w0))), fabsf(__builtin_bit_cast(float, w1)));
-            mx_q = fmaxf(fmaxf(mx_q, fabsf(__builtin_bit_cast(float, w0 << 16))), fabsf(__builtin_bit_cast(float, w1 << 16)));
-          }
+          for (int k = 0; k < 4; k += 2) mx_q = bf16_max4(mx_q, raw[ks][j][k], raw[ks][j][k + 1]);
       const int ex = split_q_exponent(__builtin_bit_cast(uint32_t, quad_max(mx_q)) >> 16);
       const float scale = __builtin_amdgcn_ldexpf(1.0f, ex), inv = __builtin_amdgcn_ldexpf(1.0f, -ex);
       c_head = split_q_factor(p.scale_log2, ex);
