@@ -347,20 +347,29 @@ def test_tiny_softmax_scales_with_huge_rows_over_an_fp8_cache(heads, scale):
     parity.assert_parity(inp, out, lse, row_rel_l2=1e-2, what=f"{heads} heads, scale {scale}")
 
 
+def _rows_of_a_group(kv, heads):
+    """Of the kernels that 81 sequences of 640 tokens run on, as the planner has it and one work unit per sequence."""
+    return {("bf16", 64): {64, 128}, ("bf16", 128): {64, 128}, ("fp8", 64): {32, 64}, ("fp8", 128): {64}}.get((kv, heads), {32})
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("kv", ["bf16", "fp8"])
 @pytest.mark.parametrize("heads", [16, 64, 128])
 def test_zero_softmax_scale_with_huge_rows(kv, heads):
     """All kept tokens weigh the same however large their products with the query are; masked positions stay masked."""
-    inp = make_custom(3, heads, [333, 70, 5], 3, 100, seed=9, kv_dtype=kv, q_std=1.0, kv_std=0.7, softmax_scale=0.0)
+    lens = [333, 70, 5] + [640] * 78
+    inp = make_custom(81, heads, lens, 3, 600, seed=9, kv_dtype=kv, q_std=1.0, kv_std=0.7, softmax_scale=0.0)
     if kv == "fp8":
         inp.kv_scales = inp.kv_scales * 2.0 ** 110
     else:
         inp.kv_cache = inp.kv_cache * 2.0 ** 110
     inp = parity.to_device(inp)
+    rows = set()
     for hint in (0, 1):
-        out, lse, _ = parity.run_gpu(inp, num_splits_hint=hint)
+        out, lse, plan = parity.run_gpu(inp, num_splits_hint=hint)
+        rows.add(plan.head_block // plan.unit_groups)
         parity.assert_parity(inp, out, lse, row_rel_l2=1e-2, what=f"{kv}, {heads} heads, hint {hint}")
+    assert rows == _rows_of_a_group(kv, heads)
 
 
 @pytest.mark.gpu
@@ -369,11 +378,13 @@ def test_zero_softmax_scale_with_huge_rows(kv, heads):
 def test_a_query_element_that_is_no_number(kv, heads):
     """NaN or an infinity in one element, the lower and the upper one of a word, of the value and the rope part, beside numbers:
     that row is NaN, all others are the same bits as without it.  (fp8 cache: the row's largest element passes over it.)"""
-    inp = parity.to_device(make_custom(3, heads, [333, 70, 200], 3, 100, seed=9, kv_dtype=kv, q_std=1.0, kv_std=0.7))
-    q, bad = inp.q, (1, heads // 2 + 1)
+    lens = [333, 70, 200] + [640] * 78
+    inp = parity.to_device(make_custom(81, heads, lens, 3, 600, seed=9, kv_dtype=kv, q_std=1.0, kv_std=0.7))
+    q, bad, rows = inp.q, (1, heads // 2 + 1), set()
     for hint in (0, 1, 4):
         inp.q = q
         out0, lse0, plan = parity.run_gpu(inp, num_splits_hint=hint)
+        rows.add(plan.head_block // plan.unit_groups)
         for value in (float("nan"), float("inf"), float("-inf")):
             for dim in (16, 17, 511, 512, 575):
                 inp.q = q.clone()
@@ -382,3 +393,4 @@ def test_a_query_element_that_is_no_number(kv, heads):
                 assert torch.isnan(out[bad]).all() and torch.isnan(lse[bad]), (hint, value, dim)
                 out[bad], lse[bad] = out0[bad], lse0[bad]
                 assert torch.equal(out, out0) and torch.equal(lse, lse0), (hint, value, dim)
+    assert rows == _rows_of_a_group(kv, heads)
