@@ -154,7 +154,7 @@ __global__ __launch_bounds__(kWavesN * 64, 1) void decode_narrow_kernel(DecodePa
     // them, so that Q travels with them and is read, and split, while the first tiles are on their way; then each thread turns
     // its own entries into the table's.  us per decode, entries through registers and Q requested with tile 0 -> now: one
     // sequence, 128 heads, 2176 tokens 14.92 -> 14.54 (fp8 15.22 -> 15.02), four of 576 tokens, 16 heads 10.30 -> 10.17
-    // (fp8 11.68 -> 11.32), 128 of 2176, 16 heads 59.3 -> 59.0.
+    // (fp8 11.68 -> 11.32); 128 of 2176, 16 heads, 59, take the time they took.
     // (A segment without tiles reads no entry: its row of the table may hold nothing valid.  Query rows past the last head
     // repeat it; their results are never written.)
     constexpr int kTabPerThread = kMaxSegTiles / (kWavesN * 64);
@@ -583,8 +583,8 @@ __global__ __launch_bounds__(kWavesN * 64, 1) void decode_narrow_kernel(DecodePa
     // Rows of `row` bytes, of which the wave has `data`, `per` of them to an instruction; `put` stages four columns.  The output type is
     // decided outside, and rows leave LDS four requests at a time: a lone wave per SIMD would wait out each (eight at a time:
     // 16 heads 0.8 % slower, half of what they read is not written).  us per decode, one by one -> now: four of 576 tokens, 16 heads
-    // 10.15 -> 10.07 (fp8 11.29 -> 11.13), one sequence, 128 heads 14.58 -> 14.52 (fp8 15.02 -> 14.82), 128 of 2176, 16 heads, fp8
-    // 39.4 -> 39.2.
+    // 10.15 -> 10.07 (fp8 11.29 -> 11.13), one sequence, 128 heads, fp8 15.02 -> 14.82 (bf16, 14.5, and 128 of 2176, 16 heads: nothing
+    // beyond what two runs differ by).
     auto write_rows = [&](auto row_tag, auto put) {
       constexpr int row = decltype(row_tag)::value, data = row / 4, per = 1024 / data, stride = data + 16, kBatch = 4;
       const int sub = lane / (data / 16), off = (lane & (data / 16 - 1)) * 16;
